@@ -3,8 +3,17 @@
 //
 // inc keeps the wrap-around definition { v = x; x = x >= e ? 0 : x + 1 }
 // and uses the AMDGPU builtin that implements it; the others are the
-// compare/capture forms with 32-bit unsigned operands.  All are sequentially
-// consistent at agent scope.
+// compare/capture forms with 32-bit unsigned operands.
+//
+// Every thread makes exactly one atomic operation, so no thread orders two of
+// them: any order that respects each word's own sequence of values is an order
+// of the whole launch, and relaxed agent-scope operations are sequentially
+// consistent here as they stand (the launch's end orders their effects before
+// what follows on the stream).  Sequentially consistent builtins would put an
+// L2 write-back before and an L2 invalidation after every wave's operation:
+// 2^24 adds, one word each in random order, took 5.00 ms that way and take
+// 0.65 ms (the memory-side atomic units' rate; the operands' streams
+// alone would take 68 us).
 #include "device.h"
 #include "runtime.h"
 
@@ -30,21 +39,21 @@ __global__ __launch_bounds__(256) void atomic_apply_kernel(int op, uint32_t* __r
     uint32_t r = 0;
     switch (op) {
         case OMPRT_ATOMIC_ADD:
-            r = __hip_atomic_fetch_add(x, v, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT);
+            r = __hip_atomic_fetch_add(x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             break;
         case OMPRT_ATOMIC_INC:
-            r = __builtin_amdgcn_atomic_inc32(x, v, __ATOMIC_SEQ_CST, "agent");
+            r = __builtin_amdgcn_atomic_inc32(x, v, __ATOMIC_RELAXED, "agent");
             break;
         case OMPRT_ATOMIC_MAX:
-            r = __hip_atomic_fetch_max(x, v, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT);
+            r = __hip_atomic_fetch_max(x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             break;
         case OMPRT_ATOMIC_EXCHANGE:
-            r = __hip_atomic_exchange(x, v, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT);
+            r = __hip_atomic_exchange(x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             break;
         case OMPRT_ATOMIC_CAS: {
             uint32_t expected = v;   // on failure it receives the current value
-            __hip_atomic_compare_exchange_strong(x, &expected, d[i], __ATOMIC_SEQ_CST,
-                                                 __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_compare_exchange_strong(x, &expected, d[i], __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             r = expected;
             break;
         }
