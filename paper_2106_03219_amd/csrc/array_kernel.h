@@ -87,7 +87,7 @@ __device__ __forceinline__ bool elect_last(uint32_t* counter, uint32_t e, int* s
 // (nrows -> ceil(nrows / 2) -> ... -> 1).  Team-wide; ends with a barrier.
 template <class R>
 __device__ __forceinline__ void fold_rows(typename R::Acc* lds, int64_t nrows, int64_t wc) {
-    const int P = blockDim.x;
+    const int P = team_size();
     for (int64_t h = nrows; h > 1;) {
         const int64_t half = (h + 1) / 2;
         const int64_t cnt = (h - half) * wc;
@@ -108,7 +108,7 @@ __device__ __forceinline__ void fold_group(const uint64_t* first, int64_t stride
                                            int64_t wc, uint32_t tag, uint32_t* status,
                                            typename R::Acc* lds) {
     constexpr int NW = sizeof(typename R::Acc) / 4;
-    const int P = blockDim.x, t = threadIdx.x;
+    const int P = team_size(), t = threadIdx.x;
     if (wc * 2 > P) {
         for (int64_t j = t; j < wc; j += P)
             lds[j] = fold_tagged<R>(first + j * NW, stride, count, tag, status);
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(512) void array_reduce_kernel(
     __shared__ int s_last;
 
     const int tid = threadIdx.x;
-    const int P = blockDim.x;
+    const int P = team_size();
     const int c = (int)(blockIdx.x % (unsigned)g.col_tiles);
     const int r = (int)(blockIdx.x / (unsigned)g.col_tiles);
     const int64_t c0 = (int64_t)c * g.W;

@@ -26,7 +26,7 @@ __global__ __launch_bounds__(256) void atomic_apply_kernel(int op, uint32_t* __r
                                                            const uint32_t* __restrict__ d,
                                                            uint32_t* __restrict__ old, int64_t n,
                                                            uint32_t* status) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * team_size() + threadIdx.x;
     if (i >= n) return;
     const uint32_t k = index[i];
     if ((int64_t)k >= n_targets) {

@@ -68,9 +68,7 @@ __device__ __forceinline__ bool process_tile(const SegDesc& sd, const TileDesc& 
     for (int i = 0; i < R::kNA; ++i) acc[i] = R::identity();
     stream_range<DT, OP, VB, U>(static_cast<const typename DType<DT>::S*>(sd.in), td.lo, td.hi,
                                 acc);
-    Acc t = acc[0];
-#pragma unroll
-    for (int i = 1; i < R::kNA; ++i) t = R::combine(t, acc[i]);
+    Acc t = fold_accs<R>(acc);
     Acc* lds = static_cast<Acc*>(lds_raw);
     t = team_reduce<R>(t, lds);
     typename R::Out* x = static_cast<typename R::Out*>(sd.x);

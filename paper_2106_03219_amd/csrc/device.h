@@ -1,5 +1,5 @@
 // device.h -- gfx950 device primitives of the data-parallel core:
-// wave64 cross-lane reduction (DPP + bpermute), the intra-team tree through
+// wave64 cross-lane reduction (DPP + permlane swaps), the intra-team tree through
 // LDS with the team barrier, the cross-team publish / wrap-increment /
 // last-team protocol, compensated (float-float) arithmetic, and the
 // element-type and reduction-operator policies the kernels are templated on.
@@ -18,6 +18,12 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kWave = 64;
 constexpr int kMaxWaves = 1024 / kWave;
+
+// Threads of the team.  Every launch has whole workgroups, so this is the
+// launch's workgroup size, one scalar load (blockDim.x also allows for a
+// smaller last workgroup, which the compiler turned into a vector load of the
+// kernel's arguments at each use, one of them in the cross-team step).
+__device__ __forceinline__ int team_size() { return (int)__builtin_amdgcn_workgroup_size_x(); }
 
 // ---------------------------------------------------------------- cross-lane
 
@@ -43,48 +49,84 @@ __device__ __forceinline__ T dpp_move(const T& x) {
     return y;
 }
 
+// The other half's value: x of lanes 16 (or 32) apart, one copy of the lower
+// row (half) and one of the upper, in every lane (gfx950's permlane swaps: one
+// VALU instruction a word, where a shuffle goes through the LDS crossbar and
+// costs its latency in the middle of a dependent chain).
 template <class T>
-__device__ __forceinline__ T shfl_xor_words(const T& x, int mask) {
-    static_assert(sizeof(T) % 4 == 0, "shuffles move whole dwords");
+struct LanePair {
+    T lo, hi;
+};
+template <bool HALVES, class T>
+__device__ __forceinline__ LanePair<T> lane_pair(const T& x) {
+    static_assert(sizeof(T) % 4 == 0, "lane swaps move whole dwords");
     constexpr int W = sizeof(T) / 4;
-    int w[W];
+    uint32_t w[W], lo[W], hi[W];
     __builtin_memcpy(w, &x, sizeof(T));
 #pragma unroll
-    for (int i = 0; i < W; ++i) w[i] = __shfl_xor(w[i], mask, kWave);
-    T y;
-    __builtin_memcpy(&y, w, sizeof(T));
-    return y;
+    for (int i = 0; i < W; ++i) {
+        const auto r = HALVES ? __builtin_amdgcn_permlane32_swap(w[i], w[i], false, false)
+                              : __builtin_amdgcn_permlane16_swap(w[i], w[i], false, false);
+        lo[i] = r[0];
+        hi[i] = r[1];
+    }
+    LanePair<T> p;
+    __builtin_memcpy(&p.lo, lo, sizeof(T));
+    __builtin_memcpy(&p.hi, hi, sizeof(T));
+    return p;
+}
+
+// 16 lane partials of each row -> 1 (in every lane of the row).
+template <class R>
+__device__ __forceinline__ typename R::Acc row_reduce(typename R::Acc a) {
+    a = R::combine(a, dpp_move<kDppQuadXor1>(a));
+    a = R::combine(a, dpp_move<kDppQuadXor2>(a));
+    a = R::combine(a, dpp_move<kDppRowRor4>(a));
+    return R::combine(a, dpp_move<kDppRowRor8>(a));
 }
 
 // 64 lane partials -> 1 (every lane ends with a full combination; lane 0's
 // value is the one used).  Must be called with all 64 lanes active.
 template <class R>
 __device__ __forceinline__ typename R::Acc wave_reduce(typename R::Acc a) {
-    a = R::combine(a, dpp_move<kDppQuadXor1>(a));
-    a = R::combine(a, dpp_move<kDppQuadXor2>(a));
-    a = R::combine(a, dpp_move<kDppRowRor4>(a));
-    a = R::combine(a, dpp_move<kDppRowRor8>(a));
-    a = R::combine(a, shfl_xor_words(a, 16));
-    a = R::combine(a, shfl_xor_words(a, 32));
-    return a;
+    a = row_reduce<R>(a);
+    LanePair<typename R::Acc> p = lane_pair<false>(a);
+    a = R::combine(p.lo, p.hi);
+    p = lane_pair<true>(a);
+    return R::combine(p.lo, p.hi);
+}
+
+// A lane's NA private accumulators -> 1, pairwise (half the dependent
+// combinations of a chain).
+template <class R, int NA>
+__device__ __forceinline__ typename R::Acc fold_accs(const typename R::Acc (&acc)[NA]) {
+    typename R::Acc t[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) t[i] = acc[i];
+#pragma unroll
+    for (int h = 1; h < NA; h <<= 1)
+#pragma unroll
+        for (int i = 0; i + h < NA; i += 2 * h) t[i] = R::combine(t[i], t[i + h]);
+    return t[0];
 }
 
 // Intra-team tree: each wave reduces, lane 0 of wave w writes LDS slot w,
-// team barrier, wave 0 reduces the slots.  Slots past the wave count are
-// never read (LDS is not zero-initialised).  Result valid in thread 0.
-// blockDim.x must be a multiple of 64.
+// team barrier, the first 16 lanes of wave 0 reduce the (at most 16) slots.
+// Slots past the wave count are never read (LDS is not zero-initialised).
+// Result valid in thread 0.  blockDim.x must be a multiple of 64.
 template <class R>
 __device__ __forceinline__ typename R::Acc team_reduce(typename R::Acc a,
                                                        typename R::Acc* slots) {
+    static_assert(kMaxWaves <= 16, "one row of lanes holds every wave's partial");
     a = wave_reduce<R>(a);
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    const int nw = blockDim.x / kWave;
+    const int nw = team_size() / kWave;
     if (lane == 0) slots[wave] = a;
     __syncthreads();
     if (wave == 0) {
         a = lane < nw ? slots[lane] : R::identity();
-        a = wave_reduce<R>(a);
+        a = row_reduce<R>(a);
     }
     return a;
 }
@@ -164,13 +206,22 @@ __device__ __forceinline__ uint64_t poll_slot_word(const uint64_t* w, uint32_t t
     }
 }
 
+// One participant's partial: the words' loads issue together (a slot word is
+// read past the XCD's L2, and one after another each would wait out that
+// latency); a word that does not carry the tag yet is polled on its own.
 template <class Acc>
 __device__ __forceinline__ Acc collect_tagged(const uint64_t* slot, uint32_t tag,
                                               uint32_t* status) {
     constexpr int W = sizeof(Acc) / 4;
+    uint64_t v[W];
     uint32_t w[W];
 #pragma unroll
-    for (int i = 0; i < W; ++i) w[i] = (uint32_t)poll_slot_word(slot + i, tag, status);
+    for (int i = 0; i < W; ++i) v[i] = load_slot_word(slot + i);
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        if ((uint32_t)(v[i] >> 32) != tag) v[i] = poll_slot_word(slot + i, tag, status);
+        w[i] = (uint32_t)v[i];
+    }
     Acc a;
     __builtin_memcpy(&a, w, sizeof(Acc));
     return a;
@@ -201,13 +252,18 @@ __device__ __forceinline__ typename R::Acc combine_slots(const uint64_t* slots, 
                                                          typename R::Acc* lds) {
     using Acc = typename R::Acc;
     Acc c = R::identity();
-    for (int64_t i = threadIdx.x; i < count; i += blockDim.x)
+    for (int64_t i = threadIdx.x; i < count; i += team_size())
         c = R::combine(c, collect_tagged<Acc>(slots + i * slot_words<Acc>(), tag, status));
     __syncthreads();   // lds may still be read by the previous tree
     return team_reduce<R>(c, lds);
 }
 
 // ---------------------------------------------------------------- float-float
+//
+// Error-free transformations hold for the operations as written: contraction
+// is off in each of them (fusing a product into the sum that should see its
+// rounded value loses the error term; the fp32 product's tree lost 1.4e-6 of
+// a result that way).
 
 template <class F>
 struct Pair {
@@ -219,6 +275,7 @@ using dd_t = Pair<double>;
 // Knuth's TwoSum: s + err == a + b exactly.
 template <class F>
 __device__ __forceinline__ Pair<F> two_sum(F a, F b) {
+#pragma clang fp contract(off)
     const F s = a + b;
     const F bb = s - a;
     const F err = (a - (s - bb)) + (b - bb);
@@ -228,6 +285,7 @@ __device__ __forceinline__ Pair<F> two_sum(F a, F b) {
 // Dekker's Fast2Sum, valid when |a| >= |b| or a == 0.
 template <class F>
 __device__ __forceinline__ Pair<F> fast_two_sum(F a, F b) {
+#pragma clang fp contract(off)
     const F s = a + b;
     const F err = b - (s - a);
     return Pair<F>{s, err};
@@ -237,6 +295,7 @@ __device__ __forceinline__ Pair<F> fast_two_sum(F a, F b) {
 // through TwoSum, then two renormalisations (no cancellation assumption).
 template <class F>
 __device__ __forceinline__ Pair<F> pair_add(Pair<F> x, Pair<F> y) {
+#pragma clang fp contract(off)
     Pair<F> s = two_sum(x.hi, y.hi);
     const Pair<F> t = two_sum(x.lo, y.lo);
     s.lo += t.hi;
@@ -245,12 +304,29 @@ __device__ __forceinline__ Pair<F> pair_add(Pair<F> x, Pair<F> y) {
     return fast_two_sum(s.hi, s.lo);
 }
 
+// Float-float addition for the reduction trees: the high parts' rounding error
+// is exact (TwoSum), the low parts add in the working precision, like
+// comp_add's; nothing is renormalised in between.  A low part is some 2^-24 of
+// the sums it corrects, so its own rounding stays 2^-48 of them (2^-106 in
+// doubles), where the lanes' comp_add chains already are, and finish() rounds
+// hi + lo once.  Level by level only one addition follows another in the high
+// part; pair_add's thirteen made the trees of a sum about 1 us of every launch
+// longer than those of a max (kernel times of fp32 sums, before -> with this and
+// the permlane swaps: 2^10 elements 3.1 -> 2.6 us, 2^20 8.0 -> 6.5, 2^22 10.6 -> 9.4).
+template <class F>
+__device__ __forceinline__ Pair<F> pair_join(Pair<F> x, Pair<F> y) {
+#pragma clang fp contract(off)
+    const Pair<F> s = two_sum(x.hi, y.hi);
+    return Pair<F>{s.hi, s.lo + (x.lo + y.lo)};
+}
+
 // Compensated accumulation of one value: TwoSum captures the rounding error
 // of hi + x exactly whatever the magnitudes (a Kahan/Fast2Sum step would
 // need |hi| >= |x|, which sums crossing zero violate); the errors gather in
 // lo.  The pair represents hi + lo.
 template <class F>
 __device__ __forceinline__ void comp_add(Pair<F>& a, F x) {
+#pragma clang fp contract(off)
     const F s = a.hi + x;
     const F bb = s - a.hi;
     const F err = (a.hi - (s - bb)) + (x - bb);
@@ -423,7 +499,7 @@ struct CompSum {
     static constexpr int kNA = NA;
     static __device__ __forceinline__ Acc identity() { return Acc{F(0), F(0)}; }
     static __device__ __forceinline__ void elem(Acc& a, F v) { comp_add(a, v); }
-    static __device__ __forceinline__ Acc combine(Acc a, Acc b) { return pair_add(a, b); }
+    static __device__ __forceinline__ Acc combine(Acc a, Acc b) { return pair_join(a, b); }
 };
 template <> struct Red<DT_F32, OP_SUM> : CompSum<float, 4> {
     using Out = float;
@@ -536,12 +612,14 @@ struct CompProd {
     static constexpr int kNA = 2;
     static __device__ __forceinline__ Acc identity() { return Acc{F(1), F(0)}; }
     static __device__ __forceinline__ void elem(Acc& a, F v) {
+#pragma clang fp contract(off)
         const F p = a.hi * v;
         const F e = fused_ma(a.hi, v, -p);
         a.lo = fused_ma(a.lo, v, e);
         a.hi = p;
     }
     static __device__ __forceinline__ Acc combine(Acc a, Acc b) {
+#pragma clang fp contract(off)
         const F p = a.hi * b.hi;
         if (!__builtin_isfinite(p)) return Acc{p, F(0)};
         F e = fused_ma(a.hi, b.hi, -p);
@@ -550,6 +628,7 @@ struct CompProd {
         return fast_two_sum(p, e);
     }
     static __device__ __forceinline__ F value(Acc a, F x) {
+#pragma clang fp contract(off)
         const Acc r = combine(Acc{x, F(0)}, a);
         return __builtin_isfinite(r.hi) ? r.hi + r.lo : r.hi;
     }

@@ -40,7 +40,7 @@ __global__ __launch_bounds__(1024) void reduce_exact_kernel(
     const int tid = threadIdx.x;
     const uint32_t epoch = T > 1 ? read_epoch(ct.epoch) : 0u;
     const Range blk = bal_share(n, T, blockIdx.x);
-    const Range own = bal_share(blk.hi - blk.lo, blockDim.x, tid);
+    const Range own = bal_share(blk.hi - blk.lo, team_size(), tid);
     int64_t lo = blk.lo + own.lo;
     const int64_t hi = blk.lo + own.hi;
 
@@ -83,9 +83,7 @@ __global__ __launch_bounds__(1024) void reduce_exact_kernel(
         }
         for (int64_t i = p0 + nv * PER; i < hi; ++i) R::elem(acc[0], D::from(in[i]));
     }
-    Acc t = acc[0];
-#pragma unroll
-    for (int i = 1; i < R::kNA; ++i) t = R::combine(t, acc[i]);
+    Acc t = fold_accs<R>(acc);
     t = team_reduce<R>(t, lds_slots);
     if (T == 1) {
         if (tid == 0) x[0] = R::finish(t, x[0]);

@@ -51,7 +51,7 @@ __device__ __forceinline__ void loop_scale_squares(const float* __restrict__ d,
                                                    float* __restrict__ v, int64_t lo, int64_t hi,
                                                    ff_t& acc) {
     constexpr int U = kGenericUnroll;
-    const int64_t P = blockDim.x;
+    const int64_t P = team_size();
     int64_t i = lo + threadIdx.x;
     for (; i + (U - 1) * P < hi; i += U * P) {
         float a[U], b[U];
@@ -77,7 +77,7 @@ __device__ __forceinline__ void loop_scale_squares(const float* __restrict__ d,
 __device__ __forceinline__ void loop_normalise(float* __restrict__ v, int64_t lo, int64_t hi,
                                                float r) {
     constexpr int U = kGenericUnroll;
-    const int64_t P = blockDim.x;
+    const int64_t P = team_size();
     int64_t i = lo + threadIdx.x;
     for (; i + (U - 1) * P < hi; i += U * P) {
         float b[U];
@@ -114,7 +114,7 @@ __device__ __forceinline__ ff_t gather_partials(const uint64_t* set, int64_t T, 
                                                 uint32_t* status, ff_t* lds) {
     using R = Red<DT_F32, OP_SUM>;
     ff_t c = R::identity();
-    for (int64_t i = threadIdx.x; i < T; i += blockDim.x) {
+    for (int64_t i = threadIdx.x; i < T; i += team_size()) {
         const uint64_t* slot = set + i * kSlotWords;
         ff_t p;
         p.hi = __uint_as_float(gather_word(slot, tag, status));

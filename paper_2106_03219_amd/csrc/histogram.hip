@@ -63,7 +63,7 @@ template <int U, class C>
 __device__ __forceinline__ bool team_histogram(C c, const int32_t* __restrict__ keys, int64_t n,
                                                const BinRange& bins, int64_t row, int64_t rows,
                                                int32_t* __restrict__ hist) {
-    const int tid = threadIdx.x, P = blockDim.x;
+    const int tid = threadIdx.x, P = team_size();
     for (uint32_t b = tid; b < bins.tb; b += P) c.zero(b);
     __syncthreads();
     bool bad = false;
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(1024) void histogram_direct_kernel(const int32_t* _
                                                                 uint32_t* status) {
     __shared__ int s_bad;
     const int tid = threadIdx.x;
-    const int64_t P = blockDim.x;
+    const int64_t P = team_size();
     if (tid == 0) s_bad = 0;
     __syncthreads();
     uint32_t* h = reinterpret_cast<uint32_t*>(hist);
@@ -239,7 +239,7 @@ __device__ __forceinline__ void flag_bad(bool bad, int* s_bad, uint32_t* status)
 template <int U, class F>
 __device__ __forceinline__ void part_keys(const int32_t* __restrict__ keys, int64_t n,
                                           uint32_t bins, F&& f, bool& bad) {
-    const int tid = threadIdx.x, P = blockDim.x;
+    const int tid = threadIdx.x, P = team_size();
     const Range blk = bal_share(n, gridDim.x, blockIdx.x);
     if (blk.lo >= blk.hi) return;
     auto one = [&](int32_t k) {
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(kPartThreads) void hist_part_count_kernel(
     const uint32_t C = part_copies(R);
     const uint32_t copy = (uint32_t)tid % C;
     if (tid == 0) s_bad = 0;
-    for (uint32_t r = tid; r < R * C; r += blockDim.x) rc[r] = 0u;
+    for (uint32_t r = tid; r < R * C; r += team_size()) rc[r] = 0u;
     __syncthreads();
     bool bad = false;
     part_keys<4>(keys, n, bins,
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(kPartThreads) void hist_part_count_kernel(
                  },
                  bad);
     __syncthreads();
-    for (uint32_t r = tid; r < R; r += blockDim.x) {
+    for (uint32_t r = tid; r < R; r += team_size()) {
         uint32_t c = 0;
         for (uint32_t q = 0; q < C; ++q) c += rc[r * C + q];
         cnt[(size_t)r * gridDim.x + blockIdx.x] = c;
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kPartThreads) void hist_part_count_kernel(
 // thread of the workgroup calls it; the workgroup is whole waves.
 __device__ inline int64_t block_scan_inclusive(int64_t v, int64_t* wsum, int64_t* total) {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int nw = (blockDim.x + kWave - 1) / kWave;
+    const int nw = (team_size() + kWave - 1) / kWave;
     int64_t inc = v;
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(1024) void hist_part_scan_range_kernel(const uint32
     __shared__ int64_t wsum[kMaxWaves];
     const size_t r = blockIdx.x;
     int64_t carry = 0;
-    for (uint32_t t0 = 0; t0 < T; t0 += blockDim.x) {
+    for (uint32_t t0 = 0; t0 < T; t0 += team_size()) {
         const uint32_t t = t0 + threadIdx.x;
         const int64_t v = t < T ? cnt[r * T + t] : 0;
         int64_t tot = 0;
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(kPartThreads) void hist_part_scatter_kernel(
     __shared__ uint32_t toff[kPartMaxRanges * kPartCopies + 1];   // exclusive scan of tcnt
     __shared__ uint16_t buf_place[kPartTile];
     __shared__ uint16_t buf_range[kPartTile];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), P = blockDim.x;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), P = team_size();
     const uint32_t copy = (uint32_t)tid % C;
     const uint32_t RC = R * C;
     for (uint32_t r = tid; r < R; r += P)
@@ -476,7 +476,7 @@ __global__ __launch_bounds__(kPartThreads) void hist_part_range_kernel(
     uint32_t S, uint32_t* __restrict__ out) {
     extern __shared__ __align__(16) char arena[];
     lds_u32* h = (lds_u32*)arena;
-    const int tid = threadIdx.x, P = blockDim.x;
+    const int tid = threadIdx.x, P = team_size();
     const uint32_t r = blockIdx.x / S, s = blockIdx.x % S;
     const uint32_t b0 = r << kPartLog2;
     const uint32_t tb = bins - b0 < kPartBins ? bins - b0 : kPartBins;
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(kPartThreads) void hist_part_range_kernel(
 
 __global__ void hist_part_merge_kernel(const uint32_t* __restrict__ partial, uint32_t S,
                                        uint32_t bins, uint32_t* __restrict__ hist) {
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t b = (int64_t)blockIdx.x * team_size() + threadIdx.x;
     if (b >= bins) return;
     uint32_t c = 0;
     for (uint32_t s = 0; s < S; ++s) c += partial[(size_t)s * bins + b];
@@ -569,7 +569,7 @@ __global__ __launch_bounds__(kPartThreads) void hist_tsort_scatter_kernel(
     __shared__ uint32_t wtot[kTsortMaxRanges * kPartCopies / kWave];
     __shared__ __align__(16) uint16_t buf[kTsortSlot];
     __shared__ int s_bad;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), P = blockDim.x;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), P = team_size();
     const uint32_t copy = (uint32_t)tid % C;
     const uint32_t RC = R * C;
     if (tid == 0) s_bad = 0;
@@ -678,7 +678,7 @@ __global__ __launch_bounds__(kPartThreads) void hist_tsort_range_kernel(
     uint32_t R, uint32_t bins, uint32_t S, uint32_t* __restrict__ out) {
     extern __shared__ __align__(16) char arena[];
     lds_u32* h = (lds_u32*)arena;
-    const int tid = threadIdx.x, lane = tid & (SW - 1), P = blockDim.x;
+    const int tid = threadIdx.x, lane = tid & (SW - 1), P = team_size();
     const int64_t W = P / SW, wave = tid / SW;
     const uint32_t r = blockIdx.x / S, s = blockIdx.x % S;
     const uint32_t b0 = r << kPartLog2;

@@ -76,7 +76,7 @@ constexpr int64_t kRotMinLines = 16;
 
 __device__ __forceinline__ int64_t line_rot(int64_t np) {
     if (np < kRotMinLines) return 0;
-    const uint32_t g = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
+    const uint32_t g = blockIdx.x * (team_size() / kWave) + threadIdx.x / kWave;
     return np <= 0x7fffffff ? (int64_t)((g * 11u) % (uint32_t)np) : (int64_t)(g * 11u);
 }
 

@@ -65,7 +65,7 @@ struct LocRed {
 
 template <int DT, int OP, int U>
 __global__ __launch_bounds__(1024) void reduce_loc_kernel(const typename DType<DT>::S* __restrict__ in,
-                                                          int64_t n,
+                                                          BalSplit split,
                                                           typename DType<DT>::S* __restrict__ xval,
                                                           int64_t* __restrict__ xidx,
                                                           CrossTeam ct) {
@@ -80,9 +80,9 @@ __global__ __launch_bounds__(1024) void reduce_loc_kernel(const typename DType<D
 
     const int64_t T = gridDim.x;
     const int tid = threadIdx.x;
-    const int P = blockDim.x;
+    const int P = team_size();
     const uint32_t epoch = T > 1 ? read_epoch(ct.epoch) : 0u;
-    const Range blk = bal_share(n, T, blockIdx.x);
+    const Range blk = split.share(blockIdx.x);
     // one pair per element slot of a vector: independent compare chains; every
     // slot still meets its elements in increasing position
     Acc acc[PER];
@@ -149,7 +149,7 @@ static void launch_loc(const void* in, int64_t n, void* xval, int64_t* xidx, int
                        int threads, const CrossTeam& ct, hipStream_t stream) {
     using S = typename DType<DT>::S;
     hipLaunchKernelGGL((reduce_loc_kernel<DT, OP, U>), dim3(teams), dim3(threads), 0, stream,
-                       static_cast<const S*>(in), n, static_cast<S*>(xval), xidx, ct);
+                       static_cast<const S*>(in), bal_split(n, teams), static_cast<S*>(xval), xidx, ct);
 }
 
 template <int DT, int OP>

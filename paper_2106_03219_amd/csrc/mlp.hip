@@ -21,7 +21,7 @@ namespace omprt {
 __global__ void mlp_linear_kernel(const float* __restrict__ X, const float* __restrict__ W,
                                   const float* __restrict__ b, float* __restrict__ Y, int B,
                                   int in, int out, int relu) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t idx = (int64_t)blockIdx.x * team_size() + threadIdx.x;
     if (idx >= (int64_t)B * out) return;
     const int r = (int)(idx / out), j = (int)(idx % out);
     float s = b[j];
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) void mlp_softmax_ce_kernel(const float* __rest
                                                              float* __restrict__ dZ,
                                                              float* __restrict__ row_loss, int B,
                                                              int K) {
-    const int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+    const int64_t r = ((int64_t)blockIdx.x * team_size() + threadIdx.x) / kWave;
     const int lane = threadIdx.x & (kWave - 1);
     if (r >= B) return;   // whole waves
     const float* z = Z + r * K;
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void mlp_weight_grad_kernel(const float* __res
                                                               float* __restrict__ GW,
                                                               float* __restrict__ gb, int B,
                                                               int out, int in) {
-    const int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+    const int64_t w = ((int64_t)blockIdx.x * team_size() + threadIdx.x) / kWave;
     const int lane = threadIdx.x & (kWave - 1);
     if (w >= (int64_t)out * (in + 1)) return;   // whole waves
     const int j = (int)(w / (in + 1)), i = (int)(w % (in + 1));
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(256) void mlp_weight_grad_kernel(const float* __res
 __global__ void mlp_backprop_kernel(const float* __restrict__ D, const float* __restrict__ W,
                                     const float* __restrict__ Aprev, float* __restrict__ Dprev,
                                     int B, int out, int in) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t idx = (int64_t)blockIdx.x * team_size() + threadIdx.x;
     if (idx >= (int64_t)B * in) return;
     const int r = (int)(idx / in), i = (int)(idx % in);
     float s = 0.0f;
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(256) void mlp_mean_kernel(const float* __restrict__
                                                        float* __restrict__ out) {
     __shared__ ff_t slots[kMaxWaves];
     ff_t acc{0.0f, 0.0f};
-    for (int i = threadIdx.x; i < B; i += blockDim.x) comp_add(acc, v[i]);
+    for (int i = threadIdx.x; i < B; i += team_size()) comp_add(acc, v[i]);
     acc = team_reduce<MeanPolicy>(acc, slots);
     if (threadIdx.x == 0) out[0] = (acc.hi + acc.lo) / (float)B;
 }
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256) void mlp_mean_kernel(const float* __restrict__
 __global__ void mlp_adam_kernel(float* __restrict__ w, float* __restrict__ m,
                                 float* __restrict__ v, const float* __restrict__ g, int64_t n,
                                 float lr, float b1, float b2, float eps, float c1, float c2) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * team_size() + threadIdx.x;
     if (i >= n) return;
     const float gi = g[i];
     const float mi = b1 * m[i] + (1.0f - b1) * gi;
@@ -142,7 +142,7 @@ __global__ void mlp_adam_counted_kernel(float* __restrict__ w, float* __restrict
                                         float* __restrict__ v, const float* __restrict__ g,
                                         int64_t n, const int32_t* __restrict__ step, float lr,
                                         float b1, float b2, float eps) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * team_size() + threadIdx.x;
     if (i >= n) return;
     const double t = (double)step[0] + 1.0;
     const float c1 = (float)(1.0 - pow((double)b1, t));

@@ -40,7 +40,8 @@ struct MultiRed {
 
 template <int DT, int MASK, int U>
 __global__ __launch_bounds__(1024) void reduce_multi_kernel(
-    const typename DType<DT>::S* __restrict__ in, int64_t n, typename Red<DT, OP_SUM>::Out* x_sum,
+    const typename DType<DT>::S* __restrict__ in, BalSplit split,
+    typename Red<DT, OP_SUM>::Out* x_sum,
     typename Red<DT, OP_MAX>::Out* x_max, typename Red<DT, OP_MIN>::Out* x_min, CrossTeam ct) {
     using R = MultiRed<DT, MASK>;
     using Acc = typename R::Acc;
@@ -48,14 +49,12 @@ __global__ __launch_bounds__(1024) void reduce_multi_kernel(
     __shared__ int s_last;
     const int64_t T = gridDim.x;
     const uint32_t epoch = T > 1 ? read_epoch(ct.epoch) : 0u;
-    const Range blk = bal_share(n, T, blockIdx.x);
+    const Range blk = split.share(blockIdx.x);
     Acc acc[R::kNA];
 #pragma unroll
     for (int i = 0; i < R::kNA; ++i) acc[i] = R::identity();
     stream_range_with<R, DT, 16, U>(in, blk.lo, blk.hi, acc);
-    Acc t = acc[0];
-#pragma unroll
-    for (int i = 1; i < R::kNA; ++i) t = R::combine(t, acc[i]);
+    Acc t = fold_accs<R>(acc);
     t = team_reduce<R>(t, lds_slots);
     Acc c = t;
     if (T > 1) {
@@ -86,7 +85,7 @@ template <int DT, int MASK, int U>
 static void launch_multi(const void* in, int64_t n, void* const* x, int teams, int threads,
                          const CrossTeam& ct, hipStream_t stream) {
     hipLaunchKernelGGL((reduce_multi_kernel<DT, MASK, U>), dim3(teams), dim3(threads), 0, stream,
-                       static_cast<const typename DType<DT>::S*>(in), n,
+                       static_cast<const typename DType<DT>::S*>(in), bal_split(n, teams),
                        static_cast<typename Red<DT, OP_SUM>::Out*>(x[0]),
                        static_cast<typename Red<DT, OP_MAX>::Out*>(x[1]),
                        static_cast<typename Red<DT, OP_MIN>::Out*>(x[2]), ct);

@@ -14,7 +14,7 @@ namespace omprt {
 
 template <int DT, int OP, int VB, int U>
 __global__ __launch_bounds__(1024) void reduce_kernel(
-    const typename DType<DT>::S* __restrict__ in, int64_t n,
+    const typename DType<DT>::S* __restrict__ in, BalSplit split,
     typename Red<DT, OP>::Out* __restrict__ x, CrossTeam ct) {
     using R = Red<DT, OP>;
     using Acc = typename R::Acc;
@@ -25,7 +25,11 @@ __global__ __launch_bounds__(1024) void reduce_kernel(
     const int64_t T = gridDim.x;
     const int tid = threadIdx.x;
     const uint32_t epoch = T > 1 ? read_epoch(ct.epoch) : 0u;
-    const Range blk = bal_share(n, T, blockIdx.x);
+    const Range blk = split.share(blockIdx.x);
+    // x is read where its latency overlaps other loads (only the finishing
+    // team touches it)
+    typename R::Out x0{};
+    if (T == 1 && tid == 0) x0 = x[0];
 
     Acc acc[R::kNA];
 #pragma unroll
@@ -33,22 +37,21 @@ __global__ __launch_bounds__(1024) void reduce_kernel(
 
     stream_range<DT, OP, VB, U>(in, blk.lo, blk.hi, acc);
 
-    Acc t = acc[0];
-#pragma unroll
-    for (int i = 1; i < R::kNA; ++i) t = R::combine(t, acc[i]);
+    Acc t = fold_accs<R>(acc);
     t = team_reduce<R>(t, lds_slots);
 
     if (T == 1) {   // single team: no cross-team step
-        if (tid == 0) x[0] = R::finish(t, x[0]);
+        if (tid == 0) x[0] = R::finish(t, x0);
         return;
     }
     const uint32_t tag = launch_tag(epoch);
     if (!publish_and_elect(t, ct.slots + (size_t)blockIdx.x * kSlotWords, ct.counter,
                            (uint32_t)(T - 1), tag, &s_last))
         return;
+    if (tid == 0) x0 = x[0];
     const Acc c = combine_slots<R>(ct.slots, T, tag, ct.status, lds_slots);
     if (tid == 0) {
-        x[0] = R::finish(c, x[0]);
+        x[0] = R::finish(c, x0);
         advance_epoch(ct.epoch, epoch);
     }
 }
@@ -64,7 +67,7 @@ static hipError_t launch_one(const void* in, int64_t n, void* x, int teams, int 
                              const CrossTeamArgs& ct, hipStream_t stream) {
     using R = Red<DT, OP>;
     hipLaunchKernelGGL((reduce_kernel<DT, OP, VB, U>), dim3(teams), dim3(threads), 0, stream,
-                       static_cast<const typename DType<DT>::S*>(in), n,
+                       static_cast<const typename DType<DT>::S*>(in), bal_split(n, teams),
                        static_cast<typename R::Out*>(x), to_device_ct(ct));
     return hipGetLastError();
 }

@@ -27,6 +27,18 @@ OMPRT_HD Range bal_share(int64_t m, int64_t p, int64_t t) {
     return Range{lo, lo + q + (t < r ? 1 : 0)};
 }
 
+// The same split with its quotient and remainder taken once (by the host, for a
+// kernel whose every thread needs its team's share: a 64-bit division is some
+// hundred dependent scalar instructions on the device).
+struct BalSplit {
+    int64_t q, r;
+    OMPRT_HD Range share(int64_t t) const {
+        const int64_t lo = t * q + (t < r ? t : r);
+        return Range{lo, lo + q + (t < r ? 1 : 0)};
+    }
+};
+OMPRT_HD BalSplit bal_split(int64_t m, int64_t p) { return BalSplit{m / p, m % p}; }
+
 // Number of chunks of size c needed to cover m > 0 iterations.
 OMPRT_HD int64_t ceil_div_pos(int64_t m, int64_t c) { return (m - 1) / c + 1; }
 

@@ -65,7 +65,7 @@ __device__ __forceinline__ void stream_range_with(const typename DType<DT>::S* _
     constexpr int PER = L::PER;   // elements per vector
     if (a >= b) return;
     const int tid = threadIdx.x;
-    const int P = blockDim.x;
+    const int P = team_size();
     const uintptr_t mis = reinterpret_cast<uintptr_t>(in + a) & (VB - 1);
     int64_t head = (int64_t)(((VB - mis) & (VB - 1)) / sizeof(S));
     if (head > b - a) head = b - a;

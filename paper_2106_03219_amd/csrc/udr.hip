@@ -105,7 +105,7 @@ extern "C" __global__ __launch_bounds__(1024) void omprt_udr_kernel(
     __shared__ R::Acc lds[kMaxWaves];
     __shared__ int s_last;
     const int64_t T = gridDim.x;
-    const int64_t P = blockDim.x;
+    const int64_t P = team_size();
     const int64_t tid = threadIdx.x;
     const uint32_t epoch = T > 1 ? read_epoch(ct.epoch) : 0u;
     const Range blk = bal_share(n, T, blockIdx.x);
