@@ -40,161 +40,290 @@
 
 namespace omprt {
 
-enum { WORK_EXIT = 0, WORK_SCALE_SQUARES = 1, WORK_NORMALISE = 2 };
+// The work descriptor: the loops the team runs next.  The normalising loop of
+// one step and the scaling loop of the next have no sequential code between
+// them that needs either's result and put every element on the same thread, so
+// they are handed out together (two worksharing loops of one parallel region,
+// the first nowait): a step then has one hand-off and one join.
+enum { WORK_SCALE = 0, WORK_NORMALISE_SCALE = 1, WORK_NORMALISE_EXIT = 2 };
 
 constexpr int kGenericUnroll = 8;   // loads in flight per lane and array
 // Teams of the distributed form: each team reads every team's partial once a
-// step, so the all-gather grows as teams^2 (512 teams: 4 MiB of L2 reads).
+// step, so the all-gather grows as teams^2 (512 teams: 4 MiB of reads).
 constexpr int kMaxGenericTeams = 512;
+constexpr int kGatherWords = 2;     // 64-bit words of a team's partial
+// Copies of every partial, each read by every kGatherCopies-th team: all teams
+// poll at the same time, and one copy of 256 partials is 4 KiB on a few memory
+// channels that would serve every team's reads.
+constexpr int kGatherCopies = 8;
 
-__device__ __forceinline__ void loop_scale_squares(const float* __restrict__ d,
-                                                   float* __restrict__ v, int64_t lo, int64_t hi,
-                                                   ff_t& acc) {
-    constexpr int U = kGenericUnroll;
-    const int64_t P = team_size();
-    int64_t i = lo + threadIdx.x;
-    for (; i + (U - 1) * P < hi; i += U * P) {
-        float a[U], b[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            a[u] = d[i + u * P];
-            b[u] = v[i + u * P];
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float w = a[u] * b[u];
-            v[i + u * P] = w;
-            comp_add(acc, w * w);
-        }
-    }
-    for (; i < hi; i += P) {
-        const float w = d[i] * v[i];
-        v[i] = w;
-        comp_add(acc, w * w);
-    }
+__device__ __forceinline__ float scaled_square(float d, float v, ff_t& acc) {
+    const float w = d * v;
+    comp_add(acc, w * w);
+    return w;
 }
 
-__device__ __forceinline__ void loop_normalise(float* __restrict__ v, int64_t lo, int64_t hi,
-                                               float r) {
-    constexpr int U = kGenericUnroll;
-    const int64_t P = team_size();
-    int64_t i = lo + threadIdx.x;
-    for (; i + (U - 1) * P < hi; i += U * P) {
-        float b[U];
+// The calling thread's iterations lo + t, lo + t + P, ... of both loops, with v
+// and d in memory: the loops' pair reads d and v and writes v, 12 bytes an
+// element and step.
+struct MemoryShare {
+    const float* __restrict__ d;
+    float* __restrict__ v;
+    int64_t i0, hi, P;
+    __device__ __forceinline__ MemoryShare(const float* d_, float* v_, const Range& blk)
+        : d(d_), v(v_), i0(blk.lo + threadIdx.x), hi(blk.hi), P(team_size()) {}
+    // v = w = d * (NORMALISE ? v * r : v), acc += w * w
+    template <bool NORMALISE>
+    __device__ __forceinline__ void scale(float r, ff_t& acc) {
+        constexpr int U = kGenericUnroll;
+        int64_t i = i0;
+        for (; i + (U - 1) * P < hi; i += U * P) {
+            float a[U], b[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) b[u] = v[i + u * P];
+            for (int u = 0; u < U; ++u) {
+                a[u] = d[i + u * P];
+                b[u] = v[i + u * P];
+            }
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[i + u * P] = b[u] * r;
-    }
-    for (; i < hi; i += P) v[i] *= r;
-}
-
-// Poll one slot word for `tag`, bounded like poll_slot_word; every 256 polls
-// it also looks at *status, so once one poll of the launch has timed out the
-// others give up at once instead of each waiting out its own limit.
-__device__ __forceinline__ uint32_t gather_word(const uint64_t* w, uint32_t tag, uint32_t* status) {
-    for (uint32_t polls = 1;; ++polls) {
-        const uint64_t x = load_slot_word(w);
-        if ((uint32_t)(x >> 32) == tag) return (uint32_t)x;
-        if (polls >= kPollLimit) {
-            __hip_atomic_fetch_or(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return (uint32_t)x;
+            for (int u = 0; u < U; ++u)
+                v[i + u * P] = scaled_square(a[u], NORMALISE ? b[u] * r : b[u], acc);
         }
-        if ((polls & 255) == 0 &&
-            (__hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u))
-            return (uint32_t)x;
-        __builtin_amdgcn_s_sleep(1);
+        for (; i < hi; i += P) v[i] = scaled_square(d[i], NORMALISE ? v[i] * r : v[i], acc);
     }
-}
+    __device__ __forceinline__ void finish(float r) {
+        constexpr int U = kGenericUnroll;
+        int64_t i = i0;
+        for (; i + (U - 1) * P < hi; i += U * P) {
+            float b[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) b[u] = v[i + u * P];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[i + u * P] = b[u] * r;
+        }
+        for (; i < hi; i += P) v[i] *= r;
+    }
+};
 
-// All-gather: every team's partial of this step, combined in team order
-// (thread t takes teams t, t + P, ...; then the team tree).  Result valid in
-// thread 0.
-__device__ __forceinline__ ff_t gather_partials(const uint64_t* set, int64_t T, uint32_t tag,
-                                                uint32_t* status, ff_t* lds) {
+// The same with the thread's elements (at most E) in registers for the whole
+// region: d and v are read once, v is written once, and a step touches no
+// memory but the all-gather's slots.  Elements past the share are zeros, which
+// add exactly nothing to the sum (an infinite or NaN r makes them NaN, but then
+// every real element of the loop is infinite or NaN and the sum NaN as well).
+template <int E>
+struct RegisterShare {
+    float d[E], v[E];
+    float* __restrict__ out;   // the block's first element
+    int len, P;                // the block has at most E * P elements
+    __device__ __forceinline__ RegisterShare(const float* __restrict__ d_, float* __restrict__ v_,
+                                             const Range& blk)
+        : out(v_ + blk.lo), len((int)(blk.hi - blk.lo)), P(team_size()) {
+        const float* __restrict__ in = d_ + blk.lo;
+        // an empty block reads its neighbour's element before it (blk.lo <= n)
+        const int none = len > 0 ? 0 : -1;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int i = (int)threadIdx.x + e * P;
+            const float a = in[i < len ? i : none], b = out[i < len ? i : none];
+            d[e] = i < len ? a : 0.0f;
+            v[e] = i < len ? b : 0.0f;
+        }
+    }
+    template <bool NORMALISE>
+    __device__ __forceinline__ void scale(float r, ff_t& acc) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            v[e] = scaled_square(d[e], NORMALISE ? v[e] * r : v[e], acc);
+            // keeps the products of later elements from being formed (and held
+            // in registers) ahead of the sum's chain
+            if (e % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __device__ __forceinline__ void finish(float r) {
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));   // the offsets are formed here, not kept through the region
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int i = t + e * P;
+            if (i < len) out[i] = v[e] * r;
+        }
+    }
+};
+
+// All-gather by one wave: every team's partial of this step, combined in team
+// order (lane l takes teams l, l + 64, ..., then the wave's tree).  The words
+// of up to kBatch teams load together, again and again until all of them carry
+// the tag (a word polled after another would wait out its own latency).
+// Bounded like poll_slot_word; every 256 polls it also looks at *status, so
+// once one poll of the launch has timed out the others give up at once instead
+// of each waiting out its own limit.  Result in every lane.
+__device__ __forceinline__ ff_t gather_partials(const uint64_t* set, int T, uint32_t tag,
+                                                uint32_t* status) {
     using R = Red<DT_F32, OP_SUM>;
+    constexpr int kBatch = 4;
     ff_t c = R::identity();
-    for (int64_t i = threadIdx.x; i < T; i += team_size()) {
-        const uint64_t* slot = set + i * kSlotWords;
-        ff_t p;
-        p.hi = __uint_as_float(gather_word(slot, tag, status));
-        p.lo = __uint_as_float(gather_word(slot + 1, tag, status));
-        c = R::combine(c, p);
+    for (int t0 = threadIdx.x & (kWave - 1); t0 < T; t0 += kBatch * kWave) {
+        uint64_t w[kBatch][kGatherWords];
+        for (uint32_t polls = 1;; ++polls) {
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) {
+                const int t = t0 + b * kWave < T ? t0 + b * kWave : t0;
+#pragma unroll
+                for (int i = 0; i < kGatherWords; ++i)
+                    w[b][i] = load_slot_word(set + (size_t)t * kGatherWords + i);
+            }
+            bool all = true;
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b)
+#pragma unroll
+                for (int i = 0; i < kGatherWords; ++i) all = all && (uint32_t)(w[b][i] >> 32) == tag;
+            if (all) break;
+            if (polls >= kPollLimit) {
+                __hip_atomic_fetch_or(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
+            if ((polls & 255) == 0 &&
+                (__hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u))
+                break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b)
+            if (t0 + b * kWave < T)
+                c = R::combine(c, ff_t{__uint_as_float((uint32_t)w[b][0]),
+                                       __uint_as_float((uint32_t)w[b][1])});
     }
-    __syncthreads();   // lds may still be read by the previous tree
-    return team_reduce<R>(c, lds);
+    return wave_reduce<R>(c);
 }
 
-template <bool TEAMS>
-__global__ __launch_bounds__(1024) void generic_power_kernel(const float* __restrict__ d,
+// Workspace slots (of kSlotWords words) the two sets take per team.
+constexpr int kGenericSlots = 2 * kGatherCopies * kGatherWords / kSlotWords;
+
+// SHARE: MemoryShare or RegisterShare<E>; at most MAXP threads a team, at least
+// MINW waves a SIMD (8: two teams of 1024 threads a CU, which the documented
+// limit of 512 teams needs).
+template <bool TEAMS, class SHARE, int MAXP, int MINW>
+__global__ __launch_bounds__(MAXP, MINW) void generic_power_kernel(const float* __restrict__ d,
                                                              float* __restrict__ v, int64_t n,
                                                              int iters, float* __restrict__ lambda,
                                                              CrossTeam ct) {
     using R = Red<DT_F32, OP_SUM>;
-    __shared__ int s_work;       // the work descriptor: which loop runs next
-    __shared__ float s_scale;    // and its argument
+    __shared__ int s_work;       // the work descriptor: which loops run next
+    __shared__ float s_scale;    // and their argument
     __shared__ ff_t s_red[kMaxWaves];
-    __shared__ ff_t s_sum;       // result of the last reduction loop
     const int tid = threadIdx.x;
     const int64_t T = gridDim.x;
     const Range blk = TEAMS ? bal_share(n, T, blockIdx.x) : Range{0, n};
     const uint32_t epoch = TEAMS ? read_epoch(ct.epoch) : 0u;
-    int k = 0;   // steps completed (every thread follows the descriptors)
-    // the main thread's sequential state (only thread 0's copy is used)
-    int last = WORK_EXIT;
-    float s = 0.0f;
-    for (;;) {
+    SHARE share(d, v, blk);
+    float s = 0.0f;   // the main thread's sequential state (only thread 0's copy is used)
+    for (int k = 0;; ++k) {   // k: steps whose sum is complete
         if (tid == 0) {   // sequential code
-            if (last == WORK_SCALE_SQUARES) {
-                s = s_sum.hi + s_sum.lo;
-                s_scale = 1.0f / sqrtf(s);
-                s_work = WORK_NORMALISE;
-            } else if (k == iters) {
-                if (blockIdx.x == 0) lambda[0] = sqrtf(s);
-                s_work = WORK_EXIT;
+            if (k == 0) {
+                s_work = WORK_SCALE;
             } else {
-                s_work = WORK_SCALE_SQUARES;
+                s_scale = 1.0f / sqrtf(s);
+                s_work = k == iters ? WORK_NORMALISE_EXIT : WORK_NORMALISE_SCALE;
             }
         }
         __syncthreads();   // the team picks up the work descriptor
         const int work = s_work;
-        if (work == WORK_EXIT) break;
-        if (work == WORK_SCALE_SQUARES) {
-            ff_t acc = R::identity();
-            loop_scale_squares(d, v, blk.lo, blk.hi, acc);
-            acc = team_reduce<R>(acc, s_red);
-            if constexpr (TEAMS) {
-                const uint32_t tag = launch_tag(epoch + (uint32_t)k);
-                uint64_t* set = ct.slots + (size_t)(k & 1) * T * kSlotWords;
-                if (tid == 0) publish_tagged(acc, set + (size_t)blockIdx.x * kSlotWords, tag);
-                acc = gather_partials(set, T, tag, ct.status, s_red);
-            }
-            if (tid == 0) s_sum = acc;
-        } else {
-            loop_normalise(v, blk.lo, blk.hi, s_scale);
-            ++k;
+        ff_t acc = R::identity();
+        if (work == WORK_NORMALISE_EXIT) {
+            share.finish(s_scale);
+            break;
         }
-        __syncthreads();   // join: the loop is complete and its writes visible
-        last = work;
+        if (work == WORK_SCALE)
+            share.template scale<false>(1.0f, acc);
+        else
+            share.template scale<true>(s_scale, acc);
+        // The tree's barrier is the join: every thread has read the descriptor
+        // and finished its loops.  Thread 0 has the sum; the slots are written
+        // again only after the next hand-off, which thread 0's wave reaches
+        // last.
+        acc = team_reduce<R>(acc, s_red);
+        if constexpr (TEAMS) {
+            if (tid < kWave) {
+                const uint32_t tag = launch_tag(epoch + (uint32_t)k);
+                uint64_t* set = ct.slots + (size_t)(k & 1) * T * (kGatherCopies * kGatherWords);
+                acc.hi = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(acc.hi)));
+                acc.lo = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(acc.lo)));
+                if (tid < kGatherCopies)
+                    publish_tagged(acc, set + ((size_t)tid * T + blockIdx.x) * kGatherWords, tag);
+                acc = gather_partials(set + (size_t)(blockIdx.x % kGatherCopies) * T * kGatherWords,
+                                      (int)T, tag, ct.status);
+            }
+        }
+        if (tid == 0) s = acc.hi + acc.lo;
     }
-    // Every team read the epoch before publishing its first partial, and team
-    // 0 has read every team's last partial: the next launch may take new tags.
-    if (TEAMS && blockIdx.x == 0 && tid == 0)
-        __hip_atomic_store(ct.epoch, epoch + (uint32_t)iters, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
+    if (blockIdx.x == 0 && tid == 0) {
+        lambda[0] = sqrtf(s);
+        // Every team read the epoch before publishing its first partial, and team
+        // 0 has read every team's last partial: the next launch may take new tags.
+        if (TEAMS)
+            __hip_atomic_store(ct.epoch, epoch + (uint32_t)iters, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
-// Teams of `threads` that can be resident at once on the current device.
-static omprt_status coresident_teams(int threads, int* out) {
+// The kernel variants: elements a thread holds in registers (0: in memory) and
+// the largest team.  32 elements of d and of v leave room for the 16 waves of a
+// 1024-thread team a CU (128 registers a lane), 64 for 512 threads, 128 for 256
+// (512 registers a lane).
+struct GenericVariant {
+    int elems, max_threads;
+    const void* one;    // one team
+    const void* many;   // co-resident teams
+};
+template <class SHARE, int MAXP, int MINW>
+static GenericVariant generic_variant(int elems) {
+    return GenericVariant{
+        elems, MAXP, reinterpret_cast<const void*>(&generic_power_kernel<false, SHARE, MAXP, MINW>),
+        reinterpret_cast<const void*>(&generic_power_kernel<true, SHARE, MAXP, MINW>)};
+}
+static const GenericVariant* generic_variants(int* count) {
+    static const GenericVariant v[] = {
+        generic_variant<RegisterShare<4>, 1024, 8>(4),
+        generic_variant<RegisterShare<8>, 1024, 8>(8),
+        generic_variant<RegisterShare<16>, 1024, 4>(16),
+        generic_variant<RegisterShare<32>, 1024, 4>(32),
+        generic_variant<RegisterShare<64>, 512, 2>(64),
+        generic_variant<RegisterShare<128>, 256, 1>(128),
+        generic_variant<MemoryShare, 1024, 8>(0)};
+    *count = (int)(sizeof(v) / sizeof(v[0]));
+    return v;
+}
+
+// Teams of `threads` of the variant that can be resident at once on the
+// current device.
+static omprt_status coresident_teams(const GenericVariant& v, int threads, int* out) {
     int dev = 0;
     OMPRT_HIP(hipGetDevice(&dev));
     int coop = 0;
     OMPRT_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
     if (!coop) return fail(OMPRT_ERR_UNSUPPORTED, "device %d has no cooperative launch", dev);
     int per_cu = 0;
-    OMPRT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per_cu, reinterpret_cast<const void*>(&generic_power_kernel<true>), threads, 0));
+    OMPRT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, v.many, threads, 0));
     *out = per_cu * device_cus();
+    return OMPRT_OK;
+}
+
+// The variant for n elements over teams x threads: the smallest that holds a
+// thread's share in registers and keeps the teams resident, else the one that
+// keeps them in memory (whose residency limits the team count: the registers
+// are never why a launch is refused).
+static omprt_status pick_variant(int64_t n, int teams, int threads, const GenericVariant** out) {
+    int count = 0;
+    const GenericVariant* v = generic_variants(&count);
+    const int64_t share = ((n + teams - 1) / teams + threads - 1) / threads;
+    for (int i = 0; i < count; ++i) {
+        *out = &v[i];
+        if (v[i].elems == 0) break;   // the last one takes every shape
+        if (share > v[i].elems || threads > v[i].max_threads) continue;
+        if (teams == 1) break;
+        int resident = 0;
+        if (omprt_status st = coresident_teams(v[i], threads, &resident)) return st;
+        if (teams <= resident) break;
+    }
     return OMPRT_OK;
 }
 
@@ -209,11 +338,17 @@ extern "C" omprt_status omprt_generic_power(const float* d_diag, float* d_v, int
         return fail(OMPRT_ERR_INVALID, "n = %lld outside 1..2^32", (long long)n);
     if (iters < 1) return fail(OMPRT_ERR_INVALID, "iters %d < 1", iters);
     if (teams < 0) return fail(OMPRT_ERR_INVALID, "teams %d < 0", teams);
-    // default shape (measured at 2^10..2^20 elements, 100 steps): one team of
-    // 512 threads while the loops are short, else teams of 256 threads, one
-    // per 2048 elements, up to one per CU
+    // default shape (measured at 2^10..2^23 elements, 100 steps, us a step): one
+    // team of 512 threads while its loops are shorter than an all-gather (2^15:
+    // 1.95 against 2.25 with 8 teams), else teams of 512 threads with 16
+    // elements a thread up to half the CUs (2^16: 2.26 with 8 teams, 2.40 with
+    // 64 of 256; 2^20: 2.71 with 128 teams, 3.12 with 256 of 256) and one a CU
+    // past that (2^21: 3.14; 2^23: 4.15 against 16.4 with 128, whose share no
+    // longer fits the registers), of 256 threads once the loops stream (2^24:
+    // 30.9 against 34.7)
     const bool auto_threads = threads == 0;
-    if (auto_threads) threads = (teams == 1 || (teams == 0 && n <= 8192)) ? 512 : 256;
+    const int64_t cus = device_cus();
+    if (auto_threads) threads = teams > 1 || (teams == 0 && n > cus * 512 * 64) ? 256 : 512;
     if (threads < 64 || threads > 1024 || threads % 64)
         return fail(OMPRT_ERR_INVALID, "threads %d: 64..1024, a multiple of 64", threads);
     if (!d_diag || !d_v || !d_lambda) return fail(OMPRT_ERR_INVALID, "NULL pointer");
@@ -226,35 +361,41 @@ extern "C" omprt_status omprt_generic_power(const float* d_diag, float* d_v, int
     if ((lb >= vb && lb < vb + nb) || (lb >= db && lb < db + nb))
         return fail(OMPRT_ERR_INVALID, "lambda lies inside diag or v");
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const int64_t want = teams != 0  ? teams
-                         : auto_threads ? (n <= 8192 ? 1 : n / 2048)
-                                        : n / ((int64_t)threads * 8);
+    int64_t want = teams;
+    if (teams == 0) {
+        if (auto_threads)
+            want = n <= 32768 ? 1 : n / 8192 <= cus / 2 ? n / 8192 : cus;
+        else
+            want = n / ((int64_t)threads * 8);
+    }
     if (want <= 1) {
         teams = 1;
     } else {
         int maxco = 0;
-        if (omprt_status st = coresident_teams(threads, &maxco)) return st;
+        int count = 0;
+        const GenericVariant* memory = generic_variants(&count) + (count - 1);
+        if (omprt_status st = coresident_teams(*memory, threads, &maxco)) return st;
         const int limit = std::min(maxco, kMaxGenericTeams);
         if (teams == 0)
-            teams = (int)std::max<int64_t>(1, std::min<int64_t>(want, std::min(limit, device_cus())));
+            teams = (int)std::max<int64_t>(1, std::min<int64_t>(want, std::min<int64_t>(limit, cus)));
         else if (teams > limit)
             return fail(OMPRT_ERR_INVALID, "teams %d: at most %d teams of %d threads can be resident "
                         "at once here", teams, limit, threads);
     }
+    const GenericVariant* var = nullptr;
+    if (omprt_status st = pick_variant(n, teams, threads, &var)) return st;
+    CrossTeam ct{};
+    int it = iters;
+    void* args[] = {&d_diag, &d_v, &n, &it, &d_lambda, &ct};
     hipError_t e;
     if (teams == 1) {
-        hipLaunchKernelGGL(generic_power_kernel<false>, dim3(1), dim3(threads), 0, stream, d_diag,
-                           d_v, n, (int)iters, d_lambda, CrossTeam{});
-        e = hipGetLastError();
+        e = hipLaunchKernel(var->one, dim3(1), dim3(threads), args, 0, stream);
     } else {
         Workspace* ws = nullptr;
-        if (omprt_status st = workspace_get(stream, 2 * teams, &ws)) return st;
+        if (omprt_status st = workspace_get(stream, kGenericSlots * teams, &ws)) return st;
         const CrossTeamArgs ca = ws->cross();
-        CrossTeam ct{static_cast<uint64_t*>(ca.slots), ca.counter, ca.epoch, ca.status};
-        int it = iters;
-        void* args[] = {&d_diag, &d_v, &n, &it, &d_lambda, &ct};
-        e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&generic_power_kernel<true>),
-                                       dim3(teams), dim3(threads), args, 0, stream);
+        ct = CrossTeam{static_cast<uint64_t*>(ca.slots), ca.counter, ca.epoch, ca.status};
+        e = hipLaunchCooperativeKernel(var->many, dim3(teams), dim3(threads), args, 0, stream);
     }
     if (e != hipSuccess) return fail(OMPRT_ERR_DEVICE, "generic launch: %s", hipGetErrorString(e));
     return OMPRT_OK;

@@ -123,3 +123,16 @@ def test_timed_workload_sizes(gpu_lib):
         d, v0 = synth.power_inputs(n, 11)
         check(gpu_lib, d, v0, 100, 1)
         check(gpu_lib, d, v0, 100, 0)
+
+
+@pytest.mark.parametrize("elems", [4, 8, 16, 32, 64, 128])
+@pytest.mark.parametrize("teams,threads", [(1, 64), (3, 256), (2, 512), (2, 1024), (512, 64)])
+def test_register_share_edges(gpu_lib, elems, teams, threads):
+    """Shares of exactly `elems` elements a thread (the last size a register
+    variant holds), one more (the next variant, or memory past the last) and
+    one team a single element short."""
+    full = elems * teams * threads
+    for k, n in enumerate([full, full + 1, full - 1]):
+        d, v0 = synth.power_inputs(n, 500 + k)
+        for iters in (1, 4):
+            check(gpu_lib, d, v0, iters, teams, threads)
