@@ -1,9 +1,11 @@
 // mlp.hip -- the learned configuration picker's network on the GPU:
 // forward (logits), mean softmax cross-entropy with its full backward pass,
 // and the Adam update, in fp32.  Shapes are tiny (F = 16, H = 64, K <= 64,
-// batches of a few hundred to tens of thousands of rows), so every kernel is
-// a plain one-thread-per-output VALU kernel; sums over batch rows use TwoSum
-// compensation so the gradients track an FP64 reference closely.
+// batches of a few hundred to tens of thousands of rows): networks whose
+// weights fit the LDS take the fused kernels of mlp_fused.h, larger ones (up
+// to 4096 a layer) the plain one-thread-per-output kernels here.  Sums over
+// batch rows use TwoSum compensation so the gradients track an FP64 reference
+// closely.
 #include <math.h>
 #include <string.h>
 
@@ -13,6 +15,7 @@
 #include <utility>
 
 #include "device.h"
+#include "mlp_fused.h"
 #include "runtime.h"
 
 namespace omprt {
@@ -33,14 +36,6 @@ __global__ void mlp_linear_kernel(const float* __restrict__ X, const float* __re
 
 // Per row: loss_r = logsumexp(z) - z[y];  dZ[r][j] = (softmax(z)_j - [j == y]) / B.
 // One wave per row, lanes over the classes (max and sum by wave reductions).
-struct MaxPolicy {
-    using Acc = float;
-    static __device__ __forceinline__ float combine(float a, float b) { return fmaxf(a, b); }
-};
-struct AddPolicy {
-    using Acc = float;
-    static __device__ __forceinline__ float combine(float a, float b) { return a + b; }
-};
 __global__ __launch_bounds__(256) void mlp_softmax_ce_kernel(const float* __restrict__ Z,
                                                              const int32_t* __restrict__ y,
                                                              float* __restrict__ dZ,
@@ -122,37 +117,68 @@ __global__ __launch_bounds__(256) void mlp_mean_kernel(const float* __restrict__
     if (threadIdx.x == 0) out[0] = (acc.hi + acc.lo) / (float)B;
 }
 
+// One parameter's Adam update; its operations are fixed (no contraction of the
+// compiler's choice), so every kernel below makes the same one bit for bit.
+__device__ __forceinline__ float adam_update(float w, float& m, float& v, float g, float lr,
+                                             float b1, float b2, float eps, float c1, float c2) {
+#pragma clang fp contract(off)
+    m = __builtin_fmaf(b1, m, (1.0f - b1) * g);
+    v = __builtin_fmaf(b2, v, (1.0f - b2) * g * g);
+    return w - lr * (m / c1) / (sqrtf(v / c2) + eps);
+}
+
 __global__ void mlp_adam_kernel(float* __restrict__ w, float* __restrict__ m,
                                 float* __restrict__ v, const float* __restrict__ g, int64_t n,
                                 float lr, float b1, float b2, float eps, float c1, float c2) {
     const int64_t i = (int64_t)blockIdx.x * team_size() + threadIdx.x;
     if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
+    float mi = m[i], vi = v[i];
+    w[i] = adam_update(w[i], mi, vi, g[i], lr, b1, b2, eps, c1, c2);
     m[i] = mi;
     v[i] = vi;
-    w[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
 // Adam with the step count in device memory: t = *step + 1 (the bias
-// corrections are computed per thread, in double as the host path does, so
-// the update is bit for bit the one omprt_mlp_adam makes at step t).
-__global__ void mlp_adam_counted_kernel(float* __restrict__ w, float* __restrict__ m,
-                                        float* __restrict__ v, const float* __restrict__ g,
-                                        int64_t n, const int32_t* __restrict__ step, float lr,
-                                        float b1, float b2, float eps) {
+// corrections are computed in double as the host path does, so the update is
+// bit for bit the one omprt_mlp_adam makes at step t; lane 0 and lane 1 of
+// each wave take one power each, and the wave shares them).
+__device__ __forceinline__ void adam_corrections(int step, float b1, float b2, float& c1,
+                                                 float& c2) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const float c = (float)(1.0 - pow((double)(lane ? b2 : b1), (double)step + 1.0));
+    c1 = __shfl(c, 0, kWave);
+    c2 = __shfl(c, 1, kWave);
+}
+
+// `done` (an election counter, 0 between launches; nullptr: the step is
+// advanced by a launch of its own): the last workgroup to have read the step
+// advances it.
+__global__ __launch_bounds__(256) void mlp_adam_counted_kernel(
+    float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
+    const float* __restrict__ g, int64_t n, int32_t* step, uint32_t* done, float lr, float b1,
+    float b2, float eps) {
     const int64_t i = (int64_t)blockIdx.x * team_size() + threadIdx.x;
-    if (i >= n) return;
-    const double t = (double)step[0] + 1.0;
-    const float c1 = (float)(1.0 - pow((double)b1, t));
-    const float c2 = (float)(1.0 - pow((double)b2, t));
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    w[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    const int t0 = step[0];
+    const bool real = i < n;
+    float mi = 0.0f, vi = 0.0f, wi = 0.0f, gi = 0.0f;
+    if (real) {
+        mi = m[i];
+        vi = v[i];
+        wi = w[i];
+        gi = g[i];
+    }
+    float c1, c2;
+    adam_corrections(t0, b1, b2, c1, c2);
+    if (real) {
+        w[i] = adam_update(wi, mi, vi, gi, lr, b1, b2, eps, c1, c2);
+        m[i] = mi;
+        v[i] = vi;
+    }
+    if (!done) return;
+    __syncthreads();   // every thread of the workgroup has used the step
+    const uint32_t e = gridDim.x - 1;
+    if (threadIdx.x == 0 && __builtin_amdgcn_atomic_inc32(done, e, __ATOMIC_RELAXED, "agent") == e)
+        step[0] = t0 + 1;
 }
 
 __global__ void mlp_step_advance_kernel(int32_t* step) { step[0] += 1; }
@@ -207,6 +233,47 @@ static omprt_status check_dims(const omprt_mlp_dims* d) {
 
 static inline unsigned blocks(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
+// ---------------------------------------------------------------- fused path
+
+// Rows a wave of mlp_rows_kernel takes: one while the tiles' latency is what the
+// kernel takes (256 rows 10.1 us, 4096 22), four past that (a weight read from
+// LDS then serves four rows; 4096 rows run alike either way).
+static int rows_per_wave(int B) { return B <= 4096 ? 1 : 4; }
+
+// LDS of the row tiles may take; the rest of the 160 KiB stays free for a
+// second kernel's workgroups.
+constexpr int kRowsLdsLimit = 128 * 1024;
+
+// Slices of the batch rows of mlp_grads_kernel: past 64 rows a wave, up to 16.
+static int grad_slices(int B) {
+    const int per = 64 * kGradWaves;
+    return std::max(1, std::min(16, (B + per - 1) / per));
+}
+
+static MlpShape shape_of(const omprt_mlp_dims* d) { return MlpShape{d->F, d->H1, d->H2, d->K}; }
+
+// Whether the network takes the fused kernels.
+static bool fused_fits(const omprt_mlp_dims* d, int B) {
+    // (products of dimensions up to 4096 fit an int)
+    return (int64_t)mlp_rows_lds(shape_of(d), kRowsWaves * rows_per_wave(B)) * 4 <= kRowsLdsLimit;
+}
+
+template <bool TRAIN>
+static omprt_status launch_rows(const omprt_mlp_dims* d, const float* params, const float* X,
+                                const int32_t* y, int B, const MlpRowsOut& out, hipStream_t s) {
+    const int rpw = rows_per_wave(B);
+    const size_t lds = (size_t)mlp_rows_lds(shape_of(d), kRowsWaves * rpw) * 4;
+    auto go = [&](auto kernel) -> omprt_status {
+        if (lds > 64 * 1024)   // past the default dynamic LDS limit: ask for it
+            OMPRT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        hipLaunchKernelGGL(kernel, dim3(blocks(B, kRowsWaves * rpw)), dim3(kRowsThreads), lds, s,
+                           shape_of(d), mlp_parts(shape_of(d)), params, X, y, B, out);
+        return OMPRT_OK;
+    };
+    return rpw == 1 ? go(mlp_rows_kernel<TRAIN, 1>) : go(mlp_rows_kernel<TRAIN, 4>);
+}
+
 }  // namespace omprt
 
 using namespace omprt;
@@ -239,6 +306,13 @@ extern "C" omprt_status omprt_mlp_forward(const omprt_mlp_dims* d, const float* 
     if (B == 0) return OMPRT_OK;
     if (!d_params || !d_X || !d_Z) return fail(OMPRT_ERR_INVALID, "NULL pointer");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    if (fused_fits(d, B)) {
+        MlpRowsOut out{};
+        out.z = d_Z;
+        if (omprt_status st = launch_rows<false>(d, d_params, d_X, nullptr, B, out, s)) return st;
+        OMPRT_HIP(hipGetLastError());
+        return OMPRT_OK;
+    }
     float* scr = nullptr;
     if (omprt_status st = mlp_scratch(s, (int64_t)B * (d->H1 + d->H2), &scr)) return st;
     float* a1 = scr;
@@ -264,7 +338,12 @@ extern "C" omprt_status omprt_mlp_loss_grad(const omprt_mlp_dims* d, const float
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const int64_t H1 = d->H1, H2 = d->H2, K = d->K, F = d->F;
     float* scr = nullptr;
-    const int64_t need = (int64_t)B * (2 * H1 + 2 * H2 + 2 * K + 1);
+    const bool fused = fused_fits(d, B);
+    const int S = fused ? grad_slices(B) : 1;
+    const int64_t np = omprt_mlp_param_count(d);
+    // rows, rounded to whole pairs, then the slices' pairs
+    const int64_t rows_need = ((int64_t)B * (2 * H1 + 2 * H2 + 2 * K + 1) + 1) / 2 * 2;
+    const int64_t need = rows_need + (S > 1 ? 2 * S * (np + 1) : 0);
     if (omprt_status st = mlp_scratch(s, need, &scr)) return st;
     float* a1 = scr;
     float* a2 = a1 + B * H1;
@@ -273,6 +352,53 @@ extern "C" omprt_status omprt_mlp_loss_grad(const omprt_mlp_dims* d, const float
     float* d2 = dz + B * K;
     float* d1 = d2 + B * H2;
     float* rl = d1 + B * H1;
+    if (fused) {
+        MlpRowsOut out{};
+        out.a1 = a1;
+        out.a2 = a2;
+        out.dz = dz;
+        out.d2 = d2;
+        out.d1 = d1;
+        out.row_loss = rl;
+        if (omprt_status st = launch_rows<true>(d, d_params, d_X, d_y, B, out, s)) return st;
+        MlpGradPlan gp{};
+        const int at2 = d->H1 * (d->F + 1), at3 = at2 + d->H2 * (d->H1 + 1);
+        gp.l[0] = MlpLayer{d1, d_X, d->H1, d->F, 0, 0, 0};
+        gp.l[1] = MlpLayer{d2, a1, d->H2, d->H1, at2, 0, 0};
+        gp.l[2] = MlpLayer{dz, a2, d->K, d->H2, at3, 0, 0};
+        gp.row_loss = rl;
+        gp.rows = bal_split(B, S);
+        gp.B = B;
+        gp.nparams = (int)np;
+        int wg = 0;
+        for (int k = 0; k < 3; ++k) {
+            MlpLayer& l = gp.l[k];
+            l.cw = l.in <= 16 ? 16 : l.in <= 32 ? 32 : 64;
+            l.tiles_i = (l.in + l.cw - 1) / l.cw;
+            gp.first_tile[k] = wg;
+            wg += l.tiles_i * l.out;
+        }
+        gp.first_tile[3] = wg;
+        for (int k = 0; k < 3; ++k) {
+            gp.first_bias[k] = wg;
+            wg += (gp.l[k].out + kWave - 1) / kWave;
+        }
+        gp.first_bias[3] = wg++;
+        ff_t* partial = reinterpret_cast<ff_t*>(scr + rows_need);
+        const bool vec = ((d->F | d->H1 | d->H2 | d->K) & 3) == 0 &&   // a1, a2 too start on 16 bytes
+                         (reinterpret_cast<uintptr_t>(d_X) & 15) == 0;
+        if (vec)
+            hipLaunchKernelGGL(mlp_grads_kernel<true>, dim3(wg, S), dim3(kGradThreads), 0, s, gp,
+                               d_grads, d_loss, partial);
+        else
+            hipLaunchKernelGGL(mlp_grads_kernel<false>, dim3(wg, S), dim3(kGradThreads), 0, s, gp,
+                               d_grads, d_loss, partial);
+        if (S > 1)
+            hipLaunchKernelGGL(mlp_grads_merge_kernel, dim3(blocks(np + 1, 256)), dim3(256), 0, s,
+                               partial, S, (int)np, (int)B, d_grads, d_loss);
+        OMPRT_HIP(hipGetLastError());
+        return OMPRT_OK;
+    }
     const ParamView p = view(d, d_params);
     float* gW1 = d_grads;
     float* gb1 = gW1 + H1 * F;
@@ -329,9 +455,17 @@ extern "C" omprt_status omprt_mlp_adam_counted(float* d_params, float* d_m, floa
     if (reinterpret_cast<uintptr_t>(d_step) & 3)
         return fail(OMPRT_ERR_INVALID, "step counter not 4-byte aligned");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    // one launch with the stream's election counter; a stream that has no
+    // workspace and is being captured cannot get one, and takes two
+    Workspace* ws = nullptr;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (!workspace_has(s)) OMPRT_HIP(hipStreamIsCapturing(s, &cs));
+    if (cs == hipStreamCaptureStatusNone)
+        if (omprt_status st = workspace_get(s, 1, &ws)) return st;
     hipLaunchKernelGGL(mlp_adam_counted_kernel, dim3(blocks(n, 256)), dim3(256), 0, s, d_params,
-                       d_m, d_v, d_grads, n, d_step, lr, beta1, beta2, eps);
-    hipLaunchKernelGGL(mlp_step_advance_kernel, dim3(1), dim3(1), 0, s, d_step);
+                       d_m, d_v, d_grads, n, d_step, ws ? ws->counter() : nullptr, lr, beta1, beta2,
+                       eps);
+    if (!ws) hipLaunchKernelGGL(mlp_step_advance_kernel, dim3(1), dim3(1), 0, s, d_step);
     OMPRT_HIP(hipGetLastError());
     return OMPRT_OK;
 }

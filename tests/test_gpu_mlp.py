@@ -58,6 +58,44 @@ def test_loss_grad_vs_oracle(gpu_lib, B):
         off += sz
 
 
+@pytest.mark.parametrize("dims", [(16, 64, 64, 64), (1, 1, 1, 2), (5, 33, 7, 3), (17, 32, 96, 24),
+                                  (16, 96, 96, 64), (16, 97, 66, 130), (16, 128, 128, 64),
+                                  (16, 160, 200, 10)])
+@pytest.mark.parametrize("B", [1, 5, 512, 513, 1025])
+def test_network_shapes_vs_oracle(gpu_lib, dims, B):
+    """Networks on both sides of the LDS limit, layer widths off whole 16-byte
+    blocks and off whole waves, batches at the edges of the row tiles (4 and 16
+    rows) and of the gradient slices (512 rows), parameters off 16-byte alignment."""
+    om = gpu_lib
+    F, H1, H2, K = dims
+    g = np.random.Generator(np.random.PCG64(B))
+    P32 = {k: v.astype(np.float32) for k, v in _params(g, F, H1, H2, K).items()}
+    X = g.standard_normal((B, F)).astype(np.float32)
+    y = g.integers(0, K, B).astype(np.int32)
+    loss_ref, Z_ref, g_ref = oracle.mlp_loss_grad(X.astype(np.float64), y,
+                                                  {k: v.astype(np.float64) for k, v in P32.items()})
+    ref = np.concatenate([g_ref[k].ravel() for k in ("W1", "b1", "W2", "b2", "W3", "b3")])
+    flat = torch.from_numpy(_flat(P32))
+    for shift in (0, 1):
+        params = torch.zeros(flat.numel() + shift, device="cuda")[shift:]
+        params.copy_(flat)
+        Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+        Z = torch.zeros((B, K), dtype=torch.float32, device="cuda")
+        om.mlp_forward(dims, params, Xd, Z)
+        loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+        grads = torch.full_like(params, float("nan"))
+        om.mlp_loss_grad(dims, params, Xd, yd, loss, grads)
+        torch.cuda.synchronize()
+        assert _rel(Z.cpu().numpy().astype(np.float64), Z_ref) < 1e-5
+        assert abs(loss.item() - loss_ref) <= 1e-5 * abs(loss_ref)
+        gh = grads.cpu().numpy().astype(np.float64)
+        off = 0
+        for k in ("W1", "b1", "W2", "b2", "W3", "b3"):
+            sz = g_ref[k].size
+            assert _rel(gh[off:off + sz], ref[off:off + sz]) < 1e-5, (k, shift)
+            off += sz
+
+
 def test_adam_vs_oracle(gpu_lib):
     om = gpu_lib
     g = np.random.Generator(np.random.PCG64(3))
@@ -92,6 +130,37 @@ def test_adam_counted_equals_adam(gpu_lib):
         grads = torch.from_numpy(g.standard_normal(n).astype(np.float32)).cuda()
         om.mlp_adam(a[0], a[1], a[2], grads, t, lr=1e-2)
         om.mlp_adam_counted(b[0], b[1], b[2], grads, step, lr=1e-2)
+        torch.cuda.synchronize()
+        for u, w in zip(a, b):
+            assert torch.equal(u.view(torch.int32), w.view(torch.int32)), t
+        assert int(step.item()) == t
+
+
+@pytest.mark.parametrize("n", [1, 256, 257, 20_000])
+@pytest.mark.parametrize("captured", [False, True])
+def test_adam_counted_sizes(gpu_lib, n, captured):
+    """One workgroup and several; eager (the step advanced by the last workgroup) and
+    captured on a stream without a workspace (by a launch of its own), replayed."""
+    om = gpu_lib
+    g = np.random.Generator(np.random.PCG64(n))
+    p = torch.from_numpy(g.standard_normal(n).astype(np.float32)).cuda()
+    grads = torch.from_numpy(g.standard_normal(n).astype(np.float32)).cuda()
+    a = [p.clone(), torch.zeros_like(p), torch.zeros_like(p)]
+    b = [p.clone(), torch.zeros_like(p), torch.zeros_like(p)]
+    step = torch.full((1,), 6, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    graph = None
+    if captured:
+        om.finalize()   # no stream has a workspace any more
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            om.mlp_adam_counted(b[0], b[1], b[2], grads, step, lr=1e-2)
+    for t in (7, 8, 9):
+        om.mlp_adam(a[0], a[1], a[2], grads, t, lr=1e-2)
+        if captured:
+            graph.replay()
+        else:
+            om.mlp_adam_counted(b[0], b[1], b[2], grads, step, lr=1e-2)
         torch.cuda.synchronize()
         for u, w in zip(a, b):
             assert torch.equal(u.view(torch.int32), w.view(torch.int32)), t
