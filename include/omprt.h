@@ -253,7 +253,8 @@ omprt_status omprt_reduce(const void *d_in, int64_t n, int32_t dtype,
  * slot of its own (the keys read once); up to 8 388 608 bins the ranges are
  * laid out across teams (counts per range and team, a prefix sum, then the
  * scatter: the keys read twice); beyond, every key is an atomic add on
- * d_hist itself (no copy).  cfg->flags:
+ * d_hist itself (no copy).  With few keys (n (bins + 2000) under 2.3e11) up to
+ * 32 ranges are counted range by range, in one launch.  cfg->flags:
  * OMPRT_CFG_HIST_RANGES counts range by range up to 32 ranges;
  * OMPRT_CFG_HIST_TILE_SORT sorts tiles for any bin count up to 4 194 304;
  * OMPRT_CFG_HIST_PARTITION partitions across teams for any bin count up to
@@ -263,8 +264,9 @@ omprt_status omprt_reduce(const void *d_in, int64_t n, int32_t dtype,
  * falling back from LDS; atomics at L2); OMPRT_CFG_HIST_DIRECT takes
  * atomics on d_hist for any bin count; at most one of them.  cfg:
  * num_teams (default two per compute unit), threads_per_team (default
- * 512; the partitioned passes always take 512), unroll 1, 2 or 4 (default
- * 4).  bins 1..2^28.
+ * 512; the partitioned passes have their own), unroll 1, 2 or 4 (default
+ * 4); with neither given the LDS copies take teams of 1024 threads, at most
+ * one per compute unit and fewer the fewer keys there are.  bins 1..2^28.
  */
 omprt_status omprt_histogram(const int32_t *d_keys, int64_t n, int32_t bins,
                              int32_t *d_hist, const omprt_config *cfg,

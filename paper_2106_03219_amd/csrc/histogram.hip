@@ -7,6 +7,8 @@
 // ranges the default is no copy at all: atomic adds on hist.  Counts wrap modulo 2^32; keys
 // outside [0, bins) are not counted and set bit 3 (value 4) of the stream's
 // workspace status.
+#include <math.h>
+
 #include <algorithm>
 #include <map>
 #include <mutex>
@@ -25,8 +27,8 @@ typedef __attribute__((address_space(3))) uint32_t lds_u32;
 struct LdsCopy {
     lds_u32* h;
     __device__ __forceinline__ void zero(uint32_t b) { h[b] = 0u; }
-    __device__ __forceinline__ void add(uint32_t k) {
-        __hip_atomic_fetch_add(h + k, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __device__ __forceinline__ void add(uint32_t k, uint32_t n = 1u) {
+        __hip_atomic_fetch_add(h + k, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __device__ __forceinline__ uint32_t get(uint32_t b) const { return h[b]; }
 };
@@ -35,8 +37,8 @@ struct GlobalCopy {
     __device__ __forceinline__ void zero(uint32_t b) {
         __hip_atomic_store(h + b, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __device__ __forceinline__ void add(uint32_t k) {
-        __hip_atomic_fetch_add(h + k, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __device__ __forceinline__ void add(uint32_t k, uint32_t n = 1u) {
+        __hip_atomic_fetch_add(h + k, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __device__ __forceinline__ uint32_t get(uint32_t b) const {
         return __hip_atomic_load(h + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -54,6 +56,28 @@ __device__ __forceinline__ void count_key(C& c, int32_t k, const BinRange& r, bo
         bad = true;
     else if ((uint32_t)k - r.b0 < r.tb)
         c.add((uint32_t)k - r.b0);
+}
+
+// A vector of four keys a lane.  When every key of the wave's vectors is the
+// same (constant or sorted inputs) one lane adds their number: same-address
+// lanes of an LDS atomic are served one after another (10^8 equal keys into
+// 1000 bins: 333 us lane by lane, 65 this way; six operations for four
+// keys otherwise, hidden behind the keys' stream).
+using i32x4 = int32_t __attribute__((ext_vector_type(4)));
+template <class C>
+__device__ __forceinline__ void count_vector(C& c, const i32x4& k, const BinRange& r, bool& bad) {
+    const int32_t f = __builtin_amdgcn_readfirstlane(k[0]);
+    const bool same = ((k[0] ^ f) | (k[1] ^ f) | (k[2] ^ f) | (k[3] ^ f)) == 0;
+    const uint64_t active = __ballot(1);
+    if (__ballot(same) == active) {
+        if ((uint32_t)f >= r.bins)
+            bad = true;
+        else if ((uint32_t)f - r.b0 < r.tb && (int)__lane_id() == __ffsll((unsigned long long)active) - 1)
+            c.add((uint32_t)f - r.b0, 4u * (uint32_t)__popcll(active));
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) count_key(c, k[q], r, bad);
+    }
 }
 
 // Zero the copy, count the keys of the team's balanced block that fall in
@@ -76,7 +100,6 @@ __device__ __forceinline__ bool team_histogram(C c, const int32_t* __restrict__ 
         if (tid < head) count_key(c, keys[a + tid], bins, bad);
         const int64_t p0 = a + head;
         const int64_t nv = (e - p0) / 4;
-        using i32x4 = int32_t __attribute__((ext_vector_type(4)));
         const i32x4* __restrict__ vp = reinterpret_cast<const i32x4*>(keys + p0);
         int64_t v = tid;
         for (; v + (int64_t)(U - 1) * P < nv; v += (int64_t)U * P) {
@@ -84,15 +107,9 @@ __device__ __forceinline__ bool team_histogram(C c, const int32_t* __restrict__ 
 #pragma unroll
             for (int u = 0; u < U; ++u) r[u] = __builtin_nontemporal_load(vp + v + (int64_t)u * P);
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) count_key(c, r[u][q], bins, bad);
+            for (int u = 0; u < U; ++u) count_vector(c, r[u], bins, bad);
         }
-        for (; v < nv; v += P) {
-            const i32x4 r = __builtin_nontemporal_load(vp + v);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) count_key(c, r[q], bins, bad);
-        }
+        for (; v < nv; v += P) count_vector(c, __builtin_nontemporal_load(vp + v), bins, bad);
         const int64_t t0 = p0 + nv * 4;
         if (tid < e - t0) count_key(c, keys[t0 + tid], bins, bad);
     }
@@ -175,7 +192,6 @@ __global__ __launch_bounds__(1024) void histogram_direct_kernel(const int32_t* _
         if (tid < head) count(keys[a + tid]);
         const int64_t p0 = a + head;
         const int64_t nv = (e - p0) / 4;
-        using i32x4 = int32_t __attribute__((ext_vector_type(4)));
         const i32x4* __restrict__ vp = reinterpret_cast<const i32x4*>(keys + p0);
         int64_t v = tid;
         for (; v + (U - 1) * P < nv; v += U * P) {
@@ -255,7 +271,6 @@ __device__ __forceinline__ void part_keys(const int32_t* __restrict__ keys, int6
     if (tid < head) one(keys[a + tid]);
     const int64_t p0 = a + head;
     const int64_t nv = (e - p0) / 4;
-    using i32x4 = int32_t __attribute__((ext_vector_type(4)));
     const i32x4* __restrict__ vp = reinterpret_cast<const i32x4*>(keys + p0);
     int64_t v = tid;
     for (; v + (int64_t)(U - 1) * P < nv; v += (int64_t)U * P) {
@@ -543,93 +558,138 @@ __global__ void hist_part_merge_kernel(const uint32_t* __restrict__ partial, uin
 }
 
 // Tile-sorted partition, up to kTsortMaxRanges ranges: every tile of
-// kPartTile keys of a team's balanced block is ranked and sorted by range in
-// LDS as in the scatter above, but stored whole into a slot of its own,
-// kTsortSlot places: range r's run starts on a 16-byte boundary (each run is
-// padded with kTsortPad to a multiple of eight places) and the runs' starts,
-// in 16-byte vectors, go to tstart[g (R + 1) + r] (g = team x tiles per
-// team + tile; entry R is the slot's end).  No count pass and no scan
-// across teams: the range kernel then reads range r's run of every tile.
-// Key traffic: read once, places written once and read once (2 x the key
-// bytes), against three times for the partition above; the runs of a tile
-// are 8192 / R places long on average (64 at 128 ranges), and the padding
-// adds at most 8 R places a tile (12.5 % at 128 ranges).
+// kPartTile keys is ranked and sorted by range in LDS and stored whole into a
+// slot of its own, kTsortSlot places: range r's run starts on a 16-byte
+// boundary (each run is padded with kTsortPad to a multiple of eight places)
+// and the runs' starts, in 16-byte vectors, go to tstart[r G + g] (G tiles;
+// entry R is the slot's end).  No count pass and no scan across teams: the
+// range kernel then reads range r's run of every tile.  Key traffic: read
+// once, places written once and read once (2 x the key bytes), against three
+// times for the partition above; the runs of a tile are 8192 / R places long
+// on average (64 at 128 ranges), and the padding adds at most 8 R places a
+// tile (12.5 % at 128 ranges).
+//
+// How many workgroups count a range follows from how many keys it has (the
+// plan kernel): W workgroups are shared out over the ranges in proportion, so
+// a skewed input is counted by as many as a uniform one, and a range that
+// gets one adds into hist itself, without a partial.
 constexpr uint32_t kTsortMaxRanges = 128;
 constexpr uint32_t kTsortSlot = kPartTile + 8 * kTsortMaxRanges;   // places, 16-byte multiple
-constexpr uint32_t kTsortPad = 0xFFFFu;                            // never a place (< kPartBins)
+constexpr uint32_t kTsortPad = kPartBins;   // the counter past a range's bins: counted, never read
+constexpr uint32_t kTsortCounters = 256;                           // ranges x copies, at most
 static_assert(kTsortSlot % 8 == 0 && kTsortSlot / 8 < 65536, "slot of whole 16-byte vectors");
 
-__global__ __launch_bounds__(kPartThreads) void hist_tsort_scatter_kernel(
-    const int32_t* __restrict__ keys, int64_t n, uint32_t bins, uint32_t R, uint32_t NT,
-    uint16_t* __restrict__ part, uint16_t* __restrict__ tstart, uint32_t* status) {
+// Tile g of n keys whose first `head` (0..3) lie before a 16-byte boundary:
+// the head alone, then kPartTile keys each.
+struct TileSplit {
+    int64_t n, G;
+    int head;
+    __host__ __device__ __forceinline__ int64_t lo(int64_t g) const {
+        return head ? (g ? head + (g - 1) * (int64_t)kPartTile : 0) : g * (int64_t)kPartTile;
+    }
+    __host__ __device__ __forceinline__ int64_t hi(int64_t g) const {
+        const int64_t h = lo(g + 1);
+        return h < n ? h : n;
+    }
+};
+
+// Team t sorts its balanced share of the tiles and leaves the number of keys it
+// put in range r in cnt[t R + r].  Three barriers a tile: after the ranks, after
+// the scan (one wave, which also clears the counters and writes the padding),
+// after the sort; the copy to memory runs into the next tile's ranks.  Whole
+// tiles load 16-byte vectors, and a wave whose keys are all in range skips
+// their bounds checks.  2^28 keys over 32 ranges: 291 us (423 with element
+// loads, six barriers, three LDS reads a key where one precombined offset
+// does).
+__global__ __launch_bounds__(kPartThreads, 4) void hist_tsort_scatter_kernel(
+    const int32_t* __restrict__ keys, TileSplit ts, BalSplit share, uint32_t bins, uint32_t R,
+    uint16_t* __restrict__ part, uint16_t* __restrict__ tstart, uint32_t* __restrict__ cnt,
+    uint32_t* status) {
+    constexpr int P = kPartThreads, NV = kPartPerThread / 4;
     const uint32_t C = part_copies(R);
-    __shared__ uint32_t tcnt[kTsortMaxRanges * kPartCopies];       // [range][copy]
-    __shared__ uint32_t toff[kTsortMaxRanges * kPartCopies + 1];   // exclusive scan of tcnt
-    __shared__ uint32_t pst[kTsortMaxRanges + 1];                  // padded run starts
-    __shared__ uint32_t wtot[kTsortMaxRanges * kPartCopies / kWave];
+    __shared__ __align__(16) uint32_t tcnt[kTsortCounters];   // [range][copy]
+    __shared__ __align__(16) uint32_t off[kTsortCounters];    // where that copy's places go
+    __shared__ uint32_t s_vectors;                            // 16-byte vectors of the sorted tile
     __shared__ __align__(16) uint16_t buf[kTsortSlot];
     __shared__ int s_bad;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), P = team_size();
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const uint32_t copy = (uint32_t)tid % C;
-    const uint32_t RC = R * C;
     if (tid == 0) s_bad = 0;
+    if (tid < (int)kTsortCounters) tcnt[tid] = 0u;
     bool bad = false;
-    const Range blk = bal_share(n, gridDim.x, blockIdx.x);
-    // the next tile's keys are loaded while this one is sorted and stored
-    // (nothing reads them before then); positions past the block read as
-    // 0xFFFFFFFF (not a valid key)
-    uint32_t kn[kPartPerThread];
-    auto load_tile = [&](int64_t t0) {
+    const Range blk = share.share(blockIdx.x);
+    using u32x4v = uint32_t __attribute__((ext_vector_type(4)));
+    // the next tile's keys are loaded while this one is sorted and stored;
+    // positions past a partial tile's end read as 0xFFFFFFFF (not a valid key)
+    u32x4v kn[NV];
+    auto load_tile = [&](int64_t g) {
+        const int64_t lo = ts.lo(g);
+        const int count = (int)(ts.hi(g) - lo);
+        const uint32_t* __restrict__ p = reinterpret_cast<const uint32_t*>(keys) + lo;
+        if (count == kPartTile) {
 #pragma unroll
-        for (int q = 0; q < kPartPerThread; ++q) {
-            const int64_t i = t0 + (int64_t)q * P + tid;
-            kn[q] = i < blk.hi ? (uint32_t)__builtin_nontemporal_load(keys + i) : 0xFFFFFFFFu;
+            for (int q = 0; q < NV; ++q)
+                kn[q] = __builtin_nontemporal_load(reinterpret_cast<const u32x4v*>(p) + q * P + tid);
+        } else {
+#pragma unroll
+            for (int q = 0; q < NV; ++q)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int e = (q * P + tid) * 4 + u;
+                    kn[q][u] = e < count ? p[e] : 0xFFFFFFFFu;
+                }
         }
     };
+    uint32_t total[kTsortMaxRanges / kWave] = {};   // the first wave: keys of the lane's ranges
     if (blk.lo < blk.hi) load_tile(blk.lo);
-    uint32_t j = 0;
-    for (int64_t t0 = blk.lo; t0 < blk.hi; t0 += kPartTile, ++j) {
-        for (uint32_t e = tid; e < RC; e += P) tcnt[e] = 0u;
-        uint32_t kr[kPartPerThread], rank[kPartPerThread];
+    __syncthreads();
+    for (int64_t g = blk.lo; g < blk.hi; ++g) {
+        u32x4v kr[NV], rank[NV];
+        uint32_t mx = 0;
 #pragma unroll
-        for (int q = 0; q < kPartPerThread; ++q) kr[q] = kn[q];
-        if (t0 + kPartTile < blk.hi) load_tile(t0 + kPartTile);
-        __syncthreads();
+        for (int q = 0; q < NV; ++q) {
+            kr[q] = kn[q];
 #pragma unroll
-        for (int q = 0; q < kPartPerThread; ++q) {
-            if (kr[q] < bins)
-                rank[q] = __hip_atomic_fetch_add(tcnt + (kr[q] >> kPartLog2) * C + copy, 1u,
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            else if (t0 + (int64_t)q * P + tid < blk.hi)
-                bad = true;
+            for (int u = 0; u < 4; ++u) mx = mx > kr[q][u] ? mx : kr[q][u];
+        }
+        const int count = (int)(ts.hi(g) - ts.lo(g));
+        if (g + 1 < blk.hi) load_tile(g + 1);
+        const bool all_in = __ballot(mx >= bins) == 0;   // wave-uniform
+        auto rank_key = [&](uint32_t k) {
+            return __hip_atomic_fetch_add(tcnt + (k >> kPartLog2) * C + copy, 1u, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_WORKGROUP);
+        };
+        if (all_in) {
+#pragma unroll
+            for (int q = 0; q < NV; ++q)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) rank[q][u] = rank_key(kr[q][u]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < NV; ++q)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (kr[q][u] < bins)
+                        rank[q][u] = rank_key(kr[q][u]);
+                    else if ((q * P + tid) * 4 + u < count)
+                        bad = true;
+                }
         }
         __syncthreads();
-        // exclusive scan of the tile counts in (range, copy) order: entry e
-        // by thread e, the waves' totals through LDS
-        uint32_t v = 0, inc = 0;
-        if ((uint32_t)tid < RC) {
-            v = tcnt[tid];
-            inc = v;
-#pragma unroll
-            for (int d = 1; d < kWave; d <<= 1) {
-                const uint32_t o = __shfl_up(inc, d, kWave);
-                if (lane >= d) inc += o;
-            }
-            if (lane == kWave - 1 || (uint32_t)tid == RC - 1) wtot[tid / kWave] = inc;
-        }
-        __syncthreads();
-        if ((uint32_t)tid < RC) {
-            uint32_t before = 0;
-            for (int w = 0; w < tid / kWave; ++w) before += wtot[w];
-            toff[tid] = before + inc - v;
-            if ((uint32_t)tid == RC - 1) toff[RC] = before + inc;
-        }
-        __syncthreads();
-        if (tid < kWave) {   // padded run starts: each run rounded up to eight places
+        if (tid < kWave) {
+            // lane l takes ranges l and l + 64: the run's padded length, its
+            // start by a scan over the ranges, then each copy's part of the run
             uint32_t carry = 0;
-            for (uint32_t r0 = 0; r0 <= R; r0 += kWave) {
-                const uint32_t r = r0 + (uint32_t)lane;
-                const uint32_t len = r < R ? toff[(r + 1) * C] - toff[r * C] : 0u;
+#pragma unroll
+            for (uint32_t h = 0; h < kTsortMaxRanges / kWave; ++h) {
+                if (h * kWave > R) break;
+                const uint32_t r = h * kWave + (uint32_t)lane;
+                uint32_t c[kPartCopies], len = 0;
+#pragma unroll
+                for (uint32_t q = 0; q < kPartCopies; ++q) {
+                    c[q] = q < C && r < R ? tcnt[r * C + q] : 0u;
+                    len += c[q];
+                }
                 const uint32_t pl = (len + 7u) & ~7u;
                 uint32_t inc = pl;
 #pragma unroll
@@ -637,81 +697,169 @@ __global__ __launch_bounds__(kPartThreads) void hist_tsort_scatter_kernel(
                     const uint32_t o = __shfl_up(inc, d, kWave);
                     if (lane >= d) inc += o;
                 }
-                if (r <= R) pst[r] = carry + inc - pl;   // entry R: the padded total
+                const uint32_t start = carry + inc - pl;
+                if (r < R) {
+                    uint32_t at = start;
+#pragma unroll
+                    for (uint32_t q = 0; q < kPartCopies; ++q)
+                        if (q < C) {
+                            off[r * C + q] = at;
+                            tcnt[r * C + q] = 0u;
+                            at += c[q];
+                        }
+                    for (; at < start + pl; ++at) buf[at] = (uint16_t)kTsortPad;
+                    total[h] += len;
+                }
+                if (r <= R) tstart[(size_t)r * ts.G + g] = (uint16_t)(start / 8);
+                if (r == R) s_vectors = start / 8;
                 carry += __shfl(inc, kWave - 1, kWave);
             }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < kPartPerThread; ++q)
-            if (kr[q] < bins) {
-                const uint32_t r = kr[q] >> kPartLog2;
-                buf[pst[r] + toff[r * C + copy] - toff[r * C] + rank[q]] =
-                    (uint16_t)(kr[q] & (kPartBins - 1));
+            // with a multiple of 64 ranges entry R starts the next group of lanes
+            if (R % kWave == 0 && lane == 0) {
+                tstart[(size_t)R * ts.G + g] = (uint16_t)(carry / 8);
+                s_vectors = carry / 8;
             }
-        for (uint32_t e = (uint32_t)tid; e < R * 8; e += P) {   // the padding after each run
-            const uint32_t r = e / 8, u = e % 8;
-            const uint32_t at = pst[r] + (toff[(r + 1) * C] - toff[r * C]) + u;
-            if (at < pst[r + 1]) buf[at] = (uint16_t)kTsortPad;
         }
         __syncthreads();
-        const size_t g = (size_t)blockIdx.x * NT + j;
-        u32x4* __restrict__ slot = reinterpret_cast<u32x4*>(part + g * kTsortSlot);
+        auto place_key = [&](uint32_t k, uint32_t rk) {
+            buf[off[(k >> kPartLog2) * C + copy] + rk] = (uint16_t)(k & (kPartBins - 1));
+        };
+        if (all_in) {
+#pragma unroll
+            for (int q = 0; q < NV; ++q)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) place_key(kr[q][u], rank[q][u]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < NV; ++q)
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (kr[q][u] < bins) place_key(kr[q][u], rank[q][u]);
+        }
+        __syncthreads();
+        u32x4* __restrict__ slot = reinterpret_cast<u32x4*>(part + (size_t)g * kTsortSlot);
         const u32x4* lb = reinterpret_cast<const u32x4*>(buf);
-        for (uint32_t v = tid; v < pst[R] / 8; v += P) slot[v] = lb[v];
-        if ((uint32_t)tid <= R) tstart[g * (R + 1) + tid] = (uint16_t)(pst[tid] / 8);
-        // the next tile rewrites pst and buf only after two more barriers
+        for (uint32_t v = tid; v < s_vectors; v += P) slot[v] = lb[v];
+        // buf, off and s_vectors are written again only after the next ranks'
+        // barrier, which every thread reaches past this copy
     }
-    for (uint32_t e = (uint32_t)tid; e < (NT - j) * (R + 1); e += P)   // empty tiles
-        tstart[((size_t)blockIdx.x * NT + j) * (R + 1) + e] = 0;
+    if (tid < kWave)
+#pragma unroll
+        for (uint32_t h = 0; h < kTsortMaxRanges / kWave; ++h) {
+            const uint32_t r = h * kWave + (uint32_t)lane;
+            if (r < R) cnt[(size_t)blockIdx.x * R + r] = total[h];
+        }
     flag_bad(bad, &s_bad, status);
 }
 
-// Team (r, s): range r's runs in slice s of the G tile slots, each group of
-// SW lanes (a wave, or half of one when runs are short) sixteen tiles at a
-// time, one 16-byte vector of each in flight per lane (the LDS copy of the
-// range allows one team a CU, so registers are plentiful).  out is hist (S ==
-// 1) or the partials, S x bins.
+// One workgroup: the keys of every range (cnt[t R + r] over the T teams), then
+// first[r], the first of the W workgroups that count range r (first[R]: the
+// number in use): one each and the rest in proportion to the keys.
+__global__ __launch_bounds__(1024) void hist_tsort_plan_kernel(const uint32_t* __restrict__ cnt,
+                                                               uint32_t T, uint32_t R, uint32_t W,
+                                                               uint32_t* __restrict__ first) {
+    __shared__ uint64_t part_sum[1024];   // [group of teams][range]
+    __shared__ uint64_t sum[kTsortMaxRanges];
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const uint32_t rp = R <= 32 ? 32u : R <= 64 ? 64u : kTsortMaxRanges;   // ranges, padded
+    const uint32_t r = tid & (rp - 1), groups = 1024 / rp, grp = tid / rp;
+    uint64_t a = 0;
+    if (r < R)
+#pragma unroll 16
+        for (uint32_t t = grp; t < T; t += groups) a += cnt[(size_t)t * R + r];
+    part_sum[tid] = a;
+    __syncthreads();
+    if (tid < R) {
+        uint64_t q = 0;
+        for (uint32_t k = 0; k < groups; ++k) q += part_sum[k * rp + tid];
+        sum[tid] = q;
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    a = 0;
+    for (uint32_t i = lane; i < R; i += kWave) a += sum[i];
+    const double all = (double)wave_reduce<Red<DT_I64, OP_SUM>>(a);
+    uint32_t carry = 0;
+    for (uint32_t r0 = 0; r0 < R; r0 += kWave) {
+        const uint32_t i = r0 + lane;
+        // (the floor of an exact share or one less: never more than W in all)
+        const uint32_t k =
+            i < R ? 1u + (all > 0.0 ? (uint32_t)((double)(W - R) * ((double)sum[i] / all)) : 0u) : 0u;
+        uint32_t inc = k;
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const uint32_t o = __shfl_up(inc, d, kWave);
+            if ((int)lane >= d) inc += o;
+        }
+        if (i < R) first[i] = carry + inc - k;
+        carry += __shfl(inc, kWave - 1, kWave);
+    }
+    if (lane == 0) first[R] = carry;
+}
+
+// Workgroup w of range r (first[r] <= w < first[r + 1]): the range's runs in
+// its share of the G tile slots, counted in LDS.  Each group of SW lanes takes
+// K neighbouring tiles at a time, one 16-byte vector of each in flight per lane
+// (the LDS copy of the range allows one workgroup a CU: sixteen waves of it
+// keep 256 KiB of loads in flight; 2^28 keys, 32 ranges: 150 us, with eight
+// waves 193).  A range with one workgroup adds into hist, else the counts are
+// partial w.
+constexpr int kRangeThreads = 1024;
 template <int SW>
-__global__ __launch_bounds__(kPartThreads) void hist_tsort_range_kernel(
-    const uint16_t* __restrict__ part, const uint16_t* __restrict__ tstart, int64_t G,
-    uint32_t R, uint32_t bins, uint32_t S, uint32_t* __restrict__ out) {
+__global__ __launch_bounds__(kRangeThreads) void hist_tsort_range_kernel(
+    const uint16_t* __restrict__ part, const uint16_t* __restrict__ tstart, int64_t G, uint32_t R,
+    uint32_t bins, const uint32_t* __restrict__ first, uint32_t* __restrict__ partial,
+    uint32_t* __restrict__ hist) {
     extern __shared__ __align__(16) char arena[];
+    __shared__ uint32_t s_range[3];   // the range, its first workgroup, the next range's
     lds_u32* h = (lds_u32*)arena;
-    const int tid = threadIdx.x, lane = tid & (SW - 1), P = team_size();
-    const int64_t W = P / SW, wave = tid / SW;
-    const uint32_t r = blockIdx.x / S, s = blockIdx.x % S;
+    constexpr int P = kRangeThreads;
+    const int tid = threadIdx.x, lane = tid & (SW - 1);
+    uint32_t fa = 0, fb = 0;
+    if (tid < (int)R) {
+        fa = first[tid];
+        fb = first[tid + 1];
+    }
+    if (blockIdx.x >= first[R]) return;
+    if (blockIdx.x >= fa && blockIdx.x < fb) {   // one thread
+        s_range[0] = (uint32_t)tid;
+        s_range[1] = fa;
+        s_range[2] = fb;
+    }
+    for (int b = tid; b < (int)kPartBins / 4; b += P)
+        reinterpret_cast<u32x4*>(arena)[b] = u32x4{0u, 0u, 0u, 0u};
+    __syncthreads();
+    const uint32_t r = s_range[0], s = blockIdx.x - s_range[1], S = s_range[2] - s_range[1];
     const uint32_t b0 = r << kPartLog2;
     const uint32_t tb = bins - b0 < kPartBins ? bins - b0 : kPartBins;
-    for (uint32_t b = tid; b < tb; b += P) h[b] = 0u;
-    __syncthreads();
-    auto add = [&](uint32_t j) {
-        if (j != kTsortPad)
-            __hip_atomic_fetch_add(h + j, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    };
     const Range sl = bal_share(G, S, s);
-    constexpr int K = SW < 16 ? SW : 16;   // tiles of a group: one lane fetches each
-    const int64_t step = K * W;
-    // run starts and lengths of a group of K tiles (g0, g0 + W, ...): the next
-    // group's are loaded while this group's places stream in
-    // (lane k of the group loads tile k's entries; the group shares them)
+    auto add = [&](uint32_t j) {
+        __hip_atomic_fetch_add(h + j, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    constexpr int K = 8;   // tiles of a group: one lane fetches each
+    constexpr int64_t step = (int64_t)K * (P / SW);
     static_assert(K <= SW, "a lane per tile of the group");
-    const int first = (tid & (kWave - 1)) - lane;   // the group's first lane in the wave
+    const uint16_t* __restrict__ ta = tstart + (size_t)r * G;
+    const uint16_t* __restrict__ tz = ta + G;
+    // run starts and lengths of K tiles from g0 on: the next group's are loaded
+    // while this group's places stream in (lane k of the group loads tile k's
+    // entries; the group shares them)
+    const int lane0 = (tid & (kWave - 1)) - lane;   // the group's first lane in the wave
     uint32_t st[K], nv[K];
     auto fetch = [&](int64_t g0) {
-        const int64_t g = g0 + (int64_t)lane * W;
+        const int64_t g = g0 + lane;
         uint32_t a = 0, b = 0;
         if (lane < K && g < sl.hi) {
-            a = tstart[g * (R + 1) + r];
-            b = tstart[g * (R + 1) + r + 1];
+            a = ta[g];
+            b = tz[g];
         }
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            st[k] = (uint32_t)__shfl((int)a, first + k, kWave);
-            nv[k] = (uint32_t)__shfl((int)b, first + k, kWave) - st[k];
+            st[k] = (uint32_t)__shfl((int)a, lane0 + k, kWave);
+            nv[k] = (uint32_t)__shfl((int)b, lane0 + k, kWave) - st[k];
         }
     };
-    int64_t g0 = sl.lo + wave;
+    int64_t g0 = sl.lo + (int64_t)(tid / SW) * K;
     if (g0 < sl.hi) fetch(g0);
     for (; g0 < sl.hi; g0 += step) {
         uint32_t cst[K], cnv[K], mx = 0;
@@ -727,28 +875,54 @@ __global__ __launch_bounds__(kPartThreads) void hist_tsort_range_kernel(
 #pragma unroll
             for (int k = 0; k < K; ++k)
                 w[k] = i < cnv[k] ? __builtin_nontemporal_load(
-                                        reinterpret_cast<const u32x4*>(part + (g0 + k * W) * kTsortSlot) +
+                                        reinterpret_cast<const u32x4*>(part + (g0 + k) * kTsortSlot) +
                                         cst[k] + i)
-                                  : u32x4{~0u, ~0u, ~0u, ~0u};
+                                  : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
             for (int k = 0; k < K; ++k)
+                if (i < cnv[k])
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    add(w[k][q] & 0xFFFFu);
-                    add(w[k][q] >> 16);
-                }
+                    for (int q = 0; q < 4; ++q) {
+                        add(w[k][q] & 0xFFFFu);
+                        add(w[k][q] >> 16);
+                    }
         }
     }
     __syncthreads();
     if (S == 1) {
-        for (uint32_t b = tid; b < tb; b += P) {
-            const uint32_t c = h[b];
-            if (c) out[b0 + b] += c;
+        constexpr int U = 16;   // the bins' old counts load together
+        for (uint32_t b = tid; b < tb; b += U * P) {
+            uint32_t c[U], old[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                c[u] = b + u * P < tb ? h[b + u * P] : 0u;
+                old[u] = 0u;
+                if (c[u]) old[u] = hist[b0 + b + u * P];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (c[u]) hist[b0 + b + u * P] = old[u] + c[u];
         }
     } else {
-        uint32_t* o = out + (size_t)s * bins + b0;
+        uint32_t* o = partial + (size_t)blockIdx.x * kPartBins;
         for (uint32_t b = tid; b < tb; b += P) o[b] = h[b];
     }
+}
+
+// hist[b] += the partials of b's range, where it has several.
+__global__ __launch_bounds__(256) void hist_tsort_merge_kernel(const uint32_t* __restrict__ partial,
+                                                               const uint32_t* __restrict__ first,
+                                                               uint32_t bins,
+                                                               uint32_t* __restrict__ hist) {
+    const uint32_t b = blockIdx.x * 256 + threadIdx.x;
+    const uint32_t r = b >> kPartLog2;   // the same for the whole workgroup
+    if (b >= bins) return;
+    const uint32_t w0 = first[r], w1 = first[r + 1];
+    if (w1 - w0 == 1) return;
+    uint32_t c = 0;
+#pragma unroll 8
+    for (uint32_t w = w0; w < w1; ++w) c += partial[(size_t)w * kPartBins + (b & (kPartBins - 1))];
+    if (c) hist[b] += c;
 }
 
 // Global pool of the team copies that do not fit LDS: per (device, stream),
@@ -820,8 +994,33 @@ constexpr uint32_t kMaxBinTiles = 32;
 constexpr uint32_t kDefaultMaxBinTiles = 4;
 // LDS ranges the default takes before the tile sort (which reads the keys
 // once and moves 2-byte places twice): at 2^28 uniform keys 3 ranges ran at
-// 444 G keys/s against 535 for the tile sort, 2 ranges at 793 against 432.
+// 444 G keys/s against 600 for the tile sort, 2 ranges at 813 against 590 (few
+// keys take up to kMaxBinTiles ranges, see omprt_histogram).
 constexpr uint32_t kDefaultMaxTsortTiles = 2;
+
+// Default shape of the LDS copies.  A team of 1024 threads counts about 8500
+// keys a microsecond and adding its copy into hist takes about 3e-6 us a bin
+// and team (coalesced atomics) and 6e-3 us a team (teams meeting on the same
+// bins), so the time n / (8500 T) + T (3e-6 bins + 6e-3) is least at
+// T = sqrt(39 n / (bins + 2000)): one team a CU for 10^8 keys, 30 teams for 10^6
+// keys and 40 000 bins (16 us; 512 teams of 512 threads, the earlier default,
+// 36), 114 for 10^6 keys and 1000 bins (8.3 against 13).  One team of 1024 a CU
+// also beats two of 512 where a copy leaves room for one team only (2^28 keys,
+// 40 000 bins: 176 against 274 us); with small copies and keys enough for three
+// teams a CU, two of 512 stay 1 % ahead (2^28 keys, 1000 bins: 160 against 162).
+static void hist_shape(int64_t n, uint32_t bins, uint32_t tiles, int cus, int* teams,
+                       int* threads) {
+    const double best = sqrt(39.0 * (double)n / ((double)bins + 2000.0));
+    if (best >= 3.0 * cus && tiles == 1 && bins * 4 <= 64 * 1024) {
+        *teams = 2 * cus;
+        *threads = 512;
+        return;
+    }
+    const int64_t rows = std::min<int64_t>(std::max<int64_t>((int64_t)best, 1),
+                                           std::max<int64_t>(cus / (int64_t)tiles, 1));
+    *teams = (int)(rows * tiles);
+    *threads = 1024;
+}
 
 // Partitioned bins (count, scan, scatter, range, merge), teams x 512
 // threads for the passes over the keys.
@@ -878,7 +1077,7 @@ static omprt_status histogram_partitioned(const int32_t* d_keys, int64_t n, uint
     return OMPRT_OK;
 }
 
-// Tile-sorted bins (scatter into tile slots, range, merge), up to
+// Tile-sorted bins (scatter into tile slots, plan, range, merge), up to
 // kTsortMaxRanges ranges; teams x 512 threads for the pass over the keys.
 static omprt_status histogram_tsorted(const int32_t* d_keys, int64_t n, uint32_t bins,
                                       int32_t* d_hist, int teams, hipStream_t stream) {
@@ -886,59 +1085,62 @@ static omprt_status histogram_tsorted(const int32_t* d_keys, int64_t n, uint32_t
     if (R > kTsortMaxRanges)
         return fail(OMPRT_ERR_INVALID, "tile-sorted histogram: %u bins above %u", bins,
                     kTsortMaxRanges * kPartBins);
-    // no more teams than tiles: a team without keys would still own a slot
-    const uint32_t T = (uint32_t)std::min<int64_t>(teams, (n + kPartTile - 1) / kPartTile);
-    const int64_t per_team = (n + T - 1) / T;
-    const uint32_t NT = (uint32_t)std::max<int64_t>(1, (per_team + kPartTile - 1) / kPartTile);
-    const int64_t G = (int64_t)T * NT;
-    uint32_t S = (uint32_t)((2 * device_cus() + R - 1) / R);
-    S = std::min<uint32_t>(std::max<uint32_t>(S, 1u), 64u);
+    TileSplit ts{};
+    ts.n = n;
+    ts.head = (int)std::min<int64_t>((16 - (reinterpret_cast<uintptr_t>(d_keys) & 15)) % 16 / 4, n);
+    ts.G = (n - ts.head + kPartTile - 1) / kPartTile + (ts.head ? 1 : 0);
+    const uint32_t T = (uint32_t)std::min<int64_t>(teams, ts.G);   // no team without a tile
+    // Workgroups of the counting pass: one a range, and more as there are keys
+    // to count, up to one a CU, or two with so many ranges that whole shares
+    // would leave part of the chip idle.  A further workgroup costs a partial of
+    // 128 KiB written and read (about what 32768 keys cost; with many ranges
+    // three times that, 10^7 keys over 128 ranges: 82 us at 32768, 69 so).
+    const uint32_t cus = (uint32_t)device_cus();
+    const uint32_t most = std::max(R <= 64 ? cus : 2 * cus, R);
+    const int64_t keys_each = R <= 64 ? 32768 : 98304;
+    const uint32_t W = (uint32_t)std::min<int64_t>(most, R + n / keys_each);
     auto up = [](uint64_t b) { return (b + 255) / 256 * 256; };
-    const uint64_t b_part = up((uint64_t)G * kTsortSlot * 2),
-                   b_ts = up((uint64_t)G * (R + 1) * 2),
-                   b_partial = S > 1 ? up((uint64_t)S * bins * 4) : 0;
+    const uint64_t b_part = up((uint64_t)ts.G * kTsortSlot * 2),
+                   b_ts = up((uint64_t)ts.G * (R + 1) * 2), b_cnt = up((uint64_t)R * T * 4),
+                   b_first = up((uint64_t)(R + 1) * 4),
+                   b_partial = W > R ? (uint64_t)W * kPartBins * 4 : 0;
     void* pool = nullptr;
-    if (omprt_status st = pool_get(stream, b_part + b_ts + b_partial, &pool)) return st;
+    if (omprt_status st = pool_get(stream, b_part + b_ts + b_cnt + b_first + b_partial, &pool))
+        return st;
     char* p = static_cast<char*>(pool);
     uint16_t* part = reinterpret_cast<uint16_t*>(p);
     uint16_t* tstart = reinterpret_cast<uint16_t*>(p + b_part);
-    uint32_t* partial = reinterpret_cast<uint32_t*>(p + b_part + b_ts);
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(p + b_part + b_ts);
+    uint32_t* first = reinterpret_cast<uint32_t*>(p + b_part + b_ts + b_cnt);
+    uint32_t* partial = reinterpret_cast<uint32_t*>(p + b_part + b_ts + b_cnt + b_first);
     Workspace* ws = nullptr;
     if (omprt_status st = workspace_get(stream, 1, &ws)) return st;
     uint32_t* hist = reinterpret_cast<uint32_t*>(d_hist);
-    hipLaunchKernelGGL(hist_tsort_scatter_kernel, dim3(T), dim3(kPartThreads), 0, stream, d_keys,
-                       n, bins, R, NT, part, tstart, ws->status());
-    // runs average kPartTile / R places: from 16 ranges on (64 vectors or
-    // fewer) half a wave takes a tile, from 48 on a quarter, from 96 an eighth
-    const void* range_kernel =
-        R >= 96   ? reinterpret_cast<const void*>(hist_tsort_range_kernel<8>)
-        : R >= 48 ? reinterpret_cast<const void*>(hist_tsort_range_kernel<16>)
-        : R >= 16 ? reinterpret_cast<const void*>(hist_tsort_range_kernel<32>)
-                  : reinterpret_cast<const void*>(hist_tsort_range_kernel<64>);
-    const uint32_t lds = std::min(bins, kPartBins) * 4;
-    if (lds > 64 * 1024) {   // past the default dynamic LDS limit: ask for it
-        const hipError_t e =
-            hipFuncSetAttribute(range_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess)
-            return fail(OMPRT_ERR_DEVICE, "histogram: %u bytes of LDS: %s", lds,
-                        hipGetErrorString(e));
-    }
-    uint32_t* dst = S > 1 ? partial : hist;
-    if (R >= 96)
-        hipLaunchKernelGGL(hist_tsort_range_kernel<8>, dim3(R * S), dim3(kPartThreads), lds,
-                           stream, part, tstart, G, R, bins, S, dst);
-    else if (R >= 48)
-        hipLaunchKernelGGL(hist_tsort_range_kernel<16>, dim3(R * S), dim3(kPartThreads), lds,
-                           stream, part, tstart, G, R, bins, S, dst);
-    else if (R >= 16)
-        hipLaunchKernelGGL(hist_tsort_range_kernel<32>, dim3(R * S), dim3(kPartThreads), lds,
-                           stream, part, tstart, G, R, bins, S, dst);
+    hipLaunchKernelGGL(hist_tsort_scatter_kernel, dim3(T), dim3(kPartThreads), 0, stream, d_keys, ts,
+                       bal_split(ts.G, T), bins, R, part, tstart, cnt, ws->status());
+    hipLaunchKernelGGL(hist_tsort_plan_kernel, dim3(1), dim3(1024), 0, stream, cnt, T, R, W, first);
+    const uint32_t lds = (kPartBins + 4) * 4;   // a range's bins and the padding's counter
+    hipError_t attr = hipSuccess;
+    auto range = [&](auto kernel) {   // past the default dynamic LDS limit: ask for it
+        attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (attr == hipSuccess)
+            hipLaunchKernelGGL(kernel, dim3(W), dim3(kRangeThreads), lds, stream, part, tstart, ts.G,
+                               R, bins, first, partial, hist);
+    };
+    // runs average kPartTile / R places: half a wave takes a tile, from 48 ranges
+    // on (21 vectors or fewer) a quarter (2^28 keys: 4 ranges 143 us, 228 with
+    // whole waves; 32 ranges 150, 177 with quarters; 128 ranges 236, 277 with
+    // eighths)
+    if (R >= 48)
+        range(hist_tsort_range_kernel<16>);
     else
-        hipLaunchKernelGGL(hist_tsort_range_kernel<64>, dim3(R * S), dim3(kPartThreads), lds,
-                           stream, part, tstart, G, R, bins, S, dst);
-    if (S > 1)
-        hipLaunchKernelGGL(hist_part_merge_kernel, dim3((bins + 255) / 256), dim3(256), 0, stream,
-                           partial, S, bins, hist);
+        range(hist_tsort_range_kernel<32>);
+    if (attr != hipSuccess)
+        return fail(OMPRT_ERR_DEVICE, "histogram: %u bytes of LDS: %s", lds, hipGetErrorString(attr));
+    if (W > R)
+        hipLaunchKernelGGL(hist_tsort_merge_kernel, dim3((bins + 255) / 256), dim3(256), 0, stream,
+                           partial, first, bins, hist);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(OMPRT_ERR_DEVICE, "histogram launch: %s", hipGetErrorString(e));
     return OMPRT_OK;
@@ -958,7 +1160,9 @@ extern "C" omprt_status omprt_histogram(const int32_t* d_keys, int64_t n, int32_
     if (n > 0 && !d_keys) return fail(OMPRT_ERR_INVALID, "keys is NULL with n > 0");
     if ((reinterpret_cast<uintptr_t>(d_keys) | reinterpret_cast<uintptr_t>(d_hist)) & 3)
         return fail(OMPRT_ERR_INVALID, "keys / hist not 4-byte aligned");
-    int teams = 2 * device_cus(), threads = 512, unroll = 4;
+    const int cus = device_cus();
+    int teams = 2 * cus, threads = 512, unroll = 4;
+    const bool auto_shape = !cfg || (!cfg->num_teams && !cfg->threads_per_team);
     if (cfg) {
         if (cfg->num_teams < 0 || cfg->num_teams > 65535)
             return fail(OMPRT_ERR_INVALID, "num_teams %d", cfg->num_teams);
@@ -1002,15 +1206,21 @@ extern "C" omprt_status omprt_histogram(const int32_t* d_keys, int64_t n, int32_
     const bool part_fits = bins <= (int64_t)kPartMaxRanges * kPartBins &&
                            (uint64_t)n * 2 <= ((uint64_t)16 << 30);
     const bool tsort_fits = part_fits && bins <= (int64_t)kTsortMaxRanges * kPartBins;
+    // few keys: the ranges in one launch (each team reads its block once per
+    // range) while they take less than the partitions' four launches, 25 us:
+    // 2 sqrt(n / 8500 (3e-6 bins + 6e-3)) + 6 < 24 (hist_shape's time at its best
+    // T; 10^5 keys, 2^20 bins: 21 us, 51 before)
+    const bool few_keys = !forced && auto_shape && tiles > kDefaultMaxTsortTiles &&
+                          tiles <= kMaxBinTiles && (double)n * ((double)bins + 2000.0) < 2.3e11;
     if ((flags & OMPRT_CFG_HIST_TILE_SORT) ||
-        (!forced && tiles > kDefaultMaxTsortTiles && tsort_fits))
+        (!forced && tiles > kDefaultMaxTsortTiles && tsort_fits && !few_keys))
         return histogram_tsorted(d_keys, n, (uint32_t)bins, d_hist, teams, stream);
     if ((flags & OMPRT_CFG_HIST_PARTITION) ||
-        (!forced && tiles > kDefaultMaxBinTiles && part_fits))
+        (!forced && tiles > kDefaultMaxBinTiles && part_fits && !few_keys))
         return histogram_partitioned(d_keys, n, (uint32_t)bins, d_hist, teams, stream);
     const bool direct = (flags & OMPRT_CFG_HIST_DIRECT) ||
                         (tiles > kMaxBinTiles && !(flags & OMPRT_CFG_HIST_TEAM_COPY)) ||
-                        (!forced && tiles > kDefaultMaxBinTiles);
+                        (!forced && tiles > kDefaultMaxBinTiles && !few_keys);
     if (direct) {
         Workspace* ws = nullptr;
         if (omprt_status st = workspace_get(stream, 1, &ws)) return st;
@@ -1032,6 +1242,7 @@ extern "C" omprt_status omprt_histogram(const int32_t* d_keys, int64_t n, int32_
         tiles = 1;
         tile_bins = (uint32_t)bins;
     }
+    if (auto_shape && in_lds) hist_shape(n, (uint32_t)bins, tiles, cus, &teams, &threads);
     const uint64_t hbytes = ((uint64_t)tile_bins * 4 + kSharedAlign - 1) / kSharedAlign * kSharedAlign;
     const int64_t rows = std::max<int64_t>(1, teams / (int64_t)tiles);
     const int64_t grid = rows * tiles;

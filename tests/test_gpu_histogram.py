@@ -184,3 +184,35 @@ def test_tile_sort_team_with_fewer_tiles(gpu_lib):
         h0 = g.integers(-1000, 1000, bins).astype(np.int32)
         want, _ = oracle.histogram(keys, bins, hist=h0)
         assert np.array_equal(run(gpu_lib, keys, bins, h0, cfg), want), bins
+
+
+@pytest.mark.parametrize("bins", [300, 40704, 81408, 81409, 32 * 32768, 64 * 32768, 128 * 32768])
+@pytest.mark.parametrize("offset", [0, 1, 3])
+def test_alignment_tiles_and_order(gpu_lib, bins, offset):
+    """Keys off 16-byte alignment (the head is a tile of its own), counts at the edges of a
+    tile of 8192 keys, sorted and constant keys (a wave's vectors hold one key), and keys
+    that all lie in the last bin range (one range takes every counting workgroup), some
+    out of range among them."""
+    g = np.random.Generator(np.random.PCG64(bins + offset))
+    low = max(0, (bins - 1) // 32768 * 32768)
+    for n in (1, 8191, 8192, 8193 + offset, 16384, 300000):
+        for kind in ("uniform", "sorted", "constant", "last range"):
+            if kind == "last range":
+                keys = g.integers(low, bins, n)
+                keys[:: 97] = bins
+            elif kind == "constant":
+                keys = np.full(n, bins // 3)
+            else:
+                keys = g.integers(0, bins, n)
+                if kind == "sorted":
+                    keys.sort()
+            keys = keys.astype(np.int32)
+            h0 = g.integers(-1000, 1000, bins).astype(np.int32)
+            want, _ = oracle.histogram(keys, bins, hist=h0)
+            k = torch.from_numpy(np.concatenate([np.zeros(offset, np.int32), keys])).cuda()[offset:]
+            for cfg in (None, {"flags": gpu_lib.CFG_HIST_TILE_SORT}):
+                h = torch.from_numpy(h0).cuda()
+                gpu_lib.histogram(k, bins, h, config=cfg)
+                torch.cuda.synchronize()
+                assert np.array_equal(h.cpu().numpy(), want), (bins, offset, n, kind, cfg)
+    gpu_lib.workspace_reset()
