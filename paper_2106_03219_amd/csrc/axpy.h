@@ -552,6 +552,142 @@ __device__ __forceinline__ void axpy_union_lines(float a, const float* __restric
     line_passes(f, (nlines + kWave - 1) / kWave);
 }
 
+// Runs of the 64 lanes of a wave at any alignment, moved through LDS a segment
+// of 32 elements of every lane's run per pass (the LDS layout of AxpyLines,
+// eight lanes a segment).  A segment starts where the run does, not on a line:
+// its 16-byte blocks are loaded and stored off 16-byte alignment (a global
+// access needs only its elements'), so no lane has edges of its own, x and y
+// need not be aligned to each other, and the two segments that share a line
+// meet in the caches a pass apart.  The owner executes its elements from LDS in
+// increasing order.  A run's last block may be partial: it is loaded as the
+// run's last four elements and shifted into place, and stored element by
+// element; nothing outside a run is read.  Lanes with `len` 0 have no run; the
+// others have at least kSegmentMin elements, and every run lies within 2^31
+// elements of lane 0's.
+constexpr int kSegmentMin = 4;
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // any element's address
+
+struct AxpySegments {
+    static constexpr int kSeg = kLineBytes / 4;
+    float a;
+    const float* __restrict__ x;   // lane 0's first element
+    float* __restrict__ y;
+    f32x4* __restrict__ xs;
+    f32x4* __restrict__ ys;
+    ff_t* acc;
+    int32_t len;                     // this lane's run
+    int32_t whole;                   // passes in which every lane's segment is whole
+    // the block this lane moves in pass 0, instruction k; its run's last four
+    // elements' start and its end
+    int32_t src[8], last[8], end[8];
+    f32x4 vx[2][8], vy[2][8];
+
+    template <int SET>
+    __device__ __forceinline__ void load(int64_t q) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int32_t e = src[k] + (int32_t)q * kSeg;
+            const int32_t i = e < last[k] ? e : last[k];
+            vx[SET][k] = *reinterpret_cast<const f32x4_any*>(x + i);
+            vy[SET][k] = *reinterpret_cast<const f32x4_any*>(y + i);
+        }
+    }
+    static __device__ __forceinline__ f32x4 shifted(f32x4 v, int d) {   // v[u] <- v[u + d], d 0..3
+        if (d & 1) v = f32x4{v.y, v.z, v.w, v.w};
+        if (d & 2) v = f32x4{v.z, v.w, v.w, v.w};
+        return v;
+    }
+    template <int SET>
+    __device__ __forceinline__ void pass(int64_t q, int64_t np) {
+        const int lane = threadIdx.x & (kWave - 1);
+        const int sw = line_swz(lane);
+        const int32_t at = (int32_t)q * kSeg;
+        const bool full = q < whole;
+        if (!full) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int d = src[k] + at - last[k];
+                if (d > 0 && d < 4) {
+                    vx[SET][k] = shifted(vx[SET][k], d);
+                    vy[SET][k] = shifted(vy[SET][k], d);
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            xs[kWave * k + lane] = vx[SET][k];
+            ys[kWave * k + lane] = vy[SET][k];
+        }
+        if (q + 2 < np) load<SET>(q + 2);
+        wave_lds_order();
+#pragma unroll
+        for (int b = 0; b < kLineSlots; ++b) {
+            const int slot = kLineSlots * lane + (b ^ sw);
+            const f32x4 xx = xs[slot];
+            f32x4 yy = ys[slot];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) yy[u] = __builtin_fmaf(a, xx[u], yy[u]);
+            ys[slot] = yy;
+            const int left = len - at - 4 * b;   // elements of the run from this block on
+#pragma unroll
+            for (int u = 0; u < 4; ++u) comp_add(*acc, full || u < left ? yy[u] : 0.0f);
+        }
+        wave_lds_order();
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int32_t e = src[k] + at;
+            const f32x4 v = ys[kWave * k + lane];
+            if (full || e + 4 <= end[k]) {
+                *reinterpret_cast<f32x4_any*>(y + e) = v;
+            } else {
+#pragma unroll
+                for (int u = 0; u < 3; ++u)
+                    if (e + u < end[k]) y[e + u] = v[u];
+            }
+        }
+        wave_lds_order();
+    }
+};
+
+// The wave's runs [lo, hi) through AxpySegments (every lane calls it; `has`: the
+// lane has a run, of at least kSegmentMin elements; lane 0 has one).
+__device__ __forceinline__ void axpy_run_segments(float a, const float* __restrict__ x,
+                                                  float* __restrict__ y, int64_t lo, int64_t hi,
+                                                  bool has, f32x4* __restrict__ xs,
+                                                  f32x4* __restrict__ ys, ff_t& acc) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t lo0 = __shfl(lo, 0, kWave);
+    const int32_t hi0 = (int32_t)(__shfl(hi, 0, kWave) - lo0);
+    // a lane without a run reads lane 0's last block and stores nothing
+    const int32_t start = has ? (int32_t)(lo - lo0) : 0;
+    const int32_t len = has ? (int32_t)(hi - lo) : 0;
+    const int32_t last = has ? start + len - 4 : hi0 - 4;
+    AxpySegments f;
+    f.a = a;
+    f.x = x + lo0;
+    f.y = y + lo0;
+    f.xs = xs;
+    f.ys = ys;
+    f.acc = &acc;
+    f.len = len;
+    int32_t mn = len, mx = len;
+#pragma unroll
+    for (int m = 1; m < kWave; m <<= 1) {
+        const int32_t p = __shfl_xor(mn, m, kWave), q = __shfl_xor(mx, m, kWave);
+        mn = p < mn ? p : mn;
+        mx = q > mx ? q : mx;
+    }
+    f.whole = mn / AxpySegments::kSeg;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int p = 8 * k + (lane >> 3);
+        f.src[k] = __shfl(start, p, kWave) + 4 * ((lane & 7) ^ line_swz(p));
+        f.end[k] = __shfl(start + len, p, kWave);
+        f.last[k] = __shfl(last, p, kWave);
+    }
+    line_passes(f, (mx + AxpySegments::kSeg - 1) / AxpySegments::kSeg);
+}
+
 // End of the region: the team tree, the cross-team publish and last-team
 // election, and sum[0] <- sum[0] + the launch's total (compensated).
 // epoch was read at the start of the kernel (when gridDim.x > 1).

@@ -54,7 +54,8 @@ hipError_t launch_static_map(int64_t n, int teams, int threads, int64_t dist_chu
 // buffer as the union of the wave's side-by-side runs.  The host takes them
 // when the team is whole waves and x and y are co-aligned to 16 bytes, and
 // sizes lw to the waves that can have a chunk at all (later waves' lanes
-// get none); MODE 0 runs every lane alone.
+// get none); MODE 3: runs at any alignment, a segment of every lane's run per
+// pass through the same buffer; MODE 0 runs every lane alone.
 constexpr int64_t kLinesMinChunk = 64;
 constexpr int64_t kUnionMinChunk = 16;
 constexpr int kLinesWaveBytes = 2 * kStageSlots * 16;
@@ -71,6 +72,7 @@ __global__ __launch_bounds__(MODE ? 512 : 1024) void axpy_sum_kernel(
     const int t = threadIdx.x;
     const uint32_t epoch = T > 1 ? read_epoch(ct.epoch) : 0u;
     ff_t acc = R::identity();
+    const bool co = ((reinterpret_cast<uintptr_t>(x) ^ reinterpret_cast<uintptr_t>(y)) & 15) == 0;
     if (t < P) {
         f32x4* xs = stage + (size_t)(t / kWave) * (2 * kStageSlots);
         f32x4* ys = xs + kStageSlots;
@@ -84,7 +86,20 @@ __global__ __launch_bounds__(MODE ? 512 : 1024) void axpy_sum_kernel(
             }
             const int64_t nc = thread_nchunks(m, P, c, t);
             int64_t j = 0;
-            if (MODE && t / kWave < lw) {
+            if (MODE == 3 && t / kWave < lw) {
+                // the rounds in which every lane of the wave has a chunk, or, where
+                // the lanes alone would go element by element, any has (chunk
+                // counts do not grow with the thread number)
+                const int64_t rounds =
+                    c == 0 ? 1 : thread_nchunks(m, P, c, co ? t | (kWave - 1) : t & ~(kWave - 1));
+                for (; j < rounds; ++j) {
+                    const Range ch = thread_chunk(blk.lo, m, P, c, t, j < nc ? j : 0);
+                    const bool mine = j < nc;
+                    const bool run = mine && ch.hi - ch.lo >= kSegmentMin;
+                    if (__ballot(run) & 1) axpy_run_segments(a, x, y, ch.lo, ch.hi, run, xs, ys, acc);
+                    if (mine && !run) axpy_elems(a, x, y, ch.lo, ch.hi, acc);
+                }
+            } else if (MODE && t / kWave < lw) {
                 // Rounds in which every lane of the wave has a chunk (chunk
                 // counts do not grow with the thread number, so the wave's
                 // last lane has the fewest) run through LDS.
@@ -151,25 +166,48 @@ hipError_t launch_axpy_sum(float a, const float* x, float* y, float* sum, int64_
         mode = 1;
         lw = lw_lines;
     }
+    // Segments (before -> now, us; 256 x 512 threads unless said).  Not co-aligned, at
+    // least half a wave of chunks a block (with fewer, most lanes of a pass
+    // idle: 2048 x 256 threads, 1e6, chunk 200 76 -> 103): the other ways go
+    // element by element.  2^26 + 77: chunk 64 1088 -> 201, 0 1084 -> 235, 500
+    // 1621 -> 248; 7e6: 75 -> 24, 102 -> 26; chunk 16 1e6 15.0 -> 13.3; chunk
+    // 12 1.6e7 80 -> 59, but 1e6 13.0 -> 13.8.  Co-aligned, off the line grid,
+    // inside the last-level cache: chunk 32 (1.6e7 45.5 -> 37.0, 2^25 87 -> 68),
+    // 20 to 31 (2^25 85 -> 75, 1e6 12.3 -> 13.0; 2^26 + 77 159 -> 165), and
+    // chunks of 64 to 128 with between one wave and half a round of them a
+    // block, where a lane has few lines to hide its edges behind (chunk 64 2e6
+    // 17.9 -> 14.2, 128 3e6 30.3 -> 17.7; past half a round chunk 100 1.2e7
+    // 39.5 -> 49).
+    const int64_t block_chunks = chunk > 0 ? (m_hi + chunk - 1) / chunk : threads;
+    const int64_t run = chunk > 0 ? chunk : m_hi / threads;
+    const bool co_segments =
+        !whole_runs && n < ((int64_t)1 << 26) &&
+        (chunk == 32 || (chunk >= 20 && chunk < 32 && n >= ((int64_t)1 << 22)) ||
+         (chunk >= 64 && chunk <= 128 && block_chunks >= kWave && block_chunks <= threads / 2));
+    const bool any_segments =
+        block_chunks >= kWave / 2 && run < ((int64_t)1 << 24) &&
+        (chunk == 0 ? run >= 8 : chunk >= 16 || (chunk >= 12 && n >= ((int64_t)1 << 23)));
+    if (waves && n > 0 && (co_aligned ? co_segments : any_segments)) {
+        mode = 3;
+        lw = (int)std::min<int64_t>(threads / kWave, (block_chunks + kWave - 1) / kWave);
+    }
     if (mode == 0 || lw == 0) {
         hipLaunchKernelGGL(axpy_sum_kernel<0>, dim3(teams), dim3(block), 0, stream, a, x, y, sum,
                            n, threads, dist_chunk, chunk, 0, dct);
         return hipGetLastError();
     }
     const size_t lds = (size_t)lw * kLinesWaveBytes;
-    const void* fn = mode == 2 ? reinterpret_cast<const void*>(axpy_sum_kernel<2>)
-                               : reinterpret_cast<const void*>(axpy_sum_kernel<1>);
+    auto* const kernel = mode == 3   ? axpy_sum_kernel<3>
+                         : mode == 2 ? axpy_sum_kernel<2>
+                                     : axpy_sum_kernel<1>;
     if (lds > 64 * 1024) {   // past the default dynamic LDS limit: ask for it
         const hipError_t attr =
-            hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (attr != hipSuccess) return attr;
     }
-    if (mode == 2)
-        hipLaunchKernelGGL(axpy_sum_kernel<2>, dim3(teams), dim3(block), lds, stream, a, x, y, sum,
-                           n, threads, dist_chunk, chunk, lw, dct);
-    else
-        hipLaunchKernelGGL(axpy_sum_kernel<1>, dim3(teams), dim3(block), lds, stream, a, x, y, sum,
-                           n, threads, dist_chunk, chunk, lw, dct);
+    hipLaunchKernelGGL(kernel, dim3(teams), dim3(block), lds, stream, a, x, y, sum, n, threads,
+                       dist_chunk, chunk, lw, dct);
     return hipGetLastError();
 }
 

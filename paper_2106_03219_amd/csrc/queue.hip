@@ -138,7 +138,9 @@ __global__ __launch_bounds__(1024) void queue_map_kernel(QueueCfg qc, int64_t n,
 // order, line_rot, for dynamic chunks, whose runs sit a multiple of 4 KiB
 // apart for power-of-two chunks; MODE 3: in increasing order, for guided
 // chunks, which rotating measured slower), or the union of the wave's runs
-// (MODE 2, for dynamic chunks of 16 to kUnionRun iterations).
+// (MODE 2, for dynamic chunks of 16 to kUnionRun iterations).  MODE 4: every
+// round goes through the buffer, a segment of each lane's chunk per pass, at
+// any alignment and with lanes that hold no chunk.
 template <bool ONE, int MODE>
 __global__ __launch_bounds__(512) void queue_axpy_kernel(QueueCfg qc, float a,
                                                           const float* __restrict__ x,
@@ -165,7 +167,27 @@ __global__ __launch_bounds__(512) void queue_axpy_kernel(QueueCfg qc, float a,
             Grab g;
             const float* xb = x + blk.lo;
             float* yb = y + blk.lo;
-            while (queue_next(&queue, bq.nchunks, qc.tickets, g)) {
+            if (MODE == 4) {
+                // a wave takes 64 neighbouring chunks at a time and stays
+                // together to the end of the queue (teams are whole waves)
+                const int lane = t & (kWave - 1);
+                f32x4* xs = stage + (size_t)(t / kWave) * (2 * kStageSlots);
+                for (;;) {
+                    uint64_t base = 0;
+                    if (lane == 0) base = atomicAdd((unsigned long long*)&queue, (unsigned long long)kWave);
+                    base = read_lane64(base, 0);
+                    if ((int64_t)base >= bq.nchunks) break;
+                    const int64_t tk = (int64_t)base + lane;
+                    const bool mine = tk < bq.nchunks;
+                    const Range ch = bq.chunk(mine ? tk : bq.nchunks - 1);
+                    const bool run = mine && ch.hi - ch.lo >= kSegmentMin;
+                    // (of neighbouring chunks the first is the longest)
+                    if (__ballot(run) & 1)
+                        axpy_run_segments(a, xb, yb, ch.lo, ch.hi, run, xs, xs + kStageSlots, acc);
+                    if (mine && !run) axpy_elems(a, xb, yb, ch.lo, ch.hi, acc);
+                }
+            }
+            while (MODE != 4 && queue_next(&queue, bq.nchunks, qc.tickets, g)) {
                 if (ONE) {
                     // one-iteration chunks: the lanes of a wave hold neighbouring
                     // iterations; the tickets' loads issue together
@@ -449,9 +471,37 @@ extern "C" omprt_status omprt_axpy_sum_queue(float a, const float* d_x, float* d
             hipLaunchKernelGGL(kernel, dim3(teams), dim3(block), lds, stream, qc, a, d_x, d_y,
                                d_sum, s->n, s->dist_chunk, ct);
     };
+    // Segments, where half a wave of chunks can be taken at once (before ->
+    // now, us, default launch).  Not co-aligned, the other ways go element by
+    // element: 2^26 + 77 dynamic 64 605 -> 188, guided 16 1162 -> 225; dynamic
+    // 16 1e6 14.8 -> 12.9, 8 3e6 22.3 -> 22.7, 8 2^25 153 -> 149; guided 1 1e6
+    // 14.0 -> 16.7, 3e6 27.0 -> 22.9.  Co-aligned, off the line grid: dynamic
+    // 32 (7e6 34.5 -> 22.2, 2^26 + 77 231 -> 161), 64 (31.6 -> 26.7, 198 ->
+    // 191), 20 to 31 (24: 29.8 -> 28.1, 211 -> 192; 2e6 16.0 -> 17.6); 16 and
+    // 100 ran alike through the union and the lines.  Guided rounds, whose
+    // lanes' chunks shrink along the wave so that few have lines: 16 7e6 43.4
+    // -> 31.3, 2^24 67 -> 58; not from where the first chunks are long (2^25,
+    // 512 iterations: 107 -> 114; 2^26: 185 -> 228), for chunks past two
+    // segments (100: 7e6 32.2 -> 36.3) or the smallest blocks (7: 1e5 10.0 ->
+    // 11.9).
+    const int64_t m_hi = s->dist_chunk ? std::min<int64_t>(s->dist_chunk, s->n)
+                                       : (s->n + teams - 1) / teams;
+    const int64_t first = kind == KIND_GUIDED ? std::max((m_hi + threads - 1) / threads, c) : c;
+    bool segments = waves && first < ((int64_t)1 << 24) && m_hi / c >= kWave / 2;
+    if (kind == KIND_GUIDED)
+        segments = segments && (co ? c <= 64 && m_hi / c >= kWave && first <= 384 && m_hi >= 1024
+                                   : c >= 16 || m_hi >= 8192);
+    else
+        segments = segments &&
+                   (co ? !(on_grid && c % 32 == 0) &&
+                             (c == 32 || c == 64 ||
+                              (c >= 20 && c < 32 && s->n >= ((int64_t)1 << 22)))
+                       : c >= 16 || (c >= 8 && s->n >= ((int64_t)1 << 23)));
     if (kind == KIND_DYNAMIC && qc.cmin == 1) {
         hipLaunchKernelGGL((queue_axpy_kernel<true, 0>), dim3(teams), dim3(block), 0, stream,
                            qc, a, d_x, d_y, d_sum, s->n, s->dist_chunk, ct);
+    } else if (segments) {
+        launch_staged(queue_axpy_kernel<false, 4>);
     } else if (waves && co && union_runs) {
         launch_staged(queue_axpy_kernel<false, 2>);
     } else if (lines && kind == KIND_DYNAMIC) {

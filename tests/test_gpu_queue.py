@@ -112,3 +112,37 @@ def test_queue_axpy_2pow26_all_chunks_agree(gpu_lib):
     xh, yh = x[idx].cpu().numpy(), y0[idx].cpu().numpy()
     ry, _ = oracle.axpy_sum(0.7, xh, yh)
     assert np.array_equal(yref[idx].cpu().numpy().view(np.uint32), ry.view(np.uint32))
+
+
+# (n, T, P, dist_chunk, chunk, x offset, y offset): x and y not co-aligned, or
+# blocks off the line grid; last chunks of 1, 2 and 3 elements, a last round of
+# one lane, chunks of exactly two segments and one element over, chunk 0
+SEGMENTS = [
+    (3 * 20011, 3, 64, 0, 32, 0, 0), (64 * 32 + 1, 1, 64, 0, 32, 1, 1), (2 * 64 * 64 + 77, 2, 256, 0, 64, 0, 0),
+    (2 * 70 * 127 + 3, 2, 256, 0, 127, 2, 2), (65 * 24 + 2, 1, 128, 0, 24, 1, 0),
+    (5 * 33 * 65 + 3, 5, 64, 0, 65, 0, 3), (7001, 2, 128, 1733, 16, 3, 1), (4097, 3, 128, 0, 0, 0, 1),
+    (9 << 20 | 5, 64, 512, 0, 12, 2, 1), ((4 << 20) + 7, 256, 64, 0, 20, 0, 0), (50003, 3, 64, 0, 7, 0, 2),
+]
+
+
+@pytest.mark.parametrize("kind", ["static", "dynamic", "guided"])
+@pytest.mark.parametrize("case", SEGMENTS)
+def test_axpy_segments(gpu_lib, kind, case):
+    om = gpu_lib
+    n, T, P, dc, c, xo, yo = case
+    pad = 40
+    xh = synth.f32_normal(n + 2 * pad, 14)
+    yh = synth.f32_normal(n + 2 * pad, 15)
+    lo_x, lo_y = pad + xo, pad + yo
+    ref_y, ref_s = oracle.axpy_sum(0.7, xh[lo_x:lo_x + n], yh[lo_y:lo_y + n], 0.25)
+    xb, yb = torch.from_numpy(xh).cuda(), torch.from_numpy(yh.copy()).cuda()
+    x, y = xb[lo_x:lo_x + n], yb[lo_y:lo_y + n]
+    s = torch.tensor([0.25], dtype=torch.float32, device="cuda")
+    if kind == "static":
+        om.axpy_sum(0.7, x, y, s, T, P, dc, c)
+    else:
+        om.axpy_sum_queue(kind, 0.7, x, y, s, T, P, dc, c)
+    torch.cuda.synchronize()
+    out = yb.cpu().numpy()
+    check_axpy(out[lo_y:lo_y + n], s.item(), ref_y, ref_s, 0.25, (kind, case))
+    assert np.array_equal(out[:lo_y], yh[:lo_y]) and np.array_equal(out[lo_y + n:], yh[lo_y + n:])
