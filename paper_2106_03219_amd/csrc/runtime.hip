@@ -166,7 +166,8 @@ int device_cus() {
 // measured fastest on gfx950: 6.97 TB/s fp32, 7.11 TB/s int64 at 2^28) and
 // one team per 32 KiB of input (one unrolled sweep) below that.  The AXPY
 // body (body 1; body 2 is the AXPY-then-sum region) keeps 256 threads and
-// up to 8 teams per CU, except for user chunks (2^26 fp32 on gfx950): the
+// up to 8 teams per CU for the smallest loops and for most past the
+// last-level cache, and otherwise looks at the chunk (2^26 fp32 on gfx950): the
 // AXPY's chunk 1 takes one team of 512 threads per CU (5.35 TB/s against
 // 4.95 with 8 teams of 256; the region's stays at 6.0 with the latter), and
 // chunks of more than 512 iterations take 512 threads and about 128 chunks
@@ -198,6 +199,31 @@ static LaunchCfg heuristic(int64_t n, int dtype, int body, int64_t chunk) {
         } else {
             t = std::min(waves, cus);
             c.threads = (int)(kLanes * std::min<int64_t>((waves + t - 1) / t, 8));
+        }
+    } else if (body && chunk != 1 && n >= ((int64_t)1 << 19)) {
+        // One team of 512 a CU instead of eight of 256: with the loop's data in
+        // the last-level cache a launch of many short teams is bound by their
+        // starts, slots and single rounds.  us, eight of 256 -> one of 512: chunk
+        // 0 1e6 18.9 -> 12.4, 2^22 35.8 -> 14.7, 1.2e7 42 -> 35; 64 7e6 46.0 ->
+        // 25.7; 100 1.2e7 57 -> 40; two loops, chunk 64 7e6 52 -> 34, 2^24 60 ->
+        // 53; 3e5 alike.  Chunks of 2 and 3 are lane-alone runs that want more
+        // waves: two teams of 512 (2: 2^22 36.8 -> 19.8, 2^24 57.9 -> 43.0; 3:
+        // 52.5 -> 37.3), two loops from 2^22 on the general launch (2: 7e6 53.5
+        // -> 56.9 with one).  Past the cache the general launch streams as well
+        // or better (2^26 chunk 64 148.7 -> 152.9, 0 144.9 -> 153.3) but for runs
+        // that are not whole lines (7: 284 -> 211, 100: 196 -> 160) and, until
+        // the blocks are long, chunks past 256 (500, 5e7 170 -> 134).
+        const bool cached = n <= (body == 2 ? (int64_t)1 << 24 : (int64_t)5 << 22);
+        const bool two_or_three = chunk == 2 || chunk == 3;
+        if (two_or_three && n >= ((int64_t)1 << 22)) {
+            if (body == 1 && (cached || n <= ((int64_t)1 << 25))) {
+                c.threads = 512;
+                cap = 2 * cus;
+            }
+        } else if (cached || (body == 1 && chunk > 4 && chunk < 128 && chunk % 16 && chunk != 8) ||
+                   (chunk > 256 && n < ((int64_t)1 << 26))) {
+            c.threads = 512;
+            cap = cus;
         }
     }
     t = std::min<int64_t>(std::max<int64_t>(t, 1), cap);

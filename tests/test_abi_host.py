@@ -209,6 +209,21 @@ def test_heuristic_large_user_chunks():
     assert pick(300 * 64 * 1024, 1024) == (256, 128)   # 300 waves: two a team on 44 CUs
 
 
+@pytest.mark.parametrize("n,chunk,launch", [
+    ((1 << 19) - 1, 64, (384, 256)), (1 << 19, 64, (256, 512)), (5 << 22, 0, (256, 512)),
+    ((5 << 22) + 1, 0, (2048, 256)), ((5 << 22) + 1, 100, (256, 512)),
+    ((5 << 22) + 1, 8, (2048, 256)), ((1 << 26) - 1, 500, (256, 512)),
+    (1 << 26, 500, (2048, 256)), (1 << 26, 7, (256, 512)), ((1 << 22) - 1, 2, (256, 512)),
+    (1 << 22, 2, (512, 512)), ((1 << 25) + 1, 3, (2048, 256)),
+])
+def test_heuristic_axpy_body(n, chunk, launch):
+    """The edges of the AXPY body's default launch for chunks up to 512 (256 compute units
+    without a GPU): one team of 512 threads a CU where the loop's data fits the last-level
+    cache, two for chunks of 2 and 3, else the general launch of up to 8 teams of 256 a CU."""
+    cfg, src = om.resolve_config(n, om.F32, "sum", 1, chunk)
+    assert src == 3 and (cfg["teams"], cfg["threads"]) == launch
+
+
 def test_model_features():
     f = om.model_features(1 << 20, om.F32, "sum", 0, -1)
     assert f[0] == 20.0 and f[3] == 1.0 and sum(f[1:6]) == 1.0
