@@ -407,15 +407,19 @@ omprt_status omprt_reduce_loc(const void *d_in, int64_t n, int32_t dtype,
  * bf16 sums), arithmetic and determinism are those of omprt_reduce.
  * rows == 0 or m == 0 leaves d_x unchanged.  d_in and d_x need element
  * alignment; a 16-byte aligned d_in streams in 16-byte vectors when its rows
- * (whole, or cut into column tiles) keep that alignment, otherwise one
- * element per load.  The runtime cuts the block into column tiles and row
+ * (whole, or cut into column tiles) keep that alignment, otherwise in vectors
+ * at any element's address, or, for fewer than 16 bytes of columns a team
+ * could hold or with explicit vec_bytes of the element size or an explicit
+ * unroll, one element per load.  The runtime cuts the block into column tiles and row
  * periods (omprt_reduce_array_plan); teams on one tile combine through
  * tagged slots and wrap-around-increment elections, in one or two levels
  * of groups.
  * cfg (may be NULL): num_teams is the total team count aimed at (default
- * one per compute unit, two with element loads); threads_per_team 64..512 in steps of 64 (default
- * 512); unroll 1, 2, 4 or 8 loads in flight per lane (default 4 with
- * 16-byte loads, which take at most 4; 8 with element loads).  A team
+ * at most one per compute unit, two with element loads, and fewer where the
+ * combination of so many would cost more than it saves); threads_per_team
+ * 64..512 in steps of 64 (default 512); unroll 1, 2, 4 or 8 loads in flight
+ * per lane (default 4 with aligned 16-byte loads, which take at most 4, 2 for
+ * column tiles of fp32 sums; 8 with element loads).  A team
  * gathers its private copies in LDS at the end: threads x unroll x elements
  * per load of them, or threads x elements per load when each load layer
  * holds whole rows of the tile; they must fit 64 KiB.  The default unroll
@@ -434,7 +438,9 @@ omprt_status omprt_reduce_array(const void *d_in, int64_t rows, int64_t m,
 /*
  * The launch omprt_reduce_array would make (host only, no device work):
  * h_out8 = {tile width W, rows per period R, column tiles, row teams per
- * tile, election groups per tile, bytes per load, threads, unroll}.
+ * tile, election groups per tile, bytes per load, threads, unroll}.  For
+ * vectors at any element's address the bytes are the element's and the unroll
+ * counts elements.
  * aligned16 says whether d_in would be 16-byte aligned.  rows, m >= 1.
  */
 omprt_status omprt_reduce_array_plan(int64_t rows, int64_t m, int32_t dtype,

@@ -30,13 +30,13 @@
 
 namespace omprt {
 
-static ArrayLauncher array_launcher(int dtype, int op, bool vec, int u) {
+static ArrayLauncher array_launcher(int dtype, int op, int loads, int u) {
     switch (dtype) {
-        case DT_I32: return array_launcher_i32(op, vec, u);
-        case DT_I64: return array_launcher_i64(op, vec, u);
-        case DT_F32: return array_launcher_f32(op, vec, u);
-        case DT_F64: return array_launcher_f64(op, vec, u);
-        case DT_BF16: return array_launcher_bf16(op, vec, u);
+        case DT_I32: return array_launcher_i32(op, loads, u);
+        case DT_I64: return array_launcher_i64(op, loads, u);
+        case DT_F32: return array_launcher_f32(op, loads, u);
+        case DT_F64: return array_launcher_f64(op, loads, u);
+        case DT_BF16: return array_launcher_bf16(op, loads, u);
     }
     return nullptr;
 }
@@ -182,9 +182,29 @@ static int64_t lds_entries(const ArrayGeom& g, int64_t layer, int U) {
     return need;
 }
 
+// Geometry for ragged loads of E elements (array_kernel.h): the element loads'
+// tiles, a period of U layers of RL rows, one vector a lane and layer.
+static bool ragged_geometry(int64_t rows, int64_t m, int E, int P, int U, int ab, ArrayGeom* g) {
+    g->rows = rows;
+    g->m = m;
+    const int64_t wmax = std::min<int64_t>(kTileCols, (int64_t)P * E);
+    const int64_t tiles = (m + wmax - 1) / wmax;
+    g->W = (m + tiles - 1) / tiles;
+    if (tiles > INT32_MAX) return false;
+    g->col_tiles = (int32_t)((m + g->W - 1) / g->W);
+    const int64_t wl = m - (g->col_tiles - 1) * g->W;   // the last tile's width
+    if (tiles > 1 && wl < E) return false;
+    g->RL = (int32_t)(g->col_tiles == 1 ? (int64_t)P * E / m : P / ((g->W + E - 1) / E));
+    g->RL = (int32_t)std::min<int64_t>(g->RL, kMaxLdsBytes / (ab * g->W * U));
+    if (g->RL < 1 || g->RL * g->W < E) return false;
+    g->R = (int64_t)U * g->RL;
+    g->np = rows / g->R;
+    return true;
+}
+
 struct ArrayPlan {
     ArrayGeom g;
-    bool vec;
+    int loads;   // ArrayLoads
     int threads, unroll;
     size_t lds;
 };
@@ -223,13 +243,35 @@ static omprt_status plan_array(int64_t rows, int64_t m, int dtype, int op, const
     ArrayPlan pl{};
     pl.threads = P;
     bool found = false;
-    // 16-byte loads first, then element loads; the default unroll is lowered
-    // until the private copies fit LDS, an explicit one is kept or dropped.
+    // 16-byte loads first, then ragged, then element loads; the default unroll
+    // is lowered until the private copies fit LDS, an explicit one is kept or
+    // dropped.
     for (int pass = allow_vec ? 0 : 1; pass < 2 && !found; ++pass) {
         const bool vec = pass == 0;
+        if (!vec && allow_vec && !explicit_u) {
+            const int E = 16 / esize;
+            for (int u = 2; u >= 1 && !found; u /= 2) {
+                ArrayGeom g{};
+                if (!ragged_geometry(rows, m, E, P, u, ab, &g)) continue;
+                if (u > 1 && g.np < device_cus() / g.col_tiles) continue;
+                pl.g = g;
+                pl.loads = kRagged;
+                pl.unroll = u;
+                pl.lds = (size_t)std::max<int64_t>(g.RL * g.W, P) * ab;
+                found = true;
+            }
+            if (found) break;
+        }
         if (vec && (reinterpret_cast<uintptr_t>(in) & 15)) continue;
         const int E = vec ? 16 / esize : 1;
-        const int u0 = vec ? std::min(U, 4) : (explicit_u ? U : 8);   // element loads: 8 in flight
+        // element loads: 8 in flight; vectors of column tiles of fp32 pairs, two
+        // and two of the next period (65536 x 1000 55.6 -> 53.2 us; bf16 36.4 ->
+        // 36.9)
+        const bool tiled = m > std::min<int64_t>(kTileCols, (int64_t)P * E * 4);
+        const int u0 = explicit_u                                       ? (vec ? std::min(U, 4) : U)
+                       : !vec                                           ? 8
+                       : tiled && dtype == DT_F32 && ab == 8            ? 2
+                                                                        : 4;
         for (int u = u0; u >= 1 && !found; u /= 2) {
             ArrayGeom g{};
             if (array_geometry(rows, m, E, (int64_t)P * E * u, &g)) {
@@ -238,7 +280,7 @@ static omprt_status plan_array(int64_t rows, int64_t m, int dtype, int op, const
                     (size_t)std::max<int64_t>(lds_entries(g, (int64_t)P * E, u), P) * ab;
                 if (bytes <= (size_t)kMaxLdsBytes) {
                     pl.g = g;
-                    pl.vec = vec;
+                    pl.loads = vec ? kVectors : kElements;
                     pl.unroll = u;
                     pl.lds = bytes;
                     found = true;
@@ -252,18 +294,58 @@ static omprt_status plan_array(int64_t rows, int64_t m, int dtype, int op, const
                     "no launch geometry: the private copies of threads %d x unroll %d do not "
                     "fit %d bytes of LDS", P, U, kMaxLdsBytes);
     ArrayGeom& g = pl.g;
-    // default: one team per compute unit with 16-byte loads, two with element
-    // loads (which keep a quarter of the bytes in flight per lane or less)
-    if (!want_teams) want_teams = device_cus() * (pl.vec ? 1 : 2);
+    // at most one team per compute unit with vectors, two with element loads
+    // (which keep a quarter of the bytes in flight per lane or less)
+    const bool choose = !want_teams;
+    if (choose) want_teams = device_cus() * (pl.loads == kElements ? 2 : 1);
     int64_t rt = std::max<int64_t>(1, want_teams / g.col_tiles);
     rt = std::min<int64_t>(rt, std::max<int64_t>(1, g.np));
-    g.rt = (int32_t)rt;
     // Election groups: as many teams as the last one can fold with at most
     // kFoldItems partials per thread (fold_group); one group when all fit.
     const int64_t wc_max = std::min(g.W, m);
     const int64_t per_col = wc_max * 2 > P ? 1 : P / wc_max;   // threads per column
     const int64_t rounds = (wc_max + P - 1) / P;               // columns per thread
     const int64_t gs_max = std::max<int64_t>(2, kFoldItems * per_col / rounds);
+    if (choose && rt > 1) {
+        // Fewer row teams make the combination shorter and the streams longer.
+        // Estimated us (fitted on gfx950 over 10^3 to 10^8 elements, 4 to 256
+        // teams a tile): a period's latency and its bytes, twice that from 64 MiB
+        // on; a level of groups its teams' serial increments, its
+        // batches of slot loads and the partials a thread folds in a row.
+        const int nw = ab / 4;
+        const bool pairs = dtype != DT_I32 && dtype != DT_I64 && (op == OP_SUM || op == OP_PROD);
+        const double part = !pairs ? 0.05 : nw == 2 ? 0.2 : 0.4;
+        const int64_t batch = nw <= 2 ? 16 : 8;   // fold_tagged
+        auto level = [&](int64_t teams) {
+            const int64_t parts = (teams + per_col - 1) / per_col * rounds;
+            return 0.018 * teams + 1.5 * ((parts + batch - 1) / batch) + part * parts;
+        };
+        const double kib = (double)g.R * wc_max * esize / 1024.0;
+        const double period = (0.1 + 0.25 / 16 * kib) *
+                              (rows * m * esize > ((int64_t)64 << 20) ? 2.0 : 1.0);
+        auto cost = [&](int64_t r) {
+            const int64_t gs = std::min(r, gs_max), ng = (r + gs - 1) / gs;
+            return period * ((g.np + r - 1) / r) + (r > 1 ? level(gs) : 0.0) +
+                   (ng > 1 ? 2.5 + level(ng) : 0.0);
+        };
+        int64_t best = rt;
+        double least = cost(rt) - 1.0;   // the estimate's own error
+        auto consider = [&](int64_t r) {
+            if (r < 1 || r > rt) return;
+            const double c = cost(r);
+            if (c < least) {
+                least = c;
+                best = r;
+            }
+        };
+        consider(gs_max);
+        consider(per_col * batch / rounds);   // one batch
+        // by whole numbers of periods a team
+        for (int64_t k = (g.np + rt - 1) / rt; k <= g.np; k += std::max<int64_t>(1, k / 4))
+            consider((g.np + k - 1) / k);
+        rt = best;
+    }
+    g.rt = (int32_t)rt;
     g.gs = (int32_t)std::min(rt, gs_max);
     g.ng = (int32_t)((rt + g.gs - 1) / g.gs);
     *out = pl;
@@ -310,7 +392,7 @@ extern "C" omprt_status omprt_reduce_array(const void* d_in, int64_t rows, int64
         ct = ArrayCross{ws.slots(), ws.slots() + (int64_t)g.rt * m * nw, ws.ctrs(), ws.done(),
                         ws.epoch(), ws.status()};
     }
-    const ArrayLauncher f = array_launcher(dtype, op, pl.vec, pl.unroll);
+    const ArrayLauncher f = array_launcher(dtype, op, pl.loads, pl.unroll);
     if (!f) return fail(OMPRT_ERR_UNSUPPORTED, "no array kernel for this combination");
     if ((int64_t)g.col_tiles * g.rt > INT32_MAX) return fail(OMPRT_ERR_INVALID, "grid too large");
     f(d_in, d_x, g, ct, pl.threads, pl.lds, stream);
@@ -330,7 +412,8 @@ extern "C" omprt_status omprt_reduce_array_plan(int64_t rows, int64_t m, int32_t
     const void* fake = reinterpret_cast<const void*>(aligned16 ? (uintptr_t)256 : (uintptr_t)260);
     if (omprt_status st = plan_array(rows, m, dtype, op, fake, cfg, &pl)) return st;
     const int64_t v[8] = {pl.g.W, pl.g.R, pl.g.col_tiles, pl.g.rt, pl.g.ng,
-                          pl.vec ? 16 : dtype_bytes(dtype), pl.threads, pl.unroll};
+                          pl.loads == kVectors ? 16 : dtype_bytes(dtype), pl.threads,
+                          pl.loads == kRagged ? pl.unroll * (16 / dtype_bytes(dtype)) : pl.unroll};
     for (int i = 0; i < 8; ++i) h_out8[i] = v[i];
     return OMPRT_OK;
 }

@@ -3,8 +3,8 @@
 
 namespace omprt {
 
-ArrayLauncher array_launcher_bf16(int op, bool vec, int u) {
-    return array_launcher_impl<DT_BF16>(op, vec, u);
+ArrayLauncher array_launcher_bf16(int op, int loads, int u) {
+    return array_launcher_impl<DT_BF16>(op, loads, u);
 }
 
 }  // namespace omprt

@@ -3,8 +3,8 @@
 
 namespace omprt {
 
-ArrayLauncher array_launcher_f32(int op, bool vec, int u) {
-    return array_launcher_impl<DT_F32>(op, vec, u);
+ArrayLauncher array_launcher_f32(int op, int loads, int u) {
+    return array_launcher_impl<DT_F32>(op, loads, u);
 }
 
 }  // namespace omprt

@@ -3,8 +3,8 @@
 
 namespace omprt {
 
-ArrayLauncher array_launcher_i64(int op, bool vec, int u) {
-    return array_launcher_impl<DT_I64>(op, vec, u);
+ArrayLauncher array_launcher_i64(int op, int loads, int u) {
+    return array_launcher_impl<DT_I64>(op, loads, u);
 }
 
 }  // namespace omprt

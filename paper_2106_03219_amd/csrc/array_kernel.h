@@ -19,6 +19,7 @@ struct ArrayGeom {
     int32_t rt;           // row teams per tile
     int32_t gs;           // teams per election group
     int32_t ng;           // groups per tile
+    int32_t RL;           // rows per layer (ragged loads: R = U * RL), else 0
 };
 
 struct ArrayCross {
@@ -124,15 +125,28 @@ __device__ __forceinline__ void fold_group(const uint64_t* first, int64_t stride
     fold_rows<R>(lds, tpc, wc);
 }
 
-// Loads of the streaming loop: one 16-byte vector (stream.h) or one element.
-template <int DT, bool VEC>
+// How the streaming loop loads: one element; one 16-byte vector at a 16-byte
+// aligned address (stream.h); or one 16-byte vector at any element's address.
+enum ArrayLoads { kElements, kVectors, kRagged };
+
+template <int DT, int LD>
 struct ArrayLoad {
     using L = VecLoad<DT, 16>;
     using S = typename DType<DT>::S;
     using T = typename L::T;
     static constexpr int E = L::PER;
     static __device__ __forceinline__ T load(const S* p) {
-        return L::load(reinterpret_cast<const T*>(p));
+        if constexpr (LD == kRagged) {
+            typedef T Any __attribute__((aligned(sizeof(S))));
+            // (nontemporal for 8-byte elements: 65536 x 1001 fp64 104.6 -> 99.3 us;
+            // fp32 52.4 -> 53.1)
+            if constexpr (sizeof(S) == 8)
+                return __builtin_nontemporal_load(reinterpret_cast<const Any*>(p));
+            else
+                return *reinterpret_cast<const Any*>(p);
+        } else {
+            return L::load(reinterpret_cast<const T*>(p));
+        }
     }
     template <class R>
     static __device__ __forceinline__ void fold(typename R::Acc* acc, const T& v) {
@@ -141,7 +155,7 @@ struct ArrayLoad {
     }
 };
 template <int DT>
-struct ArrayLoad<DT, false> {
+struct ArrayLoad<DT, kElements> {
     using S = typename DType<DT>::S;
     using T = S;
     static constexpr int E = 1;
@@ -152,7 +166,68 @@ struct ArrayLoad<DT, false> {
     }
 };
 
-template <int DT, int OP, bool VEC, int U>
+// The streaming loop over periods [lo, hi) of `step` elements: each lane loads
+// a vector (or element) at each of its U offsets and folds it into the copies
+// of that slot.  AHEAD: the next period's loads are issued before a period is
+// folded.
+template <class R, class Ld, int U, bool AHEAD, class Offset>
+__device__ __forceinline__ void array_stream(const typename Ld::S* __restrict__ base, int64_t lo,
+                                             int64_t hi, int64_t step, const Offset& off,
+                                             typename R::Acc (*acc)[Ld::E]) {
+    const typename Ld::S* __restrict__ bp = base + lo * step;
+    if constexpr (!AHEAD) {
+        for (int64_t p = lo; p < hi; ++p, bp += step) {
+            typename Ld::T v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = Ld::load(bp + off(u));
+#pragma unroll
+            for (int u = 0; u < U; ++u) Ld::template fold<R>(acc[u], v[u]);
+        }
+    } else if (lo < hi) {
+        typename Ld::T v[2][U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[0][u] = Ld::load(bp + off(u));
+        for (int64_t p = lo;; p += 2) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                if (p + s + 1 < hi) {
+                    bp += step;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) v[1 - s][u] = Ld::load(bp + off(u));
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) Ld::template fold<R>(acc[u], v[s][u]);
+                if (p + s + 1 >= hi) return;
+            }
+        }
+    }
+}
+
+// Ragged loads, for blocks whose rows do not keep 16-byte alignment: a period
+// is U layers of RL rows, and lane t has one 16-byte vector of a layer, at the
+// same place in each: a layer's vectors are cut per row of the tile or, where
+// the tile is the whole row, over the layer's RL * m contiguous elements.  The
+// cut's last vector is moved back to end with it and the elements it shares
+// with the one before are not used, so nothing is masked in the loop and
+// nothing outside the row is read.
+template <int E>
+struct RaggedSlot {
+    bool live;
+    int unit;        // row of the layer (0 where a layer is one run)
+    int start;       // first element in that row / run
+    int skip;        // elements at the start that are the vector before's
+    __device__ __forceinline__ RaggedSlot(int t, int64_t ulen, int64_t units) {
+        const int nv = (int)((ulen + E - 1) / E);
+        unit = t / nv;
+        live = unit < units;
+        if (!live) unit = 0;
+        const int v = live ? t % nv : 0;
+        start = v * E < ulen - E ? v * E : (int)ulen - E;
+        skip = v * E - start;
+    }
+};
+
+template <int DT, int OP, int LD, int U>
 __global__ __launch_bounds__(512) void array_reduce_kernel(
     const typename DType<DT>::S* __restrict__ in, typename Red<DT, OP>::Out* __restrict__ x,
     ArrayGeom g, ArrayCross ct) {
@@ -160,7 +235,7 @@ __global__ __launch_bounds__(512) void array_reduce_kernel(
     using R = Red<DT, OP>;
     using Acc = typename R::Acc;
     using S = typename D::S;
-    using Ld = ArrayLoad<DT, VEC>;
+    using Ld = ArrayLoad<DT, LD>;
     constexpr int E = Ld::E;
     constexpr int NW = sizeof(Acc) / 4;
 
@@ -178,16 +253,6 @@ __global__ __launch_bounds__(512) void array_reduce_kernel(
     const bool cross = g.rt > 1;
     const uint32_t epoch = cross ? read_epoch(ct.epoch) : 0u;
 
-    // Lane slot u covers flat offsets o .. o + E - 1 of every period; aoff is
-    // its element offset from the period's first element.  A slot past the
-    // period's span reads the period's first vector instead and its copy is
-    // never used: the loads stay unconditional, one straight run per period.
-    int64_t aoff[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int64_t o = ((int64_t)u * P + tid) * E;
-        aoff[u] = o < span ? (o / wc) * g.m + (o % wc) : 0;
-    }
     Acc acc[U][E];
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -196,51 +261,87 @@ __global__ __launch_bounds__(512) void array_reduce_kernel(
 
     const S* __restrict__ base = in + c0;
     const Range pr = bal_share(g.np, g.rt, r);
-    for (int64_t p = pr.lo; p < pr.hi; ++p) {
-        const S* __restrict__ bp = base + p * g.R * g.m;
-        typename Ld::T v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = Ld::load(bp + aoff[u]);
-#pragma unroll
-        for (int u = 0; u < U; ++u) Ld::template fold<R>(acc[u], v[u]);
-    }
-    if (r == g.rt - 1) {   // rows after the whole periods, element by element
-        const int64_t tl = (g.rows - g.np * g.R) * wc;
-        if (tl > 0) {
-            const S* __restrict__ bp = base + g.np * g.R * g.m;
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int k = 0; k < E; ++k) {
-                    const int64_t o = ((int64_t)u * P + tid) * E + k;
-                    if (o < tl) R::elem(acc[u][k], D::from(bp[(o / wc) * g.m + (o % wc)]));
-                }
-        }
-    }
-
-    // Private copies -> LDS as a [rows][wc] matrix, whose rows are then
-    // folded pairwise.  When every slot of a period is live and one layer of
-    // P * E offsets holds whole rows, a lane's U slots are copies of the same
-    // list items: they fold in registers first and LDS holds P * E / wc rows.
-    const int64_t layer = (int64_t)P * E;
-    const bool fold_u = U > 1 && span == U * layer && layer % wc == 0;
+    const int64_t left = r == g.rt - 1 ? g.rows - g.np * g.R : 0;   // rows after the whole periods
+    const S* __restrict__ lp = base + g.np * g.R * g.m;
     int64_t nrows = g.R;
-    if (fold_u) {
+    if constexpr (LD == kRagged) {
+        const bool run = g.col_tiles == 1;
+        const int64_t ulen = run ? g.RL * wc : wc;
+        const RaggedSlot<E> sl(tid, ulen, run ? 1 : g.RL);
+        const int64_t at = sl.unit * g.m + sl.start, layer = g.RL * g.m;
+        array_stream<R, Ld, U, true>(base, pr.lo, pr.hi, g.R * g.m,
+                                     [&](int u) { return at + u * layer; }, acc);
+        // what is left, a layer at a time: whole vectors, then single elements
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t have = run ? (left - u * g.RL) * g.m - sl.start   // elements from `start` on
+                                     : (u * g.RL + sl.unit < left ? E : 0);
+            if (have >= E) {
+                Ld::template fold<R>(acc[u], Ld::load(lp + at + u * layer));
+            } else {
+#pragma unroll
+                for (int k = 0; k < E - 1; ++k)
+                    if (k < have) R::elem(acc[u][k], D::from(lp[at + u * layer + k]));
+            }
+        }
+        // a lane's slots are copies of the same list items
 #pragma unroll
         for (int u = 1; u < U; ++u)
 #pragma unroll
             for (int k = 0; k < E; ++k) acc[0][k] = R::combine(acc[0][k], acc[u][k]);
 #pragma unroll
-        for (int k = 0; k < E; ++k) lds[(int64_t)tid * E + k] = acc[0][k];
-        nrows = layer / wc;
+        for (int k = 0; k < E; ++k)
+            if (sl.live && k >= sl.skip) lds[sl.unit * wc + sl.start + k] = acc[0][k];
+        nrows = g.RL;
     } else {
+        // Lane slot u covers flat offsets o .. o + E - 1 of every period; aoff is
+        // its element offset from the period's first element.  A slot past the
+        // period's span reads the period's first vector instead and its copy is
+        // never used: the loads stay unconditional, one straight run per period.
+        int64_t aoff[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u) {
+            const int64_t o = ((int64_t)u * P + tid) * E;
+            aoff[u] = o < span ? (o / wc) * g.m + (o % wc) : 0;
+        }
+        // loads ahead where the fold is a 32- or 16-bit float pair's (65536000 / 20
+        // rows of 20 fp32: sum 56 -> 47 us, max 45 -> 47; element loads 61 -> 67)
+        constexpr bool kAhead = LD == kVectors && sizeof(S) <= 4 && sizeof(Acc) == 8;
+        array_stream<R, Ld, U, kAhead>(base, pr.lo, pr.hi, g.R * g.m,
+                                       [&](int u) { return aoff[u]; }, acc);
+        const int64_t tl = left * wc;   // element by element
+        if (tl > 0) {
 #pragma unroll
-            for (int k = 0; k < E; ++k) {
-                const int64_t o = ((int64_t)u * P + tid) * E + k;
-                if (o < span) lds[o] = acc[u][k];
-            }
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int k = 0; k < E; ++k) {
+                    const int64_t o = ((int64_t)u * P + tid) * E + k;
+                    if (o < tl) R::elem(acc[u][k], D::from(lp[(o / wc) * g.m + (o % wc)]));
+                }
+        }
+
+        // Private copies -> LDS as a [rows][wc] matrix, whose rows are then
+        // folded pairwise.  When every slot of a period is live and one layer of
+        // P * E offsets holds whole rows, a lane's U slots are copies of the same
+        // list items: they fold in registers first and LDS holds P * E / wc rows.
+        const int64_t layer = (int64_t)P * E;
+        if (U > 1 && span == U * layer && layer % wc == 0) {
+#pragma unroll
+            for (int u = 1; u < U; ++u)
+#pragma unroll
+                for (int k = 0; k < E; ++k) acc[0][k] = R::combine(acc[0][k], acc[u][k]);
+#pragma unroll
+            for (int k = 0; k < E; ++k) lds[(int64_t)tid * E + k] = acc[0][k];
+            nrows = layer / wc;
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int k = 0; k < E; ++k) {
+                    const int64_t o = ((int64_t)u * P + tid) * E + k;
+                    if (o < span) lds[o] = acc[u][k];
+                }
+        }
     }
     __syncthreads();
     fold_rows<R>(lds, nrows, wc);
@@ -286,27 +387,37 @@ __global__ __launch_bounds__(512) void array_reduce_kernel(
 using ArrayLauncher = void (*)(const void*, void*, const ArrayGeom&, const ArrayCross&, int,
                                size_t, hipStream_t);
 
-template <int DT, int OP, bool VEC, int U>
+template <int DT, int OP, int LD, int U>
 static void launch_array_one(const void* in, void* x, const ArrayGeom& g, const ArrayCross& ct,
                              int threads, size_t lds, hipStream_t stream) {
     const unsigned teams = (unsigned)((int64_t)g.col_tiles * g.rt);
-    hipLaunchKernelGGL((array_reduce_kernel<DT, OP, VEC, U>), dim3(teams), dim3(threads), lds,
+    hipLaunchKernelGGL((array_reduce_kernel<DT, OP, LD, U>), dim3(teams), dim3(threads), lds,
                        stream, static_cast<const typename DType<DT>::S*>(in),
                        static_cast<typename Red<DT, OP>::Out*>(x), g, ct);
 }
 
 // Element loads: unroll 1..8.  16-byte loads: unroll 1..4 (eight vectors of
 // private copies per lane would crowd out the registers).
+template <int DT, int OP, int LD>
+static ArrayLauncher array_pick_u(int u) {
+    switch (u) {
+        case 1: return launch_array_one<DT, OP, LD, 1>;
+        case 2: return launch_array_one<DT, OP, LD, 2>;
+        case 4: return launch_array_one<DT, OP, LD, 4>;
+    }
+    if constexpr (LD == kElements)
+        if (u == 8) return launch_array_one<DT, OP, LD, 8>;
+    return nullptr;
+}
 template <int DT, int OP>
-static ArrayLauncher array_pick_v(bool vec, int u) {
+static ArrayLauncher array_pick_v(int loads, int u) {
     if constexpr (!op_defined(DT, OP)) {
         return nullptr;
     } else {
-        switch (u) {
-            case 1: return vec ? launch_array_one<DT, OP, true, 1> : launch_array_one<DT, OP, false, 1>;
-            case 2: return vec ? launch_array_one<DT, OP, true, 2> : launch_array_one<DT, OP, false, 2>;
-            case 4: return vec ? launch_array_one<DT, OP, true, 4> : launch_array_one<DT, OP, false, 4>;
-            case 8: return vec ? nullptr : launch_array_one<DT, OP, false, 8>;
+        switch (loads) {
+            case kElements: return array_pick_u<DT, OP, kElements>(u);
+            case kVectors: return array_pick_u<DT, OP, kVectors>(u);
+            case kRagged: return array_pick_u<DT, OP, kRagged>(u);
         }
         return nullptr;
     }
@@ -314,25 +425,25 @@ static ArrayLauncher array_pick_v(bool vec, int u) {
 
 // The launcher of one element type (array_<type>.hip instantiates it).
 template <int DT>
-ArrayLauncher array_launcher_impl(int op, bool vec, int u) {
+ArrayLauncher array_launcher_impl(int op, int loads, int u) {
     switch (op) {
-        case OP_SUM: return array_pick_v<DT, OP_SUM>(vec, u);
-        case OP_MAX: return array_pick_v<DT, OP_MAX>(vec, u);
-        case OP_MIN: return array_pick_v<DT, OP_MIN>(vec, u);
-        case OP_PROD: return array_pick_v<DT, OP_PROD>(vec, u);
-        case OP_BAND: return array_pick_v<DT, OP_BAND>(vec, u);
-        case OP_BOR: return array_pick_v<DT, OP_BOR>(vec, u);
-        case OP_BXOR: return array_pick_v<DT, OP_BXOR>(vec, u);
-        case OP_LAND: return array_pick_v<DT, OP_LAND>(vec, u);
-        case OP_LOR: return array_pick_v<DT, OP_LOR>(vec, u);
+        case OP_SUM: return array_pick_v<DT, OP_SUM>(loads, u);
+        case OP_MAX: return array_pick_v<DT, OP_MAX>(loads, u);
+        case OP_MIN: return array_pick_v<DT, OP_MIN>(loads, u);
+        case OP_PROD: return array_pick_v<DT, OP_PROD>(loads, u);
+        case OP_BAND: return array_pick_v<DT, OP_BAND>(loads, u);
+        case OP_BOR: return array_pick_v<DT, OP_BOR>(loads, u);
+        case OP_BXOR: return array_pick_v<DT, OP_BXOR>(loads, u);
+        case OP_LAND: return array_pick_v<DT, OP_LAND>(loads, u);
+        case OP_LOR: return array_pick_v<DT, OP_LOR>(loads, u);
     }
     return nullptr;
 }
 
-ArrayLauncher array_launcher_i32(int op, bool vec, int u);
-ArrayLauncher array_launcher_i64(int op, bool vec, int u);
-ArrayLauncher array_launcher_f32(int op, bool vec, int u);
-ArrayLauncher array_launcher_f64(int op, bool vec, int u);
-ArrayLauncher array_launcher_bf16(int op, bool vec, int u);
+ArrayLauncher array_launcher_i32(int op, int loads, int u);
+ArrayLauncher array_launcher_i64(int op, int loads, int u);
+ArrayLauncher array_launcher_f32(int op, int loads, int u);
+ArrayLauncher array_launcher_f64(int op, int loads, int u);
+ArrayLauncher array_launcher_bf16(int op, int loads, int u);
 
 }  // namespace omprt

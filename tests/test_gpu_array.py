@@ -168,3 +168,23 @@ def test_full_size_sampled_columns(gpu_lib, rows, m, dtype, op):
     cols = sorted(set([0, 1, m // 2, m - 1] + list(np.random.Generator(np.random.PCG64(1))
                                                      .integers(0, m, 12))))
     run_and_check(gpu_lib, host, dtype, op, x_init(dtype, op, m, 3), cols=cols)
+
+
+# rows that do not keep 16-byte alignment: one run of whole rows (m below the tile width),
+# tiles with a last one of 1 .. E elements fewer, last vectors that overlap the one before by
+# every amount, no whole period, rows left over in the first and the second layer
+RAGGED = [(1000, 5), (61, 255), (40, 257), (131, 259), (64, 513), (70, 1023), (3, 1027), (37, 2047),
+          (9001, 33), (4099, 131), (20000, 301), (1, 777), (2, 8191)]
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("rows,m", RAGGED)
+def test_ragged_rows(gpu_lib, dtype, rows, m):
+    flat = synth.host(dtype, rows * m + 3, 6000)
+    for off in (0, 1, 3):
+        dev = to_device(flat, dtype)[off:off + rows * m]
+        host = flat[off:off + rows * m].reshape(rows, m)
+        cols = sorted({0, 1, m // 2, m - 2, m - 1} | set(range(250, min(m, 262)))) if m > 40 else None
+        for op in ("sum", "min"):
+            run_and_check(gpu_lib, host, dtype, op, x_init(dtype, op, m, 8), inp=dev,
+                          cols=None if op == "min" and rows < 100 else cols)
