@@ -103,26 +103,26 @@ __device__ __forceinline__ void fold_rows(typename R::Acc* lds, int64_t nrows, i
 // lds[0 .. wc).  With fewer columns than threads, tpc = P / wc threads share
 // a column: thread (q0, j) folds rows q0, q0 + tpc, ... in order, and the
 // tpc results are folded pairwise in LDS.  Team-wide; ends with a barrier.
-// lds must hold max(P, wc) entries.
+// lds must hold max(P, wc) entries.  One fold_tagged site for every width: it
+// is a third of the kernel's code, and small blocks wait for instructions
+// (with 32-bit slot divisions 62 -> 31 KB for fp32 sums, 278 x 54 int64 9.2 ->
+// 8.6 us).
 template <class R>
 __device__ __forceinline__ void fold_group(const uint64_t* first, int64_t stride, int count,
                                            int64_t wc, uint32_t tag, uint32_t* status,
                                            typename R::Acc* lds) {
     constexpr int NW = sizeof(typename R::Acc) / 4;
     const int P = team_size(), t = threadIdx.x;
-    if (wc * 2 > P) {
-        for (int64_t j = t; j < wc; j += P)
-            lds[j] = fold_tagged<R>(first + j * NW, stride, count, tag, status);
-        __syncthreads();
-        return;
-    }
-    const int tpc = (int)(P / wc) < count ? (int)(P / wc) : count;
-    const int q0 = t / (int)wc, j = t % (int)wc;
+    const bool wide = wc * 2 > P;   // a thread a column, or several columns
+    const int w32 = (int)wc;
+    const int tpc = wide ? 1 : (P / w32 < count ? P / w32 : count);
+    const int q0 = wide ? 0 : t / w32;
     if (q0 < tpc)
-        lds[(int64_t)q0 * wc + j] = fold_tagged<R>(first + q0 * stride + j * NW, stride * tpc,
-                                                   (count - q0 + tpc - 1) / tpc, tag, status);
+        for (int j = wide ? t : t % w32; j < w32; j += wide ? P : w32)
+            lds[q0 * w32 + j] = fold_tagged<R>(first + q0 * stride + (int64_t)j * NW, stride * tpc,
+                                               (count - q0 + tpc - 1) / tpc, tag, status);
     __syncthreads();
-    fold_rows<R>(lds, tpc, wc);
+    if (tpc > 1) fold_rows<R>(lds, tpc, wc);
 }
 
 // How the streaming loop loads: one element; one 16-byte vector at a 16-byte
@@ -298,11 +298,12 @@ __global__ __launch_bounds__(512) void array_reduce_kernel(
         // its element offset from the period's first element.  A slot past the
         // period's span reads the period's first vector instead and its copy is
         // never used: the loads stay unconditional, one straight run per period.
+        const uint32_t w32 = (uint32_t)wc;   // (tiles and periods are a team's slots at most)
         int64_t aoff[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t o = ((int64_t)u * P + tid) * E;
-            aoff[u] = o < span ? (o / wc) * g.m + (o % wc) : 0;
+            const uint32_t o = (uint32_t)(u * P + tid) * E;
+            aoff[u] = o < span ? (int64_t)(o / w32) * g.m + (o % w32) : 0;
         }
         // loads ahead where the fold is a 32- or 16-bit float pair's (65536000 / 20
         // rows of 20 fp32: sum 56 -> 47 us, max 45 -> 47; element loads 61 -> 67)
@@ -315,8 +316,8 @@ __global__ __launch_bounds__(512) void array_reduce_kernel(
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int k = 0; k < E; ++k) {
-                    const int64_t o = ((int64_t)u * P + tid) * E + k;
-                    if (o < tl) R::elem(acc[u][k], D::from(lp[(o / wc) * g.m + (o % wc)]));
+                    const uint32_t o = (uint32_t)(u * P + tid) * E + k;
+                    if (o < tl) R::elem(acc[u][k], D::from(lp[(int64_t)(o / w32) * g.m + (o % w32)]));
                 }
         }
 
@@ -338,7 +339,7 @@ __global__ __launch_bounds__(512) void array_reduce_kernel(
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int k = 0; k < E; ++k) {
-                    const int64_t o = ((int64_t)u * P + tid) * E + k;
+                    const int o = (u * P + tid) * E + k;
                     if (o < span) lds[o] = acc[u][k];
                 }
         }
