@@ -7,6 +7,8 @@ team sweep 1..2048 x 256 in the benchmark's launch configuration; x_orig
 handling, n = 0, determinism; iteration maps of many schedules; the
 cross-team protocol under 10^4 back-to-back launches.
 """
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -388,3 +390,34 @@ def test_exact_thread_map_2pow28(gpu_lib, big_inputs):
         torch.cuda.synchronize()
         ref, sabs = refs[(key, "sum")]
         check_value(x_value(x), ref, sabs, dtype, "sum", "exact 2^28")
+
+
+@pytest.mark.parametrize("where", ["default", "side", "thread", "capture"])
+def test_current_stream_handle(gpu_lib, where):
+    """The stream a call without one runs on is torch's current stream: the default one, one
+    made current, one made current in another thread only, one that is being captured."""
+    om, seen = gpu_lib, []
+
+    def look():
+        seen.append((om._stream(None), torch.cuda.current_stream().cuda_stream or None))
+
+    if where == "default":
+        look()
+    elif where == "side":
+        with torch.cuda.stream(torch.cuda.Stream()):
+            look()
+        look()
+    elif where == "thread":
+        def run():
+            with torch.cuda.stream(torch.cuda.Stream()):
+                look()
+        t = threading.Thread(target=run)
+        with torch.cuda.stream(torch.cuda.Stream()):
+            t.start()
+            t.join()
+            look()
+        assert seen[0][0] != seen[1][0]
+    else:
+        with torch.cuda.graph(torch.cuda.CUDAGraph()):
+            look()
+    assert all(a == b for a, b in seen)
