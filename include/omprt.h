@@ -407,7 +407,7 @@ omprt_status omprt_reduce_loc(const void *d_in, int64_t n, int32_t dtype,
  * bf16 sums), arithmetic and determinism are those of omprt_reduce.
  * rows == 0 or m == 0 leaves d_x unchanged.  d_in and d_x need element
  * alignment; a 16-byte aligned d_in streams in 16-byte vectors when its rows
- * (whole, or cut into column tiles) keep that alignment, otherwise in vectors
+ * (whole, or cut into column tiles of whole lines) keep that alignment, otherwise in vectors
  * at any element's address, or, for fewer than 16 bytes of columns a team
  * could hold or with explicit vec_bytes of the element size or an explicit
  * unroll, one element per load.  The runtime cuts the block into column tiles and row

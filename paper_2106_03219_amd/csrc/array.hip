@@ -143,12 +143,32 @@ static int64_t gcd64(int64_t a, int64_t b) {
     return a;
 }
 
+// Column tiles of rows wider than wmax: as few as hold them, or, for blocks
+// that fill the chip, a power of two of at least sqrt(m / 32) tiles.  With one
+// team a compute unit over them (256 / tiles a tile) one group of teams then
+// folds a tile in one level, and a row team's tiles go to one XCD evenly.  us,
+// fewest tiles -> this: 65536 x 1001 fp32 47.4 -> 43.6, fp64 94.7 -> 87.7;
+// 16000 x 1001 23.2 -> 19.4; 196000 x 333 47.6 -> 44.2; 80000 x 100 20.1 ->
+// 15.3; 256000 x 256 fp64 93.9 -> 85.0; but 1000 x 1001 10.4 -> 11.8, past 32
+// tiles (3276 x 19999) 46.4 -> 48.2, and narrow tiles of 8-byte elements past
+// the last-level cache (1008246 x 65 fp64 92 -> 112; 101265 x 79 28.6 -> 23.1).
+static int64_t tile_count(int64_t rows, int64_t m, int64_t wmax, int esize) {
+    const int64_t least = (m + wmax - 1) / wmax;
+    const int64_t bytes = rows * m * esize;
+    if (m <= 64 || least > 32 || bytes < ((int64_t)16 << 20)) return least;
+    int64_t t = 1;
+    while (t < least || t * t * 32 < m) t *= 2;
+    while (esize == 8 && bytes > ((int64_t)128 << 20) && t > least && m * esize < t * 520) t /= 2;
+    return std::max(t, least);
+}
+
 // Geometry for E elements per load; false if it cannot stream in vectors.
 static bool array_geometry(int64_t rows, int64_t m, int E, int64_t L, ArrayGeom* g) {
     g->rows = rows;
     g->m = m;
     const int64_t wmax = std::min<int64_t>(kTileCols, L) / E * E;
-    if (m <= wmax) {   // whole rows; a period's first element must stay 16-byte aligned
+    const int64_t tiles = tile_count(rows, m, wmax, 16 / E);
+    if (tiles == 1) {   // whole rows; a period's first element must stay 16-byte aligned
         const int64_t step = E / gcd64(m, E);
         g->W = m;
         g->R = (L / m) / step * step;
@@ -156,7 +176,6 @@ static bool array_geometry(int64_t rows, int64_t m, int E, int64_t L, ArrayGeom*
         if (g->R < 1) return false;
     } else {           // balanced column tiles; every row start must be aligned
         if (m % E != 0) return false;
-        const int64_t tiles = (m + wmax - 1) / wmax;
         g->W = ((m + tiles - 1) / tiles + E - 1) / E * E;
         g->R = L / g->W;
         const int64_t used = (m + g->W - 1) / g->W;
@@ -188,7 +207,7 @@ static bool ragged_geometry(int64_t rows, int64_t m, int E, int P, int U, int ab
     g->rows = rows;
     g->m = m;
     const int64_t wmax = std::min<int64_t>(kTileCols, (int64_t)P * E);
-    const int64_t tiles = (m + wmax - 1) / wmax;
+    const int64_t tiles = tile_count(rows, m, wmax, 16 / E);
     g->W = (m + tiles - 1) / tiles;
     if (tiles > INT32_MAX) return false;
     g->col_tiles = (int32_t)((m + g->W - 1) / g->W);
@@ -275,6 +294,10 @@ static omprt_status plan_array(int64_t rows, int64_t m, int dtype, int op, const
         for (int u = u0; u >= 1 && !found; u /= 2) {
             ArrayGeom g{};
             if (array_geometry(rows, m, E, (int64_t)P * E * u, &g)) {
+                // tiles that are not whole lines share them with their neighbours:
+                // ragged loads keep the lines in the caches
+                if (vec && !explicit_u && g.col_tiles > 1 && (g.W * esize % 128 || m * esize % 128))
+                    break;
                 // the group fold also needs one entry per thread
                 const size_t bytes =
                     (size_t)std::max<int64_t>(lds_entries(g, (int64_t)P * E, u), P) * ab;

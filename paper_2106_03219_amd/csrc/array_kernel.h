@@ -138,8 +138,8 @@ struct ArrayLoad {
     static __device__ __forceinline__ T load(const S* p) {
         if constexpr (LD == kRagged) {
             typedef T Any __attribute__((aligned(sizeof(S))));
-            // (nontemporal for 8-byte elements: 65536 x 1001 fp64 104.6 -> 99.3 us;
-            // fp32 52.4 -> 53.1)
+            // (nontemporal for 8-byte elements: 65470 x 1001 int64 93.0 -> 88.1 us;
+            // the others keep the lines that neighbouring lanes and tiles share)
             if constexpr (sizeof(S) == 8)
                 return __builtin_nontemporal_load(reinterpret_cast<const Any*>(p));
             else
@@ -245,8 +245,16 @@ __global__ __launch_bounds__(512) void array_reduce_kernel(
 
     const int tid = threadIdx.x;
     const int P = team_size();
-    const int c = (int)(blockIdx.x % (unsigned)g.col_tiles);
-    const int r = (int)(blockIdx.x / (unsigned)g.col_tiles);
+    // The tiles of eight row teams at a time go to eight XCDs, a row team's tiles
+    // all to the same one (consecutive workgroups go round the XCDs): neighbouring
+    // tiles share the lines at their edges, in one L2.  65536 x 1001 fp32 53 -> 48
+    // us, 196000 x 333 55 -> 48.  Not for teams of a few periods, which wait for
+    // the combination (244 x 4096 10.9 -> 11.4 with it).
+    const unsigned ct_n = (unsigned)g.col_tiles, eights = (unsigned)g.rt / 8 * 8 * ct_n;
+    const unsigned q = blockIdx.x / 8;
+    const bool swz = blockIdx.x < eights && g.np >= 4 * (int64_t)g.rt;
+    const int c = (int)((swz ? q : blockIdx.x) % ct_n);
+    const int r = (int)(swz ? q / ct_n * 8 + blockIdx.x % 8 : blockIdx.x / ct_n);
     const int64_t c0 = (int64_t)c * g.W;
     const int64_t wc = g.m - c0 < g.W ? g.m - c0 : g.W;
     const int64_t span = g.R * wc;

@@ -188,3 +188,18 @@ def test_ragged_rows(gpu_lib, dtype, rows, m):
         for op in ("sum", "min"):
             run_and_check(gpu_lib, host, dtype, op, x_init(dtype, op, m, 8), inp=dev,
                           cols=None if op == "min" and rows < 100 else cols)
+
+
+# blocks that fill the chip: rows of one tile cut into several, tiles of whole lines and not,
+# row teams that are not a multiple of eight (the last ones' tiles are not grouped by XCD)
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("rows,m,config", [(84001, 101, None), (33000, 256, None), (28001, 300, {"teams": 100}),
+                                           (8600, 1001, None), (1800, 4833, {"teams": 400})])
+def test_many_tiles(gpu_lib, dtype, rows, m, config):
+    plan = gpu_lib.reduce_array_plan(rows, m, dtype, "sum", config=config)
+    assert plan[2] > 1
+    host = synth.host(dtype, rows * m, 6100).reshape(rows, m)
+    W = plan[0]
+    cols = sorted({0, 1, W - 1, W, min(2 * W, m) - 1, m - W % 7 - 1, m - 1})
+    for op in ("sum", "max"):
+        run_and_check(gpu_lib, host, dtype, op, x_init(dtype, op, m, 12), config=config, cols=cols)
