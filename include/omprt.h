@@ -450,12 +450,13 @@ omprt_status omprt_reduce_array_plan(int64_t rows, int64_t m, int32_t dtype,
 /*
  * count independent reductions in ONE persistent kernel launch.  h_segs is
  * a host array; each segment follows omprt_reduce's semantics.  The plan
- * (descriptor and tile tables) and a captured HIP graph of the launch are
- * cached per (stream, segment list, configuration): a repeat call with the
- * same list only replays the graph.  Segments may not alias each other's
+ * (descriptor and tile tables) is cached per (stream, segment list,
+ * configuration): a repeat call with the same list is that one launch, which a
+ * caller may also capture into a graph.  Segments may not alias each other's
  * outputs.  cfg's threads_per_team / unroll / vec_bytes select the tile
- * kernel; num_teams the persistent grid size (0 = one full wave of the
- * device).
+ * kernel; num_teams the most workgroups of the persistent grid (0 = one full
+ * wave of the device); tile_kib 0: 1024, or less where that would leave
+ * compute units idle.  Segments of a few KB are reduced by one wave each.
  * Defining passages: each segment is one reduction region with omprt_reduce's
  * semantics; the tiles of a segment play its teams: each reduces its part
  * through the team-shared tree and the last tile, elected by the wrap-around

@@ -251,7 +251,7 @@ def make_segments(items):
 
 
 def reduce_batched(segments, config=None, stream=None):
-    """All segments in one persistent, graph-replayed launch (see make_segments)."""
+    """All segments in one persistent launch of a cached plan (see make_segments)."""
     arr = segments if isinstance(segments, ctypes.Array) else make_segments(segments)
     check(load().omprt_reduce_batched(arr, len(arr), _cfg(config), _stream(stream)),
           "reduce_batched")

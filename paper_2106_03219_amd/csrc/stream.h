@@ -54,18 +54,18 @@ __device__ __forceinline__ void accumulate_vec(typename R::Acc* acc,
 }
 
 // Streaming with any accumulation policy R (elem, kNA, Acc); acc has
-// R::kNA entries; every thread of the team calls this with the same [a, b).
+// R::kNA entries; P threads (at least a wave), numbered tid, call this with
+// the same [a, b).
 template <class R, int DT, int VB, int U>
-__device__ __forceinline__ void stream_range_with(const typename DType<DT>::S* __restrict__ in,
-                                                  int64_t a, int64_t b, typename R::Acc* acc) {
+__device__ __forceinline__ void stream_range_by(const typename DType<DT>::S* __restrict__ in,
+                                                int64_t a, int64_t b, typename R::Acc* acc,
+                                                int tid, int P) {
     using D = DType<DT>;
     using S = typename D::S;
     using L = VecLoad<DT, VB>;
     using Vec = typename L::T;
     constexpr int PER = L::PER;   // elements per vector
     if (a >= b) return;
-    const int tid = threadIdx.x;
-    const int P = team_size();
     const uintptr_t mis = reinterpret_cast<uintptr_t>(in + a) & (VB - 1);
     int64_t head = (int64_t)(((VB - mis) & (VB - 1)) / sizeof(S));
     if (head > b - a) head = b - a;
@@ -87,6 +87,13 @@ __device__ __forceinline__ void stream_range_with(const typename DType<DT>::S* _
     }
     const int64_t t0 = p0 + nv * PER;
     if (tid < b - t0) R::elem(acc[0], D::from(in[t0 + tid]));
+}
+
+// By every thread of the team.
+template <class R, int DT, int VB, int U>
+__device__ __forceinline__ void stream_range_with(const typename DType<DT>::S* __restrict__ in,
+                                                  int64_t a, int64_t b, typename R::Acc* acc) {
+    stream_range_by<R, DT, VB, U>(in, a, b, acc, threadIdx.x, team_size());
 }
 
 // The plain reduction's streaming: policy Red<DT, OP>.

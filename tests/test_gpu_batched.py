@@ -132,3 +132,42 @@ def test_batched_full_4096_every_segment(gpu_lib):
     om.reduce_each(segs)
     check_every_segment(ins, xs, info, what="plain")
     assert om.workspace_status() == 0
+
+
+@pytest.mark.parametrize("config", [None, {"teams": 2}, {"threads": 64}, {"threads": 192, "teams": 3},
+                                    {"flags": 2, "teams": 5}, {"vec": 8, "unroll": 1}])
+def test_short_segments(gpu_lib, config):
+    """Segments around the sizes up to which one wave takes one (8 KB; 32 KB with at least
+    eight segments a workgroup, as with two teams), off 16-byte alignment, in bundles with a
+    remainder, between longer ones and an empty one: called twice, then captured by the caller
+    and replayed, with the library's own calls in between."""
+    om = gpu_lib
+    ins, xs, meta = [], [], []
+    for dt, eb in ((synth.I32, 4), (synth.I64, 8), (synth.F32, 4), (synth.F64, 8), (synth.BF16, 2)):
+        for j, b in enumerate((eb, 5 * eb, 64 * eb, 8192 - eb, 8192, 8192 + eb, 32768, 32768 + eb, 150000 * eb)):
+            op = ("sum", "max", "min")[j % 3]
+            host = synth.host(dt, b // eb + j % 4, 30_000 + j)
+            ins.append(to_device(host, dt)[j % 4:])
+            x0 = 3 if dt in (synth.I32, synth.I64) else 0.5
+            xs.append(x_tensor(dt, op, x0))
+            meta.append((host[j % 4:], dt, op, x0))
+    empty = torch.full((1,), 5, dtype=torch.int32, device="cuda")
+    items = [(i, m[2], x) for i, x, m in zip(ins, xs, meta)]
+    segs = om.make_segments(items[:7] + [(ins[0], "sum", empty, 0)] + items[7:])
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        for _ in range(2):
+            _reset(xs, meta)
+            om.reduce_batched(segs, config=config)
+            _check_all(xs, meta)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            om.reduce_batched(segs, config=config)
+        for _ in range(3):
+            _reset(xs, meta)
+            g.replay()
+            _check_all(xs, meta)
+            _reset(xs, meta)
+            om.reduce_batched(segs, config=config)
+            _check_all(xs, meta)
+        assert empty.item() == 5 and om.workspace_status() == 0
