@@ -401,20 +401,26 @@ extern "C" omprt_status omprt_reduce_batched(const omprt_segment* h_segs, int32_
     if (count < 0) return fail(OMPRT_ERR_INVALID, "count < 0");
     if (count > 0 && !h_segs) return fail(OMPRT_ERR_INVALID, "segments pointer is NULL");
     if (count == 0) return OMPRT_OK;
-    int dev = 0, cus = 0;
-    OMPRT_HIP(hipGetDevice(&dev));
-    OMPRT_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    auto check = [&]() -> omprt_status {
+        if (omprt_status st = check_segments(h_segs, count)) return st;
+        LaunchCfg dummy;   // field validation only
+        return resolve_config(1, OMPRT_F32, OMPRT_SUM, 0, -1, cfg, &dummy, nullptr);
+    };
+    int dev = 0;
+    const hipError_t de = hipGetDevice(&dev);
+    if (de != hipSuccess) {   // argument errors come first
+        if (omprt_status st = check()) return st;
+        OMPRT_HIP(de);
+    }
+    const int cus = device_cus();
     omprt_config c;
     batched_defaults(cfg, &c, cus);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     std::lock_guard<std::mutex> lk(g_bmu);
     std::unique_ptr<Plan>& slot = g_plans[{dev, stream}];
     if (!slot || !same_plan(*slot, h_segs, count, c)) {
-        // (a list and configuration equal to the plan's passed these checks)
-        if (omprt_status st = check_segments(h_segs, count)) return st;
-        LaunchCfg dummy;
-        if (omprt_status st = resolve_config(1, OMPRT_F32, OMPRT_SUM, 0, -1, cfg, &dummy, nullptr))
-            return st;   // field validation only
+        // (a list and configuration equal to the plan's passed)
+        if (omprt_status st = check()) return st;
         hipStreamCaptureStatus cst = hipStreamCaptureStatusNone;
         OMPRT_HIP(hipStreamIsCapturing(stream, &cst));
         if (cst != hipStreamCaptureStatusNone)
