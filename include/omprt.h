@@ -713,7 +713,7 @@ omprt_status omprt_tune_set(int32_t dtype, int32_t op, int32_t body,
  * harnesses that forbid hipMalloc): the same arguments, kernels and
  * results as omprt_reduce, but the cross-team state (counter, epoch,
  * status, one 32-byte slot per team) lives in a fixed array of
- * 256 + 4096 * 32 bytes (128 KiB + 256 B) of static device memory that
+ * 4352 + 4096 * 32 bytes (132 KiB + 256 B) of static device memory that
  * each device holds until the process ends.  The call allocates nothing
  * (no hipMalloc, no hipFree, no library allocation); the array's device
  * address is looked up on the first call on each device.  Calls on one

@@ -704,7 +704,7 @@ __device__ __forceinline__ void axpy_finish_sum(ff_t acc, float* __restrict__ su
     }
     const uint32_t tag = launch_tag(epoch);
     if (!publish_and_elect(acc, ct.slots + (size_t)blockIdx.x * kSlotWords, ct.counter,
-                           (uint32_t)(T - 1), tag, s_last))
+                           (uint32_t)(T - 1), tag, s_last, ct.groups))
         return;
     const ff_t cmb = combine_slots<R>(ct.slots, T, tag, ct.status, lds_slots);
     if (t == 0) {

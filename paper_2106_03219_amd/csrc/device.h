@@ -154,6 +154,7 @@ struct CrossTeam {
     uint32_t* counter;   // election counter, 0 between launches
     uint32_t* epoch;     // launch epoch
     uint32_t* status;    // set to 1 if a poll timed out
+    int32_t groups;      // the teams elect in kElectGroups groups (launch.h)
 };
 constexpr int kSlotWords = 4;                 // 32-bit payload words per slot
 // Slot words a participant's partial of type Acc takes (whole slots: a
@@ -227,17 +228,30 @@ __device__ __forceinline__ Acc collect_tagged(const uint64_t* slot, uint32_t tag
     return a;
 }
 
+__device__ __forceinline__ bool last_of(uint32_t* counter, uint32_t e) {
+    return __builtin_amdgcn_atomic_inc32(counter, e, __ATOMIC_RELAXED, "agent") == e;
+}
+
 // Thread 0 publishes the team's partial and takes part in the election.
-// Returns the same bool in every thread of the team: true for the last.
+// Returns the same bool in every thread of the team: true for the last.  In
+// groups: the last of the workgroups k, k + kElectGroups, ... goes on to the
+// groups' own election.
 template <class Acc>
 __device__ __forceinline__ bool publish_and_elect(const Acc& partial, uint64_t* slot,
                                                   uint32_t* counter, uint32_t e, uint32_t tag,
-                                                  int* s_flag) {
+                                                  int* s_flag, int groups = 0) {
     if (threadIdx.x == 0) {
         publish_tagged(partial, slot, tag);
         __atomic_signal_fence(__ATOMIC_SEQ_CST);   // keep the stores before the increment
-        const uint32_t old = __builtin_amdgcn_atomic_inc32(counter, e, __ATOMIC_RELAXED, "agent");
-        *s_flag = (old == e) ? 1 : 0;
+        bool last;
+        if (groups) {
+            const uint32_t g = blockIdx.x % kElectGroups;
+            last = last_of(counter + (kElectGroupBytes / 4) * (g + 1), (e - g) / kElectGroups) &&
+                   last_of(counter, kElectGroups - 1);
+        } else {
+            last = last_of(counter, e);
+        }
+        *s_flag = last ? 1 : 0;
     }
     __syncthreads();
     return *s_flag != 0;

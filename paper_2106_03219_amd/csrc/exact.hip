@@ -91,7 +91,7 @@ __global__ __launch_bounds__(1024) void reduce_exact_kernel(
     }
     const uint32_t tag = launch_tag(epoch);
     if (!publish_and_elect(t, ct.slots + (size_t)blockIdx.x * kSlotWords, ct.counter,
-                           (uint32_t)(T - 1), tag, &s_last))
+                           (uint32_t)(T - 1), tag, &s_last, ct.groups))
         return;
     const Acc c = combine_slots<R>(ct.slots, T, tag, ct.status, lds_slots);
     if (tid == 0) {
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(1024) void reduce_exact_kernel(
 template <int DT, int OP>
 static hipError_t launch_exact_one(const void* in, int64_t n, void* x, int teams, int threads,
                                    const CrossTeamArgs& a, hipStream_t stream) {
-    const CrossTeam ct{static_cast<uint64_t*>(a.slots), a.counter, a.epoch, a.status};
+    const CrossTeam ct{static_cast<uint64_t*>(a.slots), a.counter, a.epoch, a.status, a.groups};
     const auto* src = static_cast<const typename DType<DT>::S*>(in);
     auto* dst = static_cast<typename Red<DT, OP>::Out*>(x);
     if (threads % kWave != 0) {

@@ -394,7 +394,7 @@ extern "C" omprt_status omprt_generic_power(const float* d_diag, float* d_v, int
         Workspace* ws = nullptr;
         if (omprt_status st = workspace_get(stream, kGenericSlots * teams, &ws)) return st;
         const CrossTeamArgs ca = ws->cross();
-        ct = CrossTeam{static_cast<uint64_t*>(ca.slots), ca.counter, ca.epoch, ca.status};
+        ct = CrossTeam{static_cast<uint64_t*>(ca.slots), ca.counter, ca.epoch, ca.status, ca.groups};
         e = hipLaunchCooperativeKernel(var->many, dim3(teams), dim3(threads), args, 0, stream);
     }
     if (e != hipSuccess) return fail(OMPRT_ERR_DEVICE, "generic launch: %s", hipGetErrorString(e));

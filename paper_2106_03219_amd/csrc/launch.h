@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "sched.h"
 
 namespace omprt {
 
@@ -10,13 +11,28 @@ namespace omprt {
 // 16 bytes, 32 bits per word).
 constexpr int kSlotBytes = 32;
 
+// Header in front of the slots: 256 bytes with the election counter, the epoch
+// and the status word, then the counters of the election's groups.
+constexpr int kHeaderBytes = 256 + kElectGroups * kElectGroupBytes;
+
 // Device words a launch of the plain kernels uses for the cross-team step.
 struct CrossTeamArgs {
     void* slots;          // teams * kSlotBytes, zero-filled at allocation
     uint32_t* counter;    // election counter, 0 between launches
     uint32_t* epoch;      // launch epoch
     uint32_t* status;     // poll-timeout flag
+    int32_t groups = 0;   // election in kElectGroups groups (elect_groups)
 };
+
+// Whether a launch's election goes in groups.  One counter serves T teams 13 ns
+// apart, which is what a short launch's teams wait for as they all end at once
+// (us, one counter -> groups: fp32 max 2^22 in 256 teams 7.6 -> 5.7, 2^18 in
+// 2048 29.0 -> 8.2; 64 teams 5.6 -> 5.9); a long one's end spread out, and there
+// a second increment is a round trip more (2^28 in 256 teams 149.0 -> 149.4),
+// short of a thousand teams (2048: 169.9 -> 162.2).
+inline int32_t elect_groups(int teams, int64_t bytes) {
+    return teams >= 1024 || (teams >= 128 && bytes <= ((int64_t)128 << 20));
+}
 
 // True if (dtype, op, vec_bytes, unroll) has a compiled reduce kernel.
 bool reduce_variant_exists(int dtype, int op, int vec_bytes, int unroll);

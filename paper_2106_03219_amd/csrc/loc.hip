@@ -143,7 +143,7 @@ __global__ __launch_bounds__(1024) void reduce_loc_kernel(const typename DType<D
     if (T > 1) {
         const uint32_t tag = launch_tag(epoch);
         if (!publish_and_elect(t, ct.slots + (size_t)blockIdx.x * kSlotWords, ct.counter,
-                               (uint32_t)(T - 1), tag, &s_last))
+                               (uint32_t)(T - 1), tag, &s_last, ct.groups))
             return;
         c = combine_slots<R>(ct.slots, T, tag, ct.status, lds_slots);
     }
@@ -229,8 +229,8 @@ extern "C" omprt_status omprt_reduce_loc(const void* d_in, int64_t n, int32_t dt
     if (omprt_status st = workspace_get(stream, lc.teams, &ws)) return st;
     const LocLauncher f = loc_launcher(dtype, op, lc.unroll);
     if (!f) return fail(OMPRT_ERR_INVALID, "unroll %d", lc.unroll);
-    const CrossTeamArgs ca = ws->cross();
-    const CrossTeam ct{static_cast<uint64_t*>(ca.slots), ca.counter, ca.epoch, ca.status};
+    const CrossTeamArgs ca = ws->cross(lc.teams, n * dtype_bytes(dtype));
+    const CrossTeam ct{static_cast<uint64_t*>(ca.slots), ca.counter, ca.epoch, ca.status, ca.groups};
     f(d_in, n, d_val, d_idx, lc.teams, lc.threads, ct, stream);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(OMPRT_ERR_DEVICE, "loc launch: %s", hipGetErrorString(e));

@@ -126,7 +126,7 @@ hipError_t launch_axpy_sum(float a, const float* x, float* y, float* sum, int64_
                            int threads, int64_t dist_chunk, int64_t chunk, const CrossTeamArgs& ct,
                            hipStream_t stream) {
     const int block = (threads + kWave - 1) / kWave * kWave;
-    const CrossTeam dct{static_cast<uint64_t*>(ct.slots), ct.counter, ct.epoch, ct.status};
+    const CrossTeam dct{static_cast<uint64_t*>(ct.slots), ct.counter, ct.epoch, ct.status, ct.groups};
     const bool co_aligned =
         ((reinterpret_cast<uintptr_t>(x) ^ reinterpret_cast<uintptr_t>(y)) & 15) == 0;
     const bool waves = threads % kWave == 0 && threads <= 512;

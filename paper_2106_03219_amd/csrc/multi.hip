@@ -60,7 +60,7 @@ __global__ __launch_bounds__(1024) void reduce_multi_kernel(
     if (T > 1) {
         const uint32_t tag = launch_tag(epoch);
         if (!publish_and_elect(t, ct.slots + (size_t)blockIdx.x * slot_words<Acc>(), ct.counter,
-                               (uint32_t)(T - 1), tag, &s_last))
+                               (uint32_t)(T - 1), tag, &s_last, ct.groups))
             return;
         c = combine_slots<R>(ct.slots, T, tag, ct.status, lds_slots);
     }
@@ -167,8 +167,8 @@ extern "C" omprt_status omprt_reduce_multi(const void* d_in, int64_t n, int32_t 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     Workspace* ws = nullptr;
     if (omprt_status st = workspace_get(stream, lc.teams * slots, &ws)) return st;
-    const CrossTeamArgs ca = ws->cross();
-    const CrossTeam ct{static_cast<uint64_t*>(ca.slots), ca.counter, ca.epoch, ca.status};
+    const CrossTeamArgs ca = ws->cross(lc.teams, n * dtype_bytes(dtype));
+    const CrossTeam ct{static_cast<uint64_t*>(ca.slots), ca.counter, ca.epoch, ca.status, ca.groups};
     f(d_in, n, x, lc.teams, lc.threads, ct, stream);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(OMPRT_ERR_DEVICE, "multi launch: %s", hipGetErrorString(e));

@@ -2,11 +2,11 @@
 // exact-map variant) with its cross-team state in a fixed device array
 // instead of a per-stream workspace, for callers that cannot allocate.
 //
-// The array, `scratch`, holds the same layout as a workspace: a 256-byte
-// header (election counter, launch epoch, status bits) and one 32-byte
+// The array, `scratch`, holds the same layout as a workspace: a header
+// (election counters, launch epoch, status bits) and one 32-byte
 // tagged slot per team, for up to kNoAllocTeams teams.  It starts zeroed
 // (static storage) and keeps the workspace invariants from call to call:
-// the election leaves the counter at 0, the finisher advances the epoch,
+// the election leaves its counters at 0, the finisher advances the epoch,
 // and slot tags are odd, so a zeroed slot never matches.  Every call on a
 // device uses that device's one copy, so calls on one device must not
 // overlap (two streams at once would mix their counters and slots).
@@ -22,7 +22,7 @@
 namespace omprt {
 
 constexpr int kNoAllocTeams = 4096;
-constexpr size_t kNoAllocBytes = 256 + (size_t)kNoAllocTeams * kSlotBytes;   // 128 KiB + 256 B
+constexpr size_t kNoAllocBytes = kHeaderBytes + (size_t)kNoAllocTeams * kSlotBytes;   // 132 KiB + 256 B
 
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes] = {};
 
@@ -79,7 +79,8 @@ extern "C" omprt_status omprt_reduce_noalloc(const void* d_in, int64_t n, int32_
     void* base = nullptr;
     if (omprt_status st = noalloc_scratch(dev, &base)) return st;
     uint32_t* words = static_cast<uint32_t*>(base);
-    const CrossTeamArgs ct{static_cast<char*>(base) + 256, words, words + 32, words + 48};
+    const CrossTeamArgs ct{static_cast<char*>(base) + kHeaderBytes, words, words + 32, words + 48,
+                           elect_groups(lc.teams, n * dtype_bytes(dtype))};
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const hipError_t e =
         exact ? launch_reduce_exact(dtype, op, d_in, n, d_x, lc.teams, lc.threads, ct, stream)

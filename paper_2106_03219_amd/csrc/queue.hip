@@ -427,8 +427,8 @@ extern "C" omprt_status omprt_axpy_sum_queue(float a, const float* d_x, float* d
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     Workspace* ws = nullptr;
     if (omprt_status st = workspace_get(stream, teams, &ws)) return st;
-    const CrossTeamArgs ca = ws->cross();
-    const CrossTeam ct{static_cast<uint64_t*>(ca.slots), ca.counter, ca.epoch, ca.status};
+    const CrossTeamArgs ca = ws->cross(teams, s->n * 12);
+    const CrossTeam ct{static_cast<uint64_t*>(ca.slots), ca.counter, ca.epoch, ca.status, ca.groups};
     // one-iteration dynamic chunks: eight per request, so that eight loads of
     // each stream are in flight per lane and a wave's LDS atomic covers 512
     // iterations (2^26 fp32, default launch: 4.45 TB/s with four, 4.98 with

@@ -46,7 +46,7 @@ __global__ __launch_bounds__(1024) void reduce_kernel(
     }
     const uint32_t tag = launch_tag(epoch);
     if (!publish_and_elect(t, ct.slots + (size_t)blockIdx.x * kSlotWords, ct.counter,
-                           (uint32_t)(T - 1), tag, &s_last))
+                           (uint32_t)(T - 1), tag, &s_last, ct.groups))
         return;
     if (tid == 0) x0 = x[0];
     const Acc c = combine_slots<R>(ct.slots, T, tag, ct.status, lds_slots);
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(1024) void reduce_kernel(
 }
 
 static CrossTeam to_device_ct(const CrossTeamArgs& a) {
-    return CrossTeam{static_cast<uint64_t*>(a.slots), a.counter, a.epoch, a.status};
+    return CrossTeam{static_cast<uint64_t*>(a.slots), a.counter, a.epoch, a.status, a.groups};
 }
 
 // ---------------------------------------------------------------- dispatch
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(1024) void empty_region_kernel(int64_t n, int P, in
     if (T > 1) {
         const uint32_t tag = launch_tag(epoch);
         if (!publish_and_elect(total, ct.slots + (size_t)blockIdx.x * kSlotWords, ct.counter,
-                               (uint32_t)(T - 1), tag, &s_last))
+                               (uint32_t)(T - 1), tag, &s_last, ct.groups))
             return;
         total = combine_slots<R>(ct.slots, T, tag, ct.status, lds_slots);
     }

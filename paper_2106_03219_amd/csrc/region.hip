@@ -284,8 +284,8 @@ extern "C" omprt_status omprt_region_axpy_sum(float a, const float* d_x, float* 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     Workspace* ws = nullptr;
     if (omprt_status st = workspace_get(stream, teams, &ws)) return st;
-    const CrossTeamArgs ca = ws->cross();
-    const CrossTeam ct{static_cast<uint64_t*>(ca.slots), ca.counter, ca.epoch, ca.status};
+    const CrossTeamArgs ca = ws->cross(teams, s->n * 16);
+    const CrossTeam ct{static_cast<uint64_t*>(ca.slots), ca.counter, ca.epoch, ca.status, ca.groups};
     const hipError_t e =
         nowait ? launch_region<true>(a, d_x, d_y, d_sum, s->n, teams, threads, s->dist_chunk,
                                      s->chunk, chunk2, ct, stream)

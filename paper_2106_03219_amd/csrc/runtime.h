@@ -36,8 +36,11 @@ struct Workspace {
     uint32_t* counter() const { return static_cast<uint32_t*>(base); }
     uint32_t* epoch() const { return static_cast<uint32_t*>(base) + 32; }
     uint32_t* status() const { return static_cast<uint32_t*>(base) + 48; }
-    void* slots() const { return static_cast<char*>(base) + 256; }
-    CrossTeamArgs cross() const { return CrossTeamArgs{slots(), counter(), epoch(), status()}; }
+    void* slots() const { return static_cast<char*>(base) + kHeaderBytes; }
+    // for a launch of `teams` teams over `bytes` of input
+    CrossTeamArgs cross(int teams = 0, int64_t bytes = 0) const {
+        return CrossTeamArgs{slots(), counter(), epoch(), status(), elect_groups(teams, bytes)};
+    }
 };
 
 // Device memory a caller's captured graph may still name is never freed while

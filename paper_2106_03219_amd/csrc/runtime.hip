@@ -105,14 +105,14 @@ omprt_status workspace_get(hipStream_t stream, int32_t teams, Workspace** out) {
                         ws.capacity, teams);
         const int32_t cap = std::max<int32_t>(teams, 4096);
         void* p = nullptr;
-        if (hipMalloc(&p, 256 + (size_t)cap * kSlotBytes) != hipSuccess)
+        if (hipMalloc(&p, kHeaderBytes + (size_t)cap * kSlotBytes) != hipSuccess)
             return fail(OMPRT_ERR_NOMEM, "workspace allocation of %d slots failed", cap);
         // earlier launches, and graphs a caller captured, may still use the old one
         retire_device_memory(dev, ws.base);
         ws.base = p;
         ws.capacity = cap;
         // header and slots, once: tags are odd, so zeroed slots never match
-        OMPRT_HIP(hipMemsetAsync(p, 0, 256 + (size_t)cap * kSlotBytes, stream));
+        OMPRT_HIP(hipMemsetAsync(p, 0, kHeaderBytes + (size_t)cap * kSlotBytes, stream));
     }
     t_ws = WsMemo{dev, stream, &ws, g_ws_generation.load(std::memory_order_acquire)};
     *out = &ws;
@@ -433,9 +433,10 @@ extern "C" omprt_status omprt_reduce(const void* d_in, int64_t n, int32_t dtype,
     if (exact && op > OMPRT_MIN)
         return fail(OMPRT_ERR_UNSUPPORTED, "EXACT_THREAD_MAP takes sum, max and min");
     const hipError_t e =
-        exact ? launch_reduce_exact(dtype, op, d_in, n, d_x, lc.teams, lc.threads, ws->cross(), stream)
+        exact ? launch_reduce_exact(dtype, op, d_in, n, d_x, lc.teams, lc.threads,
+                                    ws->cross(lc.teams, n * dtype_bytes(dtype)), stream)
               : launch_reduce(dtype, op, lc.vec, lc.unroll, d_in, n, d_x, lc.teams, lc.threads,
-                              ws->cross(), stream);
+                              ws->cross(lc.teams, n * dtype_bytes(dtype)), stream);
     if (e != hipSuccess) return fail(OMPRT_ERR_DEVICE, "reduce launch: %s", hipGetErrorString(e));
     return OMPRT_OK;
 }
@@ -481,7 +482,7 @@ extern "C" omprt_status omprt_axpy_sum(float a, const float* d_x, float* d_y, fl
     Workspace* ws = nullptr;
     if (omprt_status st = workspace_get(stream, teams, &ws)) return st;
     const hipError_t e = launch_axpy_sum(a, d_x, d_y, d_sum, s->n, teams, threads, s->dist_chunk,
-                                         s->chunk, ws->cross(), stream);
+                                         s->chunk, ws->cross(teams, s->n * 12), stream);
     if (e != hipSuccess) return fail(OMPRT_ERR_DEVICE, "axpy launch: %s", hipGetErrorString(e));
     return OMPRT_OK;
 }
@@ -497,7 +498,8 @@ extern "C" omprt_status omprt_empty_region(const omprt_sched* s, int64_t* d_iter
     Workspace* ws = nullptr;
     if (omprt_status st = workspace_get(stream, s->num_teams, &ws)) return st;
     const hipError_t e = launch_empty_region(s->n, s->num_teams, s->threads_per_team,
-                                             s->dist_chunk, s->chunk, d_iters, ws->cross(), stream);
+                                             s->dist_chunk, s->chunk, d_iters,
+                                             ws->cross(s->num_teams, 0), stream);
     if (e != hipSuccess) return fail(OMPRT_ERR_DEVICE, "empty launch: %s", hipGetErrorString(e));
     return OMPRT_OK;
 }
@@ -562,6 +564,7 @@ extern "C" omprt_status omprt_workspace_reset(void* hip_stream) {
     if (it == g_ws.end() || !it->second.base) return OMPRT_OK;
     // counter and flag back to 0; the epoch moves on (stale slot tags stay stale)
     OMPRT_HIP(hipMemsetAsync(it->second.base, 0, 128, stream));
+    OMPRT_HIP(hipMemsetAsync(static_cast<char*>(it->second.base) + 256, 0, kHeaderBytes - 256, stream));
     OMPRT_HIP(hipMemsetAsync(it->second.status(), 0, 4, stream));
     return OMPRT_OK;
 }

@@ -16,6 +16,11 @@
 
 namespace omprt {
 
+// Groups of a launch-wide election, and the distance of their counters (one
+// address takes an increment every 13 ns).
+constexpr int kElectGroups = 16;
+constexpr int kElectGroupBytes = 256;
+
 struct Range {
     int64_t lo, hi;
 };

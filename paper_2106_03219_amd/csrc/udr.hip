@@ -158,7 +158,7 @@ extern "C" __global__ __launch_bounds__(1024) void omprt_udr_kernel(
     if (T > 1) {
         const uint32_t tag = launch_tag(epoch);
         if (!publish_and_elect(a, ct.slots + (size_t)blockIdx.x * slot_words<R::Acc>(), ct.counter,
-                               (uint32_t)(T - 1), tag, &s_last))
+                               (uint32_t)(T - 1), tag, &s_last, ct.groups))
             return;
         c = combine_slots<R>(ct.slots, T, tag, ct.status, lds);
     }
@@ -370,8 +370,8 @@ extern "C" omprt_status omprt_reduce_udr(int32_t handle, const void* d_in, int64
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     Workspace* ws = nullptr;
     if (omprt_status st = workspace_get(stream, lc.teams * slots, &ws)) return st;
-    const CrossTeamArgs ca = ws->cross();
-    CrossTeam ct{static_cast<uint64_t*>(ca.slots), ca.counter, ca.epoch, ca.status};
+    const CrossTeamArgs ca = ws->cross(lc.teams, n * dtype_bytes(dtype));
+    CrossTeam ct{static_cast<uint64_t*>(ca.slots), ca.counter, ca.epoch, ca.status, ca.groups};
     void* args[] = {&d_in, &n, &d_x, &ct};
     OMPRT_HIP(hipModuleLaunchKernel(f, lc.teams, 1, 1, lc.threads, 1, 1, 0, stream, args, nullptr));
     return OMPRT_OK;

@@ -421,3 +421,30 @@ def test_current_stream_handle(gpu_lib, where):
         with torch.cuda.graph(torch.cuda.CUDAGraph()):
             look()
     assert all(a == b for a, b in seen)
+
+
+@pytest.mark.parametrize("teams", [127, 128, 129, 143, 144, 255, 1023, 1024, 4096])
+def test_grouped_election(gpu_lib, teams):
+    """Elections in groups (from 128 teams in short launches, from 1024 in all) and on one
+    counter, in turn on one workspace, with group sizes that differ by one: exact sums of
+    int64, none lost or counted twice, and counters back at 0 for the next launch."""
+    om = gpu_lib
+    short = synth.host(synth.I64, 70001, 41)
+    long_n = (128 << 20) // 8 + 1
+    dev = to_device(short, synth.I64)
+    rest = torch.ones(long_n, dtype=torch.int64, device="cuda")
+    x = torch.zeros(1, dtype=torch.int64, device="cuda")
+    y = torch.zeros(1, dtype=torch.int64, device="cuda")
+    cfg = {"teams": teams, "threads": 64}
+    reps = 20
+    for i in range(reps):
+        om.reduce(dev, "sum", x, config=cfg)
+        if i % 4 == 0:
+            om.reduce(rest, "sum", x, config=cfg)
+        om.reduce_noalloc(dev, "sum", y, config=cfg)
+    torch.cuda.synchronize()
+    total = int(short.astype(object).sum()) * reps
+    wrap = lambda v: (v + 2**63) % 2**64 - 2**63
+    assert x.item() == wrap(total + (reps + 3) // 4 * long_n)
+    assert y.item() == wrap(total)
+    assert om.workspace_status() == 0
