@@ -57,6 +57,7 @@ struct BatchState {
     uint32_t* epoch;
     uint32_t* status;
     int32_t ntiles;
+    int32_t done_groups;   // `done` counts in kElectGroups groups
 };
 
 // Reduce one tile, and combine its segment's if it is the last of them.
@@ -169,10 +170,15 @@ __global__ __launch_bounds__(1024) void batched_kernel(const SegDesc* __restrict
         }
     }
     // the last workgroup to end advances the epoch (each read it at its start)
-    if (threadIdx.x == 0 &&
-        __builtin_amdgcn_atomic_inc32(bs.done, gridDim.x - 1, __ATOMIC_RELAXED, "agent") ==
-            gridDim.x - 1)
-        advance_epoch(bs.epoch, epoch);
+    if (threadIdx.x == 0) {
+        const uint32_t e = gridDim.x - 1, g = blockIdx.x % kElectGroups;
+        const bool last =
+            bs.done_groups
+                ? last_of(bs.done + (kElectGroupBytes / 4) * (g + 1), (e - g) / kElectGroups) &&
+                      last_of(bs.done, kElectGroups - 1)
+                : last_of(bs.done, e);
+        if (last) advance_epoch(bs.epoch, epoch);
+    }
 }
 
 using BatchedKernel = void (*)(const SegDesc*, const TileDesc*, const int32_t*, BatchState, int32_t);
@@ -336,23 +342,25 @@ static omprt_status build_plan(Plan& p, hipStream_t user_stream) {
     const size_t tile_b = (sizeof(TileDesc) * td.size() + 255) / 256 * 256;
     const size_t slot_b = ((size_t)kSlotBytes * td.size() + 255) / 256 * 256;
     const size_t ctr_b = ((size_t)(count + 4) * 4 + 255) / 256 * 256;
+    constexpr size_t done_b = (size_t)kElectGroupBytes * (1 + kElectGroups);
     const size_t short_b = shorts.size() * sizeof(int32_t);
-    if (hipMalloc(&p.dmem, seg_b + tile_b + slot_b + ctr_b + short_b) != hipSuccess)
+    if (hipMalloc(&p.dmem, seg_b + tile_b + slot_b + ctr_b + done_b + short_b) != hipSuccess)
         return fail(OMPRT_ERR_NOMEM, "batched plan allocation failed");
     char* base = static_cast<char*>(p.dmem);
     SegDesc* d_seg = reinterpret_cast<SegDesc*>(base);
     TileDesc* d_tile = reinterpret_cast<TileDesc*>(base + seg_b);
     uint32_t* d_ctr = reinterpret_cast<uint32_t*>(base + seg_b + tile_b + slot_b);
     BatchState bs{reinterpret_cast<uint64_t*>(base + seg_b + tile_b), d_ctr, d_ctr + count,
-                  d_ctr + count + 1, d_ctr + count + 2, d_ctr + count + 3, p.ntiles};
-    int32_t* d_short = reinterpret_cast<int32_t*>(base + seg_b + tile_b + slot_b + ctr_b);
+                  reinterpret_cast<uint32_t*>(base + seg_b + tile_b + slot_b + ctr_b),
+                  d_ctr + count + 1, d_ctr + count + 2, p.ntiles, 0};
+    int32_t* d_short = reinterpret_cast<int32_t*>(base + seg_b + tile_b + slot_b + ctr_b + done_b);
     if (count) OMPRT_HIP(hipMemcpy(d_seg, sd.data(), sizeof(SegDesc) * sd.size(), hipMemcpyHostToDevice));
     if (!td.empty())
         OMPRT_HIP(hipMemcpy(d_tile, td.data(), sizeof(TileDesc) * td.size(), hipMemcpyHostToDevice));
     if (nshort)
         OMPRT_HIP(hipMemcpy(d_short, shorts.data(), short_b, hipMemcpyHostToDevice));
     // once: zero slots (odd tags never match 0) and every counter
-    OMPRT_HIP(hipMemsetAsync(base + seg_b + tile_b, 0, slot_b + ctr_b, user_stream));
+    OMPRT_HIP(hipMemsetAsync(base + seg_b + tile_b, 0, slot_b + ctr_b + done_b, user_stream));
     OMPRT_HIP(hipStreamSynchronize(user_stream));
     p.status = bs.status;
 
@@ -374,6 +382,8 @@ static omprt_status build_plan(Plan& p, hipStream_t user_stream) {
         if (fit > 0) teams = std::min(teams, fit * p.cus);
     }
     p.grid = std::max(1, std::min<int>(teams, std::max<int32_t>(p.ntiles, 1)));
+    if (p.ntiles <= p.grid) p.use_ticket = 0;   // a tile each: nothing to draw
+    p.state.done_groups = p.grid >= 128;
     return OMPRT_OK;
 }
 
