@@ -688,12 +688,23 @@ def bench_batched(om, torch, leg=None):
                          "gb_s": round(total_bytes / us / 1e3, 1)}
         _log(f"batched {name}: {us / 1e3:.3f} ms")
 
+    def graph_of(config=None):
+        """The call captured once into a HIP graph (its plan built by a call before); the replay."""
+        side, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            om.reduce_batched(segs, config=config)
+        with torch.cuda.graph(g, stream=side):
+            om.reduce_batched(segs, config=config)
+        torch.cuda.current_stream().wait_stream(side)
+        return g.replay
+
     measure("plain_heuristic", lambda: om.reduce_each(segs, config={"flags": om.CFG_NO_MODEL}))
     if os.path.exists(MODEL_FILE):
         om.model_load(MODEL_FILE)
         measure("plain_learned", lambda: om.reduce_each(segs))
         om.model_load(None)
-    measure("batched_graph", lambda: om.reduce_batched(segs))
+    measure("batched_graph", graph_of())
     sweep = {}
     for tk in (64, 256, 1024, 4096):
         for th in (256, 512, 1024):
@@ -702,7 +713,7 @@ def bench_batched(om, torch, leg=None):
             sweep[f"tile={tk}KiB,threads={th}"] = round(us / 1e3, 3)
     best = min(sweep, key=sweep.get)
     tk, th = [int(v.split("=")[1].rstrip("KiB")) for v in best.split(",")]
-    measure("batched_graph_tuned", lambda: om.reduce_batched(segs, config={"tile_kib": tk, "threads": th}))
+    measure("batched_graph_tuned", graph_of({"tile_kib": tk, "threads": th}))
     results["batched_graph_tuned"]["config"] = {"tile_kib": tk, "threads": th}
     out = {"segments": 4096, "bytes": total_bytes, "forms": results,
            "tile_sweep_ms": sweep,

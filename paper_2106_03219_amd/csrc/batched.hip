@@ -14,7 +14,7 @@
 // last, which advances the epoch.  Results do not depend on which
 // workgroup ran which tile.  A segment of a few KB is not worth a workgroup's
 // barriers: one wave reduces it, and a tile is a bundle of as many as the
-// workgroup has waves (4096 segments of 1000 elements: 127 -> 10.9 us).  A
+// workgroup has waves (4096 segments of 1000 elements: 127 -> 9.0 us).  A
 // repeat call is one launch of the plan: counters, ticket and epoch maintain
 // themselves, so it needs no memset, also when a caller's graph replays it.
 #include <string.h>
@@ -449,7 +449,9 @@ extern "C" omprt_status omprt_reduce_batched(const omprt_segment* h_segs, int32_
         slot = std::move(p);
     }
     if (slot->ntiles == 0) return OMPRT_OK;
-    // one kernel: replaying it as a graph took 16 us of host time, this 2.5
+    // The launch itself, not a graph of it: replaying a captured one-node graph
+    // took 16 us of host time against 2.5, and 4096 segments of 10^2 to 10^7 2498
+    // us against 2468.  A caller's own graph may hold it.
     hipLaunchKernelGGL(slot->kernel, dim3(slot->grid), dim3(slot->cfg.threads_per_team), 0, stream,
                        slot->segs_dev, slot->tiles_dev, slot->shorts_dev, slot->state,
                        slot->use_ticket);

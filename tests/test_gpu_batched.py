@@ -171,3 +171,30 @@ def test_short_segments(gpu_lib, config):
             om.reduce_batched(segs, config=config)
             _check_all(xs, meta)
         assert empty.item() == 5 and om.workspace_status() == 0
+
+
+def test_large_plan_replay_and_capture(gpu_lib):
+    """A plan of more tiles than workgroups (tickets, several rounds): repeat calls, and the call
+    inside a graph of the caller's, replayed with the library's own calls in between."""
+    om = gpu_lib
+    big = torch.ones((512 << 20) // 8 + 5, dtype=torch.int64, device="cuda")
+    small = torch.arange(1001, dtype=torch.int64, device="cuda")
+    x, y = (torch.zeros(1, dtype=torch.int64, device="cuda") for _ in range(2))
+    segs = om.make_segments([(small, "sum", y), (big, "sum", x)])
+    calls = 0
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        for _ in range(3):
+            om.reduce_batched(segs)
+            calls += 1
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            om.reduce_batched(segs)
+        for _ in range(3):
+            g.replay()
+            om.reduce_batched(segs)
+            calls += 2
+            s.synchronize()
+            assert x.item() == calls * big.numel() and y.item() == calls * 500500
+        assert om.workspace_status() == 0
