@@ -61,8 +61,7 @@ __device__ __forceinline__ void count_key(C& c, int32_t k, const BinRange& r, bo
 // A vector of four keys a lane.  When every key of the wave's vectors is the
 // same (constant or sorted inputs) one lane adds their number: same-address
 // lanes of an LDS atomic are served one after another (10^8 equal keys into
-// 1000 bins: 333 us lane by lane, 65 this way; six operations for four
-// keys otherwise, hidden behind the keys' stream).
+// 1000 bins: 333 us lane by lane, 65 this way).
 using i32x4 = int32_t __attribute__((ext_vector_type(4)));
 template <class C>
 __device__ __forceinline__ void count_vector(C& c, const i32x4& k, const BinRange& r, bool& bad) {
@@ -77,6 +76,23 @@ __device__ __forceinline__ void count_vector(C& c, const i32x4& k, const BinRang
     } else {
 #pragma unroll
         for (int q = 0; q < 4; ++q) count_key(c, k[q], r, bad);
+    }
+}
+
+// U vectors a lane, with one comparison for other inputs: only where the lanes'
+// first keys are all the same does each vector look (looking at every vector
+// cost 2 % of 2 * 10^8 uniform keys).
+template <int U, class C>
+__device__ __forceinline__ void count_vectors(C& c, const i32x4 (&k)[U], const BinRange& r,
+                                              bool& bad) {
+    if (__ballot(k[0][0] != __builtin_amdgcn_readfirstlane(k[0][0])) == 0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) count_vector(c, k[u], r, bad);
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) count_key(c, k[u][q], r, bad);
     }
 }
 
@@ -106,8 +122,7 @@ __device__ __forceinline__ bool team_histogram(C c, const int32_t* __restrict__ 
             i32x4 r[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) r[u] = __builtin_nontemporal_load(vp + v + (int64_t)u * P);
-#pragma unroll
-            for (int u = 0; u < U; ++u) count_vector(c, r[u], bins, bad);
+            count_vectors<U>(c, r, bins, bad);
         }
         for (; v < nv; v += P) count_vector(c, __builtin_nontemporal_load(vp + v), bins, bad);
         const int64_t t0 = p0 + nv * 4;
@@ -1006,14 +1021,16 @@ constexpr uint32_t kDefaultMaxTsortTiles = 2;
 // keys and 40 000 bins (16 us; 512 teams of 512 threads, the earlier default,
 // 36), 114 for 10^6 keys and 1000 bins (8.3 against 13).  One team of 1024 a CU
 // also beats two of 512 where a copy leaves room for one team only (2^28 keys,
-// 40 000 bins: 176 against 274 us); with small copies and keys enough for three
-// teams a CU, two of 512 stay 1 % ahead (2^28 keys, 1000 bins: 160 against 162).
+// 40 000 bins: 176 against 274 us); with small copies and 9e7 keys or more, two
+// of 1024 are ahead of one (217 bins: 1e8 keys 65.6 against 67.3 us, 2e8 125.9
+// against 128.8, 3e8 185 against 193; 5e7 40.0 against 35.5) and of two of 512
+// (2e8 137).
 static void hist_shape(int64_t n, uint32_t bins, uint32_t tiles, int cus, int* teams,
                        int* threads) {
     const double best = sqrt(39.0 * (double)n / ((double)bins + 2000.0));
-    if (best >= 3.0 * cus && tiles == 1 && bins * 4 <= 64 * 1024) {
+    if (best >= 3.0 * cus && n >= 90000000 && tiles == 1 && bins * 4 <= 64 * 1024) {
         *teams = 2 * cus;
-        *threads = 512;
+        *threads = 1024;
         return;
     }
     const int64_t rows = std::min<int64_t>(std::max<int64_t>((int64_t)best, 1),

@@ -216,3 +216,24 @@ def test_alignment_tiles_and_order(gpu_lib, bins, offset):
                 torch.cuda.synchronize()
                 assert np.array_equal(h.cpu().numpy(), want), (bins, offset, n, kind, cfg)
     gpu_lib.workspace_reset()
+
+
+@pytest.mark.parametrize("n", [4096, 100003, 1 << 21])
+@pytest.mark.parametrize("pattern", ["first_equal", "all_equal", "half_waves"])
+def test_equal_first_keys(gpu_lib, n, pattern):
+    """Vectors whose first keys are the same in every lane of a wave, with the other keys the
+    same, different, or out of range: counted one by one or by one lane as the keys are."""
+    om = gpu_lib
+    bins = 300
+    g = np.random.Generator(np.random.PCG64(n))
+    keys = g.integers(0, bins, n).astype(np.int32)
+    if pattern == "first_equal":
+        keys[::4] = 7
+    elif pattern == "all_equal":
+        keys[:] = 299
+    else:
+        keys[(np.arange(n) // 256) % 2 == 0] = 42
+    hist = torch.zeros(bins, dtype=torch.int32, device="cuda")
+    om.histogram(torch.from_numpy(keys).cuda(), bins, hist)
+    torch.cuda.synchronize()
+    assert np.array_equal(hist.cpu().numpy(), np.bincount(keys, minlength=bins))
