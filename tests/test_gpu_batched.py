@@ -198,3 +198,27 @@ def test_large_plan_replay_and_capture(gpu_lib):
             s.synchronize()
             assert x.item() == calls * big.numel() and y.item() == calls * 500500
         assert om.workspace_status() == 0
+
+
+@pytest.mark.parametrize("streams", [1, 2])
+def test_alternating_lists(gpu_lib, streams):
+    """A new list every call, on one stream or two in turn, with no synchronisation between:
+    each plan's tables are up before its launch and not overwritten under it."""
+    om = gpu_lib
+    lists = []
+    for k in range(3):
+        ins = [torch.full((n,), k + 1, dtype=torch.int64, device="cuda")
+               for n in (5, 700 + k, 3000, 70001 + 13 * k, 9) for _ in range(20 + 7 * k)]
+        for _ in range(streams):
+            xs = [torch.zeros(1, dtype=torch.int64, device="cuda") for _ in ins]
+            lists.append((ins, xs, om.make_segments([(i, "sum", x) for i, x in zip(ins, xs)]), k + 1))
+    torch.cuda.synchronize()
+    sides = [torch.cuda.Stream() for _ in range(streams)]
+    reps = 30
+    for _ in range(reps):
+        for j, (_, _, segs, _) in enumerate(lists):
+            with torch.cuda.stream(sides[j % streams]):
+                om.reduce_batched(segs)
+    torch.cuda.synchronize()
+    for ins, xs, _, v in lists:
+        assert [x.item() for x in xs] == [reps * v * i.numel() for i in ins]
