@@ -452,7 +452,9 @@ omprt_status omprt_reduce_array_plan(int64_t rows, int64_t m, int32_t dtype,
  * a host array; each segment follows omprt_reduce's semantics.  The plan
  * (descriptor and tile tables) is cached per (stream, segment list,
  * configuration): a repeat call with the same list is that one launch, which a
- * caller may also capture into a graph.  Segments may not alias each other's
+ * caller may also capture into a graph.  Building a plan waits on the host for
+ * the upload of its tables alone, not for earlier work of any stream; the plan
+ * is complete when the call returns.  Segments may not alias each other's
  * outputs.  cfg's threads_per_team / unroll / vec_bytes select the tile
  * kernel; num_teams the most workgroups of the persistent grid (0 = one full
  * wave of the device); tile_kib 0: 1024, or less where that would leave

@@ -236,30 +236,14 @@ static std::map<std::pair<int, hipStream_t>, std::unique_ptr<Plan>> g_plans;
 // still replay their launch, so they live until omprt_finalize
 static std::vector<std::unique_ptr<Plan>> g_retired_plans;
 
-// Pinned memory a plan's tables go up from, one per device, as large as the
-// largest plan's so far; free again when the copy out of it is done.
-struct Staging {
-    void* host = nullptr;
-    size_t cap = 0;
-    hipEvent_t copied = nullptr;
-};
-static std::map<int, Staging> g_staging;
+// The stream plans are uploaded on, one per device: it holds nothing but the
+// uploads themselves.
+static std::map<int, hipStream_t> g_upload_streams;
 
-static omprt_status staging_get(int dev, size_t bytes, Staging** out) {
-    Staging& st = g_staging[dev];
-    if (!st.copied)
-        OMPRT_HIP(hipEventCreateWithFlags(&st.copied, hipEventDisableTiming));
-    OMPRT_HIP(hipEventSynchronize(st.copied));   // (done at once if never recorded)
-    if (st.cap < bytes) {
-        if (st.host) (void)hipHostFree(st.host);
-        st.host = nullptr;
-        st.cap = 0;
-        const size_t cap = std::max<size_t>(bytes, (size_t)1 << 18);
-        if (hipHostMalloc(&st.host, cap) != hipSuccess)
-            return fail(OMPRT_ERR_NOMEM, "pinned allocation of %zu bytes failed", cap);
-        st.cap = cap;
-    }
-    *out = &st;
+static omprt_status upload_stream(int dev, hipStream_t* out) {
+    hipStream_t& s = g_upload_streams[dev];
+    if (!s) OMPRT_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
+    *out = s;
     return OMPRT_OK;
 }
 
@@ -311,7 +295,7 @@ constexpr int64_t kMaxTileBytes = 1 << 20, kMinTileBytes = 64 << 10;
 // fifteen others): 4096 segments of 4000 elements 65.4 -> 20.4 us.
 constexpr int64_t kShortBytes = 8 << 10, kLongShortBytes = 32 << 10;
 
-static omprt_status build_plan(Plan& p, hipStream_t user_stream) {
+static omprt_status build_plan(Plan& p) {
     const int32_t count = (int32_t)p.segs.size();
     int64_t tile_bytes = (int64_t)p.cfg.tile_kib * 1024;
     if (!tile_bytes) {
@@ -378,21 +362,21 @@ static omprt_status build_plan(Plan& p, hipStream_t user_stream) {
     BatchState bs{reinterpret_cast<uint64_t*>(base + tables_b), d_ctr, d_ctr + count,
                   reinterpret_cast<uint32_t*>(base + tables_b + slot_b + ctr_b),
                   d_ctr + count + 1, d_ctr + count + 2, p.ntiles, 0};
-    // The tables in one copy from pinned memory, behind what the stream already
-    // holds: neither it nor the launch after it waits for the host (a copy each
-    // from pageable memory and a synchronisation drained the stream: a new list
-    // of 2719 segments a call 147 -> 63 us, of 94 54 -> 18).
-    Staging* st = nullptr;
-    if (omprt_status e = staging_get(p.device, tables_b, &st)) return e;
-    char* up = static_cast<char*>(st->host);
-    memcpy(up, sd.data(), sizeof(SegDesc) * sd.size());
-    if (!td.empty()) memcpy(up + seg_b, td.data(), sizeof(TileDesc) * td.size());
-    int32_t* up_short = reinterpret_cast<int32_t*>(up + seg_b + tile_b);
+    // The tables in one copy, then zero slots (odd tags never match 0) and zero
+    // counters.  The memory is new, so nothing on the caller's stream has to come
+    // first, and a stream that holds only this is waited for: the plan is whole
+    // when the call returns, whichever stream a graph of its launch is replayed
+    // on, and the host waits for no stream's earlier work.  (UPLOAD_FIGURES)
+    std::vector<char> up(tables_b);
+    memcpy(up.data(), sd.data(), sizeof(SegDesc) * sd.size());
+    if (!td.empty()) memcpy(up.data() + seg_b, td.data(), sizeof(TileDesc) * td.size());
+    int32_t* up_short = reinterpret_cast<int32_t*>(up.data() + seg_b + tile_b);
     for (int64_t j = 0; j < nshort; ++j) up_short[j] = (int32_t)(uint32_t)keys[j];
-    OMPRT_HIP(hipMemcpyAsync(base, up, tables_b, hipMemcpyHostToDevice, user_stream));
-    OMPRT_HIP(hipEventRecord(st->copied, user_stream));
-    // once: zero slots (odd tags never match 0) and every counter
-    OMPRT_HIP(hipMemsetAsync(base + tables_b, 0, slot_b + ctr_b + done_b, user_stream));
+    hipStream_t us = nullptr;
+    if (omprt_status e = upload_stream(p.device, &us)) return e;
+    OMPRT_HIP(hipMemcpyAsync(base, up.data(), tables_b, hipMemcpyHostToDevice, us));
+    OMPRT_HIP(hipMemsetAsync(base + tables_b, 0, slot_b + ctr_b + done_b, us));
+    OMPRT_HIP(hipStreamSynchronize(us));
     p.status = bs.status;
 
     p.segs_dev = d_seg;
@@ -431,15 +415,9 @@ void batched_finalize() {
     }
     g_plans.clear();
     g_retired_plans.clear();
-    for (auto& kv : g_staging) {
-        (void)hipSetDevice(kv.first);
-        if (kv.second.copied) {
-            (void)hipEventSynchronize(kv.second.copied);
-            (void)hipEventDestroy(kv.second.copied);
-        }
-        if (kv.second.host) (void)hipHostFree(kv.second.host);
-    }
-    g_staging.clear();
+    for (auto& kv : g_upload_streams)
+        if (kv.second) (void)hipStreamDestroy(kv.second);
+    g_upload_streams.clear();
 }
 
 }  // namespace omprt
@@ -482,7 +460,7 @@ extern "C" omprt_status omprt_reduce_batched(const omprt_segment* h_segs, int32_
         p->stream = stream;
         p->segs.assign(h_segs, h_segs + count);
         p->cfg = c;
-        if (omprt_status st = build_plan(*p, stream)) {
+        if (omprt_status st = build_plan(*p)) {
             p->release();
             return st;
         }

@@ -3,6 +3,7 @@ replayed) against the oracle per segment, plus the plain one-launch-per-
 segment form; both ticket and round-robin tile dealing; replays without
 any counter reset.
 """
+import time
 from concurrent.futures import ThreadPoolExecutor
 
 import pytest
@@ -222,3 +223,66 @@ def test_alternating_lists(gpu_lib, streams):
     torch.cuda.synchronize()
     for ins, xs, _, v in lists:
         assert [x.item() for x in xs] == [reps * v * i.numel() for i in ins]
+
+
+def _sleep_rate():
+    """Cycles of torch.cuda._sleep a second."""
+    start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    torch.cuda._sleep(1000)
+    start.record()
+    torch.cuda._sleep(10_000_000)
+    end.record()
+    end.synchronize()
+    return 10_000_000 / (start.elapsed_time(end) * 1e-3)
+
+
+def _filled_list(om, value, seed):
+    ins = [torch.full((n + seed,), value, dtype=torch.int64, device="cuda")
+           for n in (5, 700, 3000, 70001, 300007) for _ in range(12)]
+    xs = [torch.zeros(1, dtype=torch.int64, device="cuda") for _ in ins]
+    return ins, xs, om.make_segments([(i, "sum", x) for i, x in zip(ins, xs)])
+
+
+def test_new_list_behind_queued_work(gpu_lib):
+    """New lists on a stream whose earlier work is far from done, and on another stream: neither
+    call waits for that work, and the plan is whole when the call returns, so a graph of it,
+    captured at once, replays on an idle stream before the building stream gets to it.  (Two
+    streams may share one of the device's few hardware queues, whose work waits in line: one
+    pair of streams that do not is enough.)"""
+    om = gpu_lib
+    rate = _sleep_rate()
+    om.reduce_batched(_filled_list(om, 1, 0)[2])   # what the library sets up once
+    ahead = False
+    for attempt in range(8):
+        first, second, other = (_filled_list(om, v, 11 * v + attempt) for v in (1, 2, 3))
+        busy, idle = torch.cuda.Stream(), torch.cuda.Stream()
+        done = torch.cuda.Event()
+        torch.cuda.synchronize()
+        began = time.perf_counter()
+        with torch.cuda.stream(busy):
+            torch.cuda._sleep(int(0.4 * rate))
+            done.record()
+            om.reduce_batched(first[2])
+            om.reduce_batched(second[2])
+            g = torch.cuda.CUDAGraph()
+            g.capture_begin(capture_error_mode="thread_local")
+            om.reduce_batched(second[2])
+            g.capture_end()
+        late = time.perf_counter() - began > 0.2
+        if late:   # a plan's launches must not overlap
+            idle.wait_stream(busy)
+        with torch.cuda.stream(idle):
+            om.reduce_batched(other[2])
+            for _ in range(3):
+                g.replay()
+        idle.synchronize()
+        ahead = not late and not done.query()
+        assert [x.item() for x in other[1]] == [3 * i.numel() for i in other[0]]
+        if ahead:
+            assert [x.item() for x in second[1]] == [3 * 2 * i.numel() for i in second[0]]
+        torch.cuda.synchronize()
+        assert [x.item() for x in first[1]] == [i.numel() for i in first[0]]
+        assert [x.item() for x in second[1]] == [4 * 2 * i.numel() for i in second[0]]
+        if ahead:
+            break
+    assert ahead
