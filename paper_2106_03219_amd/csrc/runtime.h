@@ -52,9 +52,6 @@ void retire_device_memory(int dev, void* p);
 // here (never while the stream is being captured).
 omprt_status workspace_get(hipStream_t stream, int32_t teams, Workspace** out);
 
-// Whether `stream` has a workspace already.
-bool workspace_has(hipStream_t stream);
-
 struct LaunchCfg {
     int teams, threads, vec, unroll;
 };

@@ -119,17 +119,6 @@ omprt_status workspace_get(hipStream_t stream, int32_t teams, Workspace** out) {
     return OMPRT_OK;
 }
 
-bool workspace_has(hipStream_t stream) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return false;
-    if (t_ws.ws && t_ws.dev == dev && t_ws.stream == stream &&
-        t_ws.generation == g_ws_generation.load(std::memory_order_acquire))
-        return true;
-    std::lock_guard<std::mutex> lk(g_mu);
-    auto it = g_ws.find({dev, stream});
-    return it != g_ws.end() && it->second.base;
-}
-
 // ---------------------------------------------------------------- configuration
 
 struct TuneKey {

@@ -186,3 +186,40 @@ def test_training_graph_replays_match_eager(gpu_lib):
     for mode in ("eager", "graph"):
         assert np.array_equal(out[mode][0].view(np.uint32), out["sync"][0].view(np.uint32)), mode
     assert out["graph"][1][-1].split()[-1] == out["eager"][1][-1].split()[-1]
+
+
+def test_adam_graph_beside_reductions(gpu_lib):
+    """A graph of the counted Adam step alone, replayed on another stream while the stream that it
+    was captured on runs reductions: the two share nothing."""
+    om = gpu_lib
+    n, reps = 9472, 300
+    g = np.random.Generator(np.random.PCG64(3))
+    state = [torch.from_numpy(g.standard_normal(n).astype(np.float32)).cuda() for _ in range(2)]
+    a, b = ([state[0].clone(), torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda")]
+            for _ in range(2))
+    grads = state[1]
+    step = torch.zeros(1, dtype=torch.int32, device="cuda")
+    big = torch.ones(1 << 24, dtype=torch.int32, device="cuda")
+    s, t = torch.cuda.Stream(), torch.cuda.Stream()
+    xs = torch.zeros(reps, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        om.reduce(big, "sum", xs[:1])
+    s.synchronize()
+    xs.zero_()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        om.mlp_adam_counted(b[0], b[1], b[2], grads, step, lr=1e-2)
+    torch.cuda.synchronize()
+    for k in range(reps):
+        with torch.cuda.stream(s):
+            om.reduce(big, "sum", xs[k:k + 1])
+        with torch.cuda.stream(t):
+            graph.replay()
+    for k in range(reps):
+        om.mlp_adam(a[0], a[1], a[2], grads, k + 1, lr=1e-2)
+    torch.cuda.synchronize()
+    assert step.item() == reps
+    assert bool((xs == big.numel()).all())
+    for p, q in zip(a, b):
+        assert torch.equal(p, q)
