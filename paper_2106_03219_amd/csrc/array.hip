@@ -162,12 +162,17 @@ static int64_t tile_count(int64_t rows, int64_t m, int64_t wmax, int esize) {
     return std::max(t, least);
 }
 
-// Geometry for E elements per load; false if it cannot stream in vectors.
-static bool array_geometry(int64_t rows, int64_t m, int E, int64_t L, ArrayGeom* g) {
+// The most columns of a tile, for L elements a period and E per load.
+static int64_t max_tile_width(int E, int64_t L) {
+    return std::min<int64_t>(kTileCols, L) / E * E;
+}
+
+// Geometry for E elements per load over `tiles` column tiles (of up to
+// max_tile_width columns); false if it cannot stream in vectors.
+static bool array_geometry(int64_t rows, int64_t m, int E, int64_t L, int64_t tiles,
+                           ArrayGeom* g) {
     g->rows = rows;
     g->m = m;
-    const int64_t wmax = std::min<int64_t>(kTileCols, L) / E * E;
-    const int64_t tiles = tile_count(rows, m, wmax, 16 / E);
     if (tiles == 1) {   // whole rows; a period's first element must stay 16-byte aligned
         const int64_t step = E / gcd64(m, E);
         g->W = m;
@@ -293,7 +298,14 @@ static omprt_status plan_array(int64_t rows, int64_t m, int dtype, int op, const
                                                                         : 4;
         for (int u = u0; u >= 1 && !found; u /= 2) {
             ArrayGeom g{};
-            if (array_geometry(rows, m, E, (int64_t)P * E * u, &g)) {
+            // A given unroll keeps the fewest tiles: it is not lowered until a
+            // tile's copies fit, and whole rows of any width stream in vectors
+            // where tiles of them would not.  So do element loads, for which more
+            // tiles were not measured.
+            const int64_t L = (int64_t)P * E * u, wmax = max_tile_width(E, L);
+            const int64_t tiles = vec && !explicit_u ? tile_count(rows, m, wmax, esize)
+                                                     : (m + wmax - 1) / wmax;
+            if (array_geometry(rows, m, E, L, tiles, &g)) {
                 // tiles that are not whole lines share them with their neighbours:
                 // ragged loads keep the lines in the caches
                 if (vec && !explicit_u && g.col_tiles > 1 && (g.W * esize % 128 || m * esize % 128))

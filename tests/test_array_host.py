@@ -160,3 +160,29 @@ def test_argument_errors_before_device():
     out = (ctypes.c_int64 * 8)()
     assert lib.omprt_reduce_array_plan(0, 5, 0, 0, 1, None, out) == _lib.ERR_INVALID
     assert lib.omprt_reduce_array_plan(5, 5, 0, 0, 1, None, None) == _lib.ERR_INVALID
+
+
+@pytest.mark.parametrize("aligned", [True, False])
+@pytest.mark.parametrize("rows,m,dt,op,config", [
+    (44894, 88, om.F64, "sum", {"unroll": 8}),
+    (131072, 131, om.F64, "sum", {"unroll": 8}),
+    (56513, 77, om.F64, "prod", {"unroll": 4}),
+    (9202, 495, om.F64, "sum", {"unroll": 8, "threads": 512}),
+    (155000, 101, om.F32, "sum", {"unroll": 4}),
+    (243819, 226, om.BF16, "max", {"unroll": 2}),
+    (20000, 101, om.BF16, "sum", {"vec": 2}),       # 4 MB
+    (100000, 101, om.BF16, "sum", {"vec": 2}),      # 20 MB
+    (40000, 100, om.F32, "max", {"vec": 4}),        # 15.3 MiB
+    (48000, 100, om.F32, "max", {"vec": 4}),        # 18.3 MiB
+    (1008246, 65, om.I64, "sum", {"vec": 8}),
+])
+def test_explicit_unroll_and_element_loads_keep_their_tiles(rows, m, dt, op, config, aligned):
+    """A given unroll, and element loads, keep the fewest tiles of up to 256 columns at any size of
+    the block, so that the call is taken, and whole rows of any width keep 16-byte loads."""
+    plan = om.reduce_array_plan(rows, m, dt, op, aligned16=aligned, config=config)
+    assert plan[2] == -(-m // 256)
+    u = config.get("unroll")
+    vectors = aligned and u and m <= 256
+    assert plan[5] == (16 if vectors else ESIZE[dt])
+    if u:
+        assert plan[7] == (min(u, 4) if vectors else u)
