@@ -448,3 +448,48 @@ def test_grouped_election(gpu_lib, teams):
     assert x.item() == wrap(total + (reps + 3) // 4 * long_n)
     assert y.item() == wrap(total)
     assert om.workspace_status() == 0
+
+
+@pytest.mark.parametrize("dtype", [synth.F32, synth.F64, synth.BF16])
+@pytest.mark.parametrize("where", ["lane", 1, 2, 8, 64, "teams"])
+def test_joins_keep_low_words(gpu_lib, dtype, where):
+    """Every level of a sum's tree adds pairs without losing the rounding error of their low
+    words: of A + p and -A + q, whose high words cancel, all of p + q is kept (2^30 + 1, or
+    2^60 + 1, takes both words), and B - p and -B then leave q.  The eight values sit where one
+    level after another joins them in that order (in one lane's accumulators, in lanes, rows,
+    waves and teams) and everything else is 0, so the sum is q exactly."""
+    om = gpu_lib
+    big, p = (2.0 ** 120, 2.0 ** 60) if dtype == synth.F64 else (2.0 ** 60, 2.0 ** 30)
+    values = [big, p, -big, 1.0, big, -p, -big, 0.0]
+    esize = {synth.F32: 4, synth.F64: 8, synth.BF16: 2}[dtype]
+    vec = 8 if dtype == synth.BF16 else 16   # bytes: as many elements as accumulators
+    per = vec // esize
+    cfg = {"teams": 1, "threads": 512, "vec": vec, "unroll": 1}
+    if where == "lane":
+        n, at = 64, range(8)
+    elif where == "teams":
+        n, at = 8 * 64, range(0, 8 * 64, 64)
+        cfg.update(teams=8, threads=64)
+    else:
+        n, at = 512 * per, range(0, 8 * where * per, where * per)
+    tdt = {synth.F32: torch.float32, synth.F64: torch.float64, synth.BF16: torch.bfloat16}[dtype]
+    dev = torch.zeros(n, dtype=tdt, device="cuda")
+    dev[list(at)] = torch.tensor(values, dtype=tdt, device="cuda")
+    odt = torch.float64 if dtype == synth.F64 else torch.float32
+    xs = [torch.zeros(1, dtype=odt, device="cuda") for _ in range(3)]
+    om.reduce(dev, "sum", xs[0], config=cfg)
+    om.reduce_noalloc(dev, "sum", xs[1], config=cfg)
+    if where != 64 and where != "teams":   # a short segment is one wave's
+        om.reduce_batched([(dev, "sum", xs[2])], config=cfg)
+    else:
+        xs[2].fill_(1.0)
+    torch.cuda.synchronize()
+    assert [x.item() for x in xs] == [1.0, 1.0, 1.0]
+    if dtype == synth.F32:
+        s = torch.zeros(1, device="cuda")
+        y = torch.zeros(512, device="cuda")
+        stride = where if isinstance(where, int) else 1
+        y[list(range(0, 8 * stride, stride))] = torch.tensor(values, device="cuda")
+        om.axpy_sum(0.5, torch.zeros_like(y), y, s, teams=1, threads=512)
+        torch.cuda.synchronize()
+        assert s.item() == 1.0
