@@ -230,11 +230,6 @@ static inline unsigned blocks(int64_t n, int t) { return (unsigned)((n + t - 1) 
 
 // ---------------------------------------------------------------- fused path
 
-// Rows a wave of mlp_rows_kernel takes: one while the tiles' latency is what the
-// kernel takes (256 rows 10.1 us, 4096 22), four past that (a weight read from
-// LDS then serves four rows; 4096 rows run alike either way).
-static int rows_per_wave(int B) { return B <= 4096 ? 1 : 4; }
-
 // LDS of the row tiles may take; the rest of the 160 KiB stays free for a
 // second kernel's workgroups.
 constexpr int kRowsLdsLimit = 128 * 1024;
@@ -247,17 +242,28 @@ static int grad_slices(int B) {
 
 static MlpShape shape_of(const omprt_mlp_dims* d) { return MlpShape{d->F, d->H1, d->H2, d->K}; }
 
-// Whether the network takes the fused kernels.
-static bool fused_fits(const omprt_mlp_dims* d, int B) {
+static int64_t rows_lds_bytes(const omprt_mlp_dims* d, int rpw) {
     // (products of dimensions up to 4096 fit an int)
-    return (int64_t)mlp_rows_lds(shape_of(d), kRowsWaves * rows_per_wave(B)) * 4 <= kRowsLdsLimit;
+    return (int64_t)mlp_rows_lds(shape_of(d), kRowsWaves * rpw) * 4;
+}
+
+// Whether the network takes the fused kernels: its weights and the smallest
+// tile fit, whatever the batch (so the scratch a call needs grows with it).
+static bool fused_fits(const omprt_mlp_dims* d) { return rows_lds_bytes(d, 1) <= kRowsLdsLimit; }
+
+// Rows a wave of mlp_rows_kernel takes: one while the tiles' latency is what the
+// kernel takes (256 rows 10.1 us, 4096 22), four past that where such a tile
+// fits (a weight read from LDS then serves four rows; 4096 rows run alike
+// either way).
+static int rows_per_wave(const omprt_mlp_dims* d, int B) {
+    return B > 4096 && rows_lds_bytes(d, 4) <= kRowsLdsLimit ? 4 : 1;
 }
 
 template <bool TRAIN>
 static omprt_status launch_rows(const omprt_mlp_dims* d, const float* params, const float* X,
                                 const int32_t* y, int B, const MlpRowsOut& out, hipStream_t s) {
-    const int rpw = rows_per_wave(B);
-    const size_t lds = (size_t)mlp_rows_lds(shape_of(d), kRowsWaves * rpw) * 4;
+    const int rpw = rows_per_wave(d, B);
+    const size_t lds = (size_t)rows_lds_bytes(d, rpw);
     auto go = [&](auto kernel) -> omprt_status {
         if (lds > 64 * 1024)   // past the default dynamic LDS limit: ask for it
             OMPRT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
@@ -301,7 +307,7 @@ extern "C" omprt_status omprt_mlp_forward(const omprt_mlp_dims* d, const float* 
     if (B == 0) return OMPRT_OK;
     if (!d_params || !d_X || !d_Z) return fail(OMPRT_ERR_INVALID, "NULL pointer");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    if (fused_fits(d, B)) {
+    if (fused_fits(d)) {
         MlpRowsOut out{};
         out.z = d_Z;
         if (omprt_status st = launch_rows<false>(d, d_params, d_X, nullptr, B, out, s)) return st;
@@ -333,7 +339,7 @@ extern "C" omprt_status omprt_mlp_loss_grad(const omprt_mlp_dims* d, const float
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const int64_t H1 = d->H1, H2 = d->H2, K = d->K, F = d->F;
     float* scr = nullptr;
-    const bool fused = fused_fits(d, B);
+    const bool fused = fused_fits(d);
     const int S = fused ? grad_slices(B) : 1;
     const int64_t np = omprt_mlp_param_count(d);
     // rows, rounded to whole pairs, then the slices' pairs

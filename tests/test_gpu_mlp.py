@@ -223,3 +223,48 @@ def test_adam_graph_beside_reductions(gpu_lib):
     assert bool((xs == big.numel()).all())
     for p, q in zip(a, b):
         assert torch.equal(p, q)
+
+
+@pytest.mark.parametrize("dims", [(16, 64, 64, 64), (16, 128, 128, 64), (16, 160, 200, 10)])
+def test_larger_batch_covers_smaller_capture(gpu_lib, dims):
+    """Batches on both sides of 4096 rows, where the row tiles change: the scratch of a call made
+    once with the larger batch is enough for a capture with a smaller one, of a network whose
+    tiles of 16 rows fit the LDS, whose tiles of 4 alone do, and of neither."""
+    om = gpu_lib
+    F, H1, H2, K = dims
+    g = np.random.Generator(np.random.PCG64(H1))
+    P32 = {k: v.astype(np.float32) for k, v in _params(g, F, H1, H2, K).items()}
+    X = g.standard_normal((4097, F)).astype(np.float32)
+    y = g.integers(0, K, 4097).astype(np.int32)
+    params = torch.from_numpy(_flat(P32)).cuda()
+    Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    loss = torch.zeros(1, device="cuda")
+    grads = torch.zeros_like(params)
+
+    def check(B):
+        loss_ref, _, g_ref = oracle.mlp_loss_grad(X[:B].astype(np.float64), y[:B],
+                                                  {k: v.astype(np.float64) for k, v in P32.items()})
+        assert abs(loss.item() - loss_ref) <= 1e-5 * abs(loss_ref)
+        gh, off = grads.cpu().numpy().astype(np.float64), 0
+        for k in ("W1", "b1", "W2", "b2", "W3", "b3"):
+            sz = g_ref[k].size
+            assert _rel(gh[off:off + sz], g_ref[k].ravel()) < 1e-5, (k, B)
+            off += sz
+
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        om.mlp_loss_grad(dims, params, Xd, yd, loss, grads)
+    s.synchronize()
+    check(4097)
+    for B in (4096, 300):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            om.mlp_loss_grad(dims, params, Xd[:B], yd[:B], loss, grads)
+        for _ in range(2):
+            loss.fill_(-1.0)
+            grads.fill_(-1.0)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            check(B)
