@@ -1117,10 +1117,15 @@ static omprt_status histogram_tsorted(const int32_t* d_keys, int64_t n, uint32_t
     const int64_t keys_each = R <= 64 ? 32768 : 98304;
     const uint32_t W = (uint32_t)std::min<int64_t>(most, R + n / keys_each);
     auto up = [](uint64_t b) { return (b + 255) / 256 * 256; };
-    const uint64_t b_part = up((uint64_t)ts.G * kTsortSlot * 2),
-                   b_ts = up((uint64_t)ts.G * (R + 1) * 2), b_cnt = up((uint64_t)R * T * 4),
+    // room for the tiles at any alignment of the keys, and for partials that grow
+    // with the keys and the ranges, so that a call made once covers a capture with
+    // other keys, and with fewer keys or bins
+    const uint64_t W_any = (uint64_t)std::min<int64_t>(std::max(2 * cus, R), R + n / 32768);
+    const uint64_t G_any = (uint64_t)((n + kPartTile - 1) / kPartTile + 1);
+    const uint64_t b_part = up(G_any * kTsortSlot * 2), b_ts = up(G_any * (R + 1) * 2),
+                   b_cnt = up((uint64_t)R * std::min<uint64_t>((uint64_t)teams, G_any) * 4),
                    b_first = up((uint64_t)(R + 1) * 4),
-                   b_partial = W > R ? (uint64_t)W * kPartBins * 4 : 0;
+                   b_partial = W_any > R ? W_any * kPartBins * 4 : 0;
     void* pool = nullptr;
     if (omprt_status st = pool_get(stream, b_part + b_ts + b_cnt + b_first + b_partial, &pool))
         return st;

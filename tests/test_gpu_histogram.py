@@ -237,3 +237,39 @@ def test_equal_first_keys(gpu_lib, n, pattern):
     om.histogram(torch.from_numpy(keys).cuda(), bins, hist)
     torch.cuda.synchronize()
     assert np.array_equal(hist.cpu().numpy(), np.bincount(keys, minlength=bins))
+
+
+@pytest.mark.parametrize("first,then", [((3 * 8192 * 41, 1 << 20), (3 * 8192 * 41, 1 << 20)),
+                                        ((10_000_000, 1 << 22), (9_999_997, 1 << 21)),
+                                        ((10_000_000, 1 << 21), (4_000_000, 1 << 18))])
+def test_one_call_covers_captures(gpu_lib, first, then):
+    """A call made once covers the capture of calls on keys at any alignment (which are cut into
+    tiles in another place) and with fewer keys and bins (which are counted by other numbers of
+    workgroups)."""
+    om = gpu_lib
+    g = np.random.Generator(np.random.PCG64(first[0]))
+    cfg = {"flags": om.CFG_HIST_TILE_SORT}
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    n, bins = first
+    dev = torch.from_numpy(g.integers(0, bins, n).astype(np.int32)).cuda()
+    hist = torch.zeros(bins, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        om.histogram(dev, bins, hist, config=cfg)
+    s.synchronize()
+    assert torch.equal(hist.long(), torch.bincount(dev, minlength=bins))
+    n, bins = then
+    dev = torch.from_numpy(g.integers(0, bins, n + 3).astype(np.int32)).cuda()
+    hist = torch.zeros(bins, dtype=torch.int32, device="cuda")
+    for offset in (0, 1, 2, 3):
+        keys = dev[offset:n + offset]
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            om.histogram(keys, bins, hist, config=cfg)
+        hist.zero_()
+        torch.cuda.synchronize()
+        for _ in range(2):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(hist.long(), 2 * torch.bincount(keys, minlength=bins))
