@@ -90,7 +90,12 @@ static omprt_status array_ws_get(hipStream_t stream, int64_t counters, int64_t w
                         "stream is being captured and its array-reduction workspace is too "
                         "small: make the same call once before capturing");
         const int64_t nc = std::max<int64_t>({counters, ws.counters, 1024});
-        const int64_t nw = std::max<int64_t>({words, ws.words, (int64_t)1 << 16});
+        // at least what any call needs that leaves the team count to the runtime
+        // (268752 words; 512 teams of tiles of up to 256 columns, four words each,
+        // and half as many again for the groups bound it): the teams that it
+        // chooses do not grow with the block, and one call has to cover captures
+        // of smaller blocks
+        const int64_t nw = std::max<int64_t>({words, ws.words, (int64_t)786432});
         const size_t bytes = 256 + ArrayWs::ctr_bytes(nc) + (size_t)nw * 8;
         void* p = nullptr;
         if (hipMalloc(&p, bytes) != hipSuccess)

@@ -203,3 +203,27 @@ def test_many_tiles(gpu_lib, dtype, rows, m, config):
     cols = sorted({0, 1, W - 1, W, min(2 * W, m) - 1, m - W % 7 - 1, m - 1})
     for op in ("sum", "max"):
         run_and_check(gpu_lib, host, dtype, op, x_init(dtype, op, m, 12), config=config, cols=cols)
+
+
+@pytest.mark.parametrize("rows,fewer,m", [(21518, 7319, 254), (65536, 1000, 1001)])
+def test_one_call_covers_smaller_captures(gpu_lib, rows, fewer, m):
+    """A call made once covers the capture of one on fewer rows, which takes more teams a tile."""
+    om = gpu_lib
+    big = torch.randint(-1000, 1001, (rows * m + 1,), device="cuda").double()[1:]
+    x = torch.zeros(m, dtype=torch.float64, device="cuda")
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        om.reduce_array(big, rows, m, "sum", x)
+    s.synchronize()
+    assert torch.equal(x, big.reshape(rows, m).sum(0))
+    small = big[:fewer * m]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        om.reduce_array(small, fewer, m, "sum", x)
+    x.zero_()
+    torch.cuda.synchronize()
+    for _ in range(3):
+        graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(x, 3 * small.reshape(fewer, m).sum(0))
