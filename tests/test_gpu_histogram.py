@@ -273,3 +273,60 @@ def test_one_call_covers_captures(gpu_lib, first, then):
             graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(hist.long(), 2 * torch.bincount(keys, minlength=bins))
+
+
+@pytest.mark.parametrize("teams,threads,unroll", [(1, 0, 0), (4, 256, 4), (3, 64, 2), (2, 128, 1)])
+@pytest.mark.parametrize("pattern", ["first_equal", "first_equal_rest_out", "lane_equal",
+                                     "all_equal", "all_out", "first_out", "half_waves"])
+def test_groups_of_vectors(gpu_lib, teams, threads, unroll, pattern):
+    """The loop that compares a group of vectors at once (a team with more vectors than its
+    unrolled pass takes): first keys equal in every lane and the others different, partly or all
+    out of range, equal lane by lane, or equal throughout."""
+    om = gpu_lib
+    bins, n = 300, 200_003
+    P, U = threads or 512, unroll or 4
+    assert n // teams // 4 > 4 * U * P
+    g = np.random.Generator(np.random.PCG64(n + teams))
+    keys = g.integers(0, bins, n).astype(np.int32)
+    if pattern.startswith("first_equal"):
+        keys[::4] = 7
+    if pattern == "first_equal_rest_out":
+        for at, v in ((1, bins), (2, -1), (3, np.int32(-2**31))):
+            keys[at::8] = v
+        keys[5::24] = 2**31 - 1
+    elif pattern == "lane_equal":
+        keys[:n // 4 * 4] = np.repeat(keys[:n // 4], 4)
+    elif pattern == "all_equal":
+        keys[:] = 299
+    elif pattern == "all_out":
+        keys[:] = bins
+    elif pattern == "first_out":
+        keys[::4] = -5
+    elif pattern == "half_waves":
+        keys[(np.arange(n) // 256) % 2 == 0] = 42
+    h0 = g.integers(-1000, 1000, bins).astype(np.int32)
+    inside = keys[(keys >= 0) & (keys < bins)]
+    cfg = {"teams": teams, "threads": threads, "unroll": unroll}
+    for offset in (0, 3):
+        dev = torch.from_numpy(np.concatenate([np.zeros(offset, np.int32), keys])).cuda()[offset:]
+        hist = torch.from_numpy(h0).cuda()
+        om.histogram(dev, bins, hist, config=cfg)
+        torch.cuda.synchronize()
+        assert np.array_equal(hist.cpu().numpy(), h0 + np.bincount(inside, minlength=bins))
+        assert om.workspace_status() == (4 if inside.size < n else 0)
+        om.workspace_reset()
+
+
+@pytest.mark.parametrize("n", [89_999_999, 90_000_001])
+@pytest.mark.parametrize("bins", [5, 217, 16384, 16385])
+def test_teams_of_large_inputs(gpu_lib, n, bins):
+    """Both sides of the size from which small copies take two teams a compute unit."""
+    om = gpu_lib
+    g = torch.Generator(device="cuda")
+    g.manual_seed(bins)
+    keys = torch.randint(0, bins, (n,), device="cuda", dtype=torch.int32, generator=g)
+    keys[n // 3:n // 2] = bins - 1
+    hist = torch.zeros(bins, dtype=torch.int32, device="cuda")
+    om.histogram(keys, bins, hist)
+    torch.cuda.synchronize()
+    assert torch.equal(hist.long(), torch.bincount(keys, minlength=bins))
