@@ -236,6 +236,7 @@ struct ArrayPlan {
     int loads;   // ArrayLoads
     int threads, unroll;
     size_t lds;
+    int64_t most;   // row teams a tile before the estimate took fewer
 };
 
 static omprt_status plan_array(int64_t rows, int64_t m, int dtype, int op, const void* in,
@@ -340,6 +341,7 @@ static omprt_status plan_array(int64_t rows, int64_t m, int dtype, int op, const
     if (choose) want_teams = device_cus() * (pl.loads == kElements ? 2 : 1);
     int64_t rt = std::max<int64_t>(1, want_teams / g.col_tiles);
     rt = std::min<int64_t>(rt, std::max<int64_t>(1, g.np));
+    pl.most = rt;
     // Election groups: as many teams as the last one can fold with at most
     // kFoldItems partials per thread (fold_group); one group when all fit.
     const int64_t wc_max = std::min(g.W, m);
@@ -431,6 +433,12 @@ extern "C" omprt_status omprt_reduce_array(const void* d_in, int64_t rows, int64
         if (omprt_status st = array_ws_get(stream, counters, words, &ws)) return st;
         ct = ArrayCross{ws.slots(), ws.slots() + (int64_t)g.rt * m * nw, ws.ctrs(), ws.done(),
                         ws.epoch(), ws.status()};
+    } else if (pl.most > 1) {
+        // a smaller block may take several teams where the estimate gives this one
+        // a single one, and a call made once covers its capture: leave the
+        // workspace (this call itself needs none)
+        ArrayWs ws;
+        if (array_ws_get(stream, 0, 0, &ws) != OMPRT_OK) (void)hipGetLastError();
     }
     const ArrayLauncher f = array_launcher(dtype, op, pl.loads, pl.unroll);
     if (!f) return fail(OMPRT_ERR_UNSUPPORTED, "no array kernel for this combination");

@@ -205,9 +205,10 @@ def test_many_tiles(gpu_lib, dtype, rows, m, config):
         run_and_check(gpu_lib, host, dtype, op, x_init(dtype, op, m, 12), config=config, cols=cols)
 
 
-@pytest.mark.parametrize("rows,fewer,m", [(21518, 7319, 254), (65536, 1000, 1001)])
+@pytest.mark.parametrize("rows,fewer,m", [(21518, 7319, 254), (65536, 1000, 1001), (62, 46, 820)])
 def test_one_call_covers_smaller_captures(gpu_lib, rows, fewer, m):
-    """A call made once covers the capture of one on fewer rows, which takes more teams a tile."""
+    """A call made once covers the capture of one on fewer rows, which takes more teams a tile
+    (the last one four, where the larger block takes one)."""
     om = gpu_lib
     big = torch.randint(-1000, 1001, (rows * m + 1,), device="cuda").double()[1:]
     x = torch.zeros(m, dtype=torch.float64, device="cuda")
