@@ -171,18 +171,23 @@ hipError_t launch_axpy_sum(float a, const float* x, float* y, float* sum, int64_
     // idle: 2048 x 256 threads, 1e6, chunk 200 76 -> 103): the other ways go
     // element by element.  2^26 + 77: chunk 64 1088 -> 201, 0 1084 -> 235, 500
     // 1621 -> 248; 7e6: 75 -> 24, 102 -> 26; chunk 16 1e6 15.0 -> 13.3; chunk
-    // 12 1.6e7 80 -> 59, but 1e6 13.0 -> 13.8.  Co-aligned, off the line grid,
-    // inside the last-level cache: chunk 32 (1.6e7 45.5 -> 37.0, 2^25 87 -> 68),
-    // 20 to 31 (2^25 85 -> 75, 1e6 12.3 -> 13.0; 2^26 + 77 159 -> 165), and
-    // chunks of 64 to 128 with between one wave and half a round of them a
-    // block, where a lane has few lines to hide its edges behind (chunk 64 2e6
-    // 17.9 -> 14.2, 128 3e6 30.3 -> 17.7; past half a round chunk 100 1.2e7
-    // 39.5 -> 49).
+    // 12 1.6e7 80 -> 59, but 1e6 13.0 -> 13.8.  Co-aligned and off the line grid, a
+    // pass moves one segment of each lane and pays where most of it is a chunk:
+    // chunk 32 at every size below 2^26 (1e6 12.3 -> 10.1, 1.6e7 47.3 -> 36.7,
+    // 5e7 136 -> 122, 6e7 157.6 -> 151.0; 2^26 + 77 164.5 -> 165.9), more than
+    // half a segment from 2^23 on (20: 1.2e7 37.1 -> 33.1, 5e7 136 -> 124; but
+    // 7e6 22.8 -> 24.0, 6e7 161.8 -> 163.0; 18: 1.2e7 41.2 -> 35.7).  Chunks of
+    // 33 to 63 take two passes and run slower from 7e6 on (48: 7e6 22.0 -> 23.7,
+    // 1.6e7 45.3 -> 52.3), longer ones too but for chunks of 64 to 128 with
+    // between one wave and half a round of them a block, where a lane has few
+    // lines to hide its edges behind (64: 2e6 16.7 -> 12.2; 128: 3e6 31.0 ->
+    // 15.7; past half a round 100: 1.2e7 41.4 -> 49.5).
     const int64_t block_chunks = chunk > 0 ? (m_hi + chunk - 1) / chunk : threads;
     const int64_t run = chunk > 0 ? chunk : m_hi / threads;
+    constexpr int kSeg = AxpySegments::kSeg;
     const bool co_segments =
         !whole_runs && n < ((int64_t)1 << 26) &&
-        (chunk == 32 || (chunk >= 20 && chunk < 32 && n >= ((int64_t)1 << 22)) ||
+        (chunk == kSeg || (chunk > kSeg / 2 && chunk < kSeg && n >= ((int64_t)1 << 23)) ||
          (chunk >= 64 && chunk <= 128 && block_chunks >= kWave && block_chunks <= threads / 2));
     const bool any_segments =
         block_chunks >= kWave / 2 && run < ((int64_t)1 << 24) &&

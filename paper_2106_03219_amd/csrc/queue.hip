@@ -475,10 +475,15 @@ extern "C" omprt_status omprt_axpy_sum_queue(float a, const float* d_x, float* d
     // now, us, default launch).  Not co-aligned, the other ways go element by
     // element: 2^26 + 77 dynamic 64 605 -> 188, guided 16 1162 -> 225; dynamic
     // 16 1e6 14.8 -> 12.9, 8 3e6 22.3 -> 22.7, 8 2^25 153 -> 149; guided 1 1e6
-    // 14.0 -> 16.7, 3e6 27.0 -> 22.9.  Co-aligned, off the line grid: dynamic
-    // 32 (7e6 34.5 -> 22.2, 2^26 + 77 231 -> 161), 64 (31.6 -> 26.7, 198 ->
-    // 191), 20 to 31 (24: 29.8 -> 28.1, 211 -> 192; 2e6 16.0 -> 17.6); 16 and
-    // 100 ran alike through the union and the lines.  Guided rounds, whose
+    // 14.0 -> 16.7, 3e6 27.0 -> 22.9.  Co-aligned and off the line grid, a pass
+    // moves one segment of each lane and pays where most of it is a chunk: dynamic
+    // 32 (1e6 12.8 -> 9.6, 7e6 35.0 -> 22.3, 2^26 + 77 233 -> 158), more than half
+    // a segment (18: 7e6 33.8 -> 33.0, 1.6e7 72.6 -> 64.0; 24: 29.5 -> 27.4, 60.5
+    // -> 49.4; 2e6 alike) and two whole segments (64: 7e6 31.8 -> 26.5, 2^26 + 77
+    // 202 -> 186).  Chunk 16 ran alike through the union; those between one and
+    // two segments gain and lose with the size (48: 2e6 14.4 -> 13.1, 7e6 29.4
+    // -> 32.8, 2^25 115 -> 104), longer ones lose at 1e6 (80: 11.4 -> 14.2).
+    // Guided rounds, whose
     // lanes' chunks shrink along the wave so that few have lines: 16 7e6 43.4
     // -> 31.3, 2^24 67 -> 58; not from where the first chunks are long (2^25,
     // 512 iterations: 107 -> 114; 2^26: 185 -> 228), for chunks past two
@@ -487,6 +492,7 @@ extern "C" omprt_status omprt_axpy_sum_queue(float a, const float* d_x, float* d
     const int64_t m_hi = s->dist_chunk ? std::min<int64_t>(s->dist_chunk, s->n)
                                        : (s->n + teams - 1) / teams;
     const int64_t first = kind == KIND_GUIDED ? std::max((m_hi + threads - 1) / threads, c) : c;
+    constexpr int kSeg = AxpySegments::kSeg;
     bool segments = waves && first < ((int64_t)1 << 24) && m_hi / c >= kWave / 2;
     if (kind == KIND_GUIDED)
         segments = segments && (co ? c <= 64 && m_hi / c >= kWave && first <= 384 && m_hi >= 1024
@@ -494,8 +500,7 @@ extern "C" omprt_status omprt_axpy_sum_queue(float a, const float* d_x, float* d
     else
         segments = segments &&
                    (co ? !(on_grid && c % 32 == 0) &&
-                             (c == 32 || c == 64 ||
-                              (c >= 20 && c < 32 && s->n >= ((int64_t)1 << 22)))
+                             ((c > kSeg / 2 && c <= kSeg) || c == 2 * kSeg)
                        : c >= 16 || (c >= 8 && s->n >= ((int64_t)1 << 23)));
     if (kind == KIND_DYNAMIC && qc.cmin == 1) {
         hipLaunchKernelGGL((queue_axpy_kernel<true, 0>), dim3(teams), dim3(block), 0, stream,

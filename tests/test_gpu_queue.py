@@ -146,3 +146,22 @@ def test_axpy_segments(gpu_lib, kind, case):
     out = yb.cpu().numpy()
     check_axpy(out[lo_y:lo_y + n], s.item(), ref_y, ref_s, 0.25, (kind, case))
     assert np.array_equal(out[:lo_y], yh[:lo_y]) and np.array_equal(out[lo_y + n:], yh[lo_y + n:])
+
+
+@pytest.mark.parametrize("kind,n", [("dynamic", 300_007), ("static", (8 << 20) - 1),
+                                    ("static", (8 << 20) + 9)])
+@pytest.mark.parametrize("chunk", [16, 17, 18, 31, 32, 33, 63, 64, 65])
+def test_segment_chunks(gpu_lib, kind, n, chunk):
+    """Chunks on both sides of half a segment, of one and of two (32 elements each), co-aligned
+    and off the line grid, around the size from which parts of a segment go that way."""
+    om = gpu_lib
+    xh, yh = synth.f32_normal(n, 24), synth.f32_normal(n, 25)
+    ref_y, ref_s = oracle.axpy_sum(0.7, xh, yh, 0.25)
+    x, y = torch.from_numpy(xh).cuda(), torch.from_numpy(yh).cuda()
+    s = torch.tensor([0.25], dtype=torch.float32, device="cuda")
+    if kind == "static":
+        om.axpy_sum(0.7, x, y, s, 256, 128, 0, chunk)
+    else:
+        om.axpy_sum_queue(kind, 0.7, x, y, s, 37, 128, 0, chunk)
+    torch.cuda.synchronize()
+    check_axpy(y.cpu().numpy(), s.item(), ref_y, ref_s, 0.25, (kind, n, chunk))
