@@ -154,16 +154,20 @@ static int64_t gcd64(int64_t a, int64_t b) {
 // folds a tile in one level, and a row team's tiles go to one XCD evenly.  us,
 // fewest tiles -> this: 65536 x 1001 fp32 47.4 -> 43.6, fp64 94.7 -> 87.7;
 // 16000 x 1001 23.2 -> 19.4; 196000 x 333 47.6 -> 44.2; 80000 x 100 20.1 ->
-// 15.3; 256000 x 256 fp64 93.9 -> 85.0; but 1000 x 1001 10.4 -> 11.8, past 32
-// tiles (3276 x 19999) 46.4 -> 48.2, and narrow tiles of 8-byte elements past
-// the last-level cache (1008246 x 65 fp64 92 -> 112; 101265 x 79 28.6 -> 23.1).
+// 15.3; 256000 x 256 fp64 93.9 -> 85.0.  Not for blocks under 16 MiB, whose teams
+// have few periods each and wait for the combination (1000 x 1001 10.4 ->
+// 11.8), nor past 32 tiles, where the fewest already leave eight teams or fewer
+// a tile (3276 x 19999 46.4 -> 48.2).  Past the last-level cache (from 128 MiB)
+// 8-byte elements, whose loads bypass it, read the lines that tiles share from
+// memory twice: there a tile is at least four lines wide (1008246 x 65 fp64,
+// two tiles of 264 bytes, 92 -> 112; inside the cache 101265 x 79 28.6 -> 23.1).
 static int64_t tile_count(int64_t rows, int64_t m, int64_t wmax, int esize) {
     const int64_t least = (m + wmax - 1) / wmax;
     const int64_t bytes = rows * m * esize;
     if (m <= 64 || least > 32 || bytes < ((int64_t)16 << 20)) return least;
     int64_t t = 1;
     while (t < least || t * t * 32 < m) t *= 2;
-    while (esize == 8 && bytes > ((int64_t)128 << 20) && t > least && m * esize < t * 520) t /= 2;
+    while (esize == 8 && bytes > ((int64_t)128 << 20) && t > least && m * esize < t * 4 * 128) t /= 2;
     return std::max(t, least);
 }
 
