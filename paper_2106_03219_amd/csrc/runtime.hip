@@ -199,9 +199,15 @@ static LaunchCfg heuristic(int64_t n, int dtype, int body, int64_t chunk) {
         // waves: two teams of 512 (2: 2^22 36.8 -> 19.8, 2^24 57.9 -> 43.0; 3:
         // 52.5 -> 37.3), two loops from 2^22 on the general launch (2: 7e6 53.5
         // -> 56.9 with one).  Past the cache the general launch streams as well
-        // or better (2^26 chunk 64 148.7 -> 152.9, 0 144.9 -> 153.3) but for runs
-        // that are not whole lines (7: 284 -> 211, 100: 196 -> 160) and, until
-        // the blocks are long, chunks past 256 (500, 5e7 170 -> 134).
+        // or better for long runs (2^26 chunk 0 144.9 -> 153.3, 200 168 -> 174) and
+        // for runs of whole half lines on the line grid (64: 48 * 2^20 114 -> 121,
+        // 2^26 148.7 -> 152.9; 16: 48 * 2^20 116 -> 126); off the grid these would
+        // gain from one team of 512 (2^26 + 77: 16 185 -> 174, 64 159 -> 158;
+        // 2.5e7: 80 -> 75 and 88 -> 69), as would chunk 8 (2^26 174 -> 163, 5e7 197
+        // -> 188), and keep the general launch, which does not ask where a block
+        // starts.  Other runs of 5 to 127 (7: 2^26 286 -> 209; 100: 197 -> 160; but
+        // 9 on the grid 340 -> 357) and, until the blocks are long, chunks past 256
+        // (500, 5e7 170 -> 134) take one team of 512.
         const bool cached = n <= (body == 2 ? (int64_t)1 << 24 : (int64_t)5 << 22);
         const bool two_or_three = chunk == 2 || chunk == 3;
         if (two_or_three && n >= ((int64_t)1 << 22)) {
