@@ -314,10 +314,12 @@ static omprt_status build_plan(Plan& p) {
     const int32_t count = (int32_t)p.segs.size();
     int64_t tile_bytes = (int64_t)p.cfg.tile_kib * 1024;
     if (!tile_bytes) {
-        // 1 MiB, or less where that would be under two tiles a compute unit, but
-        // no segment of more than 128 (its tiles meet on one counter).  us, 1 MiB ->
-        // now: 16 segments of 200000 elements 23.3 -> 10.6, 1000 of 10^2 to 10^5.5
-        // 52.9 -> 38.1; one of 240 MB in 480 tiles 39.4 -> 48.3.
+        // 1 MiB, or less where that would be under two tiles a compute unit (or one
+        // a workgroup, where the caller asks for fewer of them), but no segment of
+        // more than 128 (its tiles meet on one counter).  us, 1 MiB -> now: 16
+        // segments of 200000 elements 23.3 -> 10.6, 1000 of 10^2 to 10^5.5 52.9 ->
+        // 38.1; one of 240 MB in 480 tiles 39.4 -> 48.3; 300 of 200000 elements
+        // over 64 workgroups 58 -> 50 (87 with tiles for every compute unit).
         int64_t total = 0, longest = 0;
         for (const omprt_segment& g : p.segs) {
             const int64_t bytes = std::min<int64_t>(g.n, (int64_t)1 << 40) * dtype_bytes(g.dtype);
@@ -325,7 +327,8 @@ static omprt_status build_plan(Plan& p) {
             longest = std::max(longest, bytes);
         }
         tile_bytes = kMaxTileBytes;
-        while (tile_bytes > kMinTileBytes && total / tile_bytes < 2 * p.cus &&
+        const int64_t want = p.cfg.num_teams < p.cus ? p.cfg.num_teams : 2 * p.cus;
+        while (tile_bytes > kMinTileBytes && total / tile_bytes < want &&
                longest / (tile_bytes / 2) <= 128)
             tile_bytes /= 2;
     }
