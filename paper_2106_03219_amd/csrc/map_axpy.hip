@@ -171,7 +171,10 @@ hipError_t launch_axpy_sum(float a, const float* x, float* y, float* sum, int64_
     // idle: 2048 x 256 threads, 1e6, chunk 200 76 -> 103): the other ways go
     // element by element.  2^26 + 77: chunk 64 1088 -> 201, 0 1084 -> 235, 500
     // 1621 -> 248; 7e6: 75 -> 24, 102 -> 26; chunk 16 1e6 15.0 -> 13.3; chunk
-    // 12 1.6e7 80 -> 59, but 1e6 13.0 -> 13.8.  Co-aligned and off the line grid, a
+    // 12 1.6e7 80 -> 59, but 1e6 13.0 -> 13.8.  Where a block is one wave's chunks
+    // and their second pass would move less than half a segment, element by
+    // element is faster (40: 1e5 in 74 teams 10.5 against 11.5, but in 16, three
+    // waves each, 15.7 against 11.8).  Co-aligned and off the line grid, a
     // pass moves one segment of each lane and pays where most of it is a chunk:
     // chunk 32 at every size below 2^26 (1e6 12.3 -> 10.1, 1.6e7 47.3 -> 36.7,
     // 5e7 136 -> 122, 6e7 157.6 -> 151.0; 2^26 + 77 164.5 -> 165.9), more than
@@ -189,8 +192,9 @@ hipError_t launch_axpy_sum(float a, const float* x, float* y, float* sum, int64_
         !whole_runs && n < ((int64_t)1 << 26) &&
         (chunk == kSeg || (chunk > kSeg / 2 && chunk < kSeg && n >= ((int64_t)1 << 23)) ||
          (chunk >= 64 && chunk <= 128 && block_chunks >= kWave && block_chunks <= threads / 2));
+    const bool thin_pass = chunk > kSeg && chunk < kSeg * 3 / 2 && block_chunks <= kWave;
     const bool any_segments =
-        block_chunks >= kWave / 2 && run < ((int64_t)1 << 24) &&
+        block_chunks >= kWave / 2 && run < ((int64_t)1 << 24) && !thin_pass &&
         (chunk == 0 ? run >= 8 : chunk >= 16 || (chunk >= 12 && n >= ((int64_t)1 << 23)));
     if (waves && n > 0 && (co_aligned ? co_segments : any_segments)) {
         mode = 3;
