@@ -1024,7 +1024,10 @@ constexpr uint32_t kDefaultMaxTsortTiles = 2;
 // 40 000 bins: 176 against 274 us); with small copies and 9e7 keys or more, two
 // of 1024 are ahead of one (217 bins: 1e8 keys 65.6 against 67.3 us, 2e8 125.9
 // against 128.8, 3e8 185 against 193; 5e7 40.0 against 35.5) and of two of 512
-// (2e8 137).
+// (2e8 137).  The counts above are for keys spread over the bins.  Keys that
+// meet on few bins are counted one after another, longer the fewer the teams
+// (10^6 keys of 16384 bins: uniform 28.3 -> 8.8 us, skewed 19.5 -> 12.3, but
+// sorted 8.0 -> 13.6 and two values 12.8 -> 15.6).
 static void hist_shape(int64_t n, uint32_t bins, uint32_t tiles, int cus, int* teams,
                        int* threads) {
     const double best = sqrt(39.0 * (double)n / ((double)bins + 2000.0));
