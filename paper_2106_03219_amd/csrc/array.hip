@@ -76,26 +76,28 @@ struct ArrayWs {
 static std::mutex g_amu;
 static std::map<std::pair<int, hipStream_t>, ArrayWs> g_aws;
 
-static omprt_status array_ws_get(hipStream_t stream, int64_t counters, int64_t words,
+// The stream's workspace for `counters` and `words`; with room for `room` words
+// unless the stream is being captured.
+static omprt_status array_ws_get(hipStream_t stream, int64_t counters, int64_t words, int64_t room,
                                  ArrayWs* out) {
     int dev = 0;
     OMPRT_HIP(hipGetDevice(&dev));
     std::lock_guard<std::mutex> lk(g_amu);
     ArrayWs& ws = g_aws[{dev, stream}];
-    if (!ws.base || ws.counters < counters || ws.words < words) {
+    const bool too_small = !ws.base || ws.counters < counters || ws.words < words;
+    if (too_small || ws.words < room) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         OMPRT_HIP(hipStreamIsCapturing(stream, &cs));
-        if (cs != hipStreamCaptureStatusNone)
-            return fail(OMPRT_ERR_INVALID,
-                        "stream is being captured and its array-reduction workspace is too "
-                        "small: make the same call once before capturing");
+        if (cs != hipStreamCaptureStatusNone) {
+            if (too_small)
+                return fail(OMPRT_ERR_INVALID,
+                            "stream is being captured and its array-reduction workspace is too "
+                            "small: make the same call once before capturing");
+            *out = ws;
+            return OMPRT_OK;
+        }
         const int64_t nc = std::max<int64_t>({counters, ws.counters, 1024});
-        // at least what any call needs that leaves the team count to the runtime
-        // (268752 words; 512 teams of tiles of up to 256 columns, four words each,
-        // and half as many again for the groups bound it): the teams that it
-        // chooses do not grow with the block, and one call has to cover captures
-        // of smaller blocks
-        const int64_t nw = std::max<int64_t>({words, ws.words, (int64_t)786432});
+        const int64_t nw = std::max<int64_t>({words, room, ws.words, (int64_t)1 << 16});
         const size_t bytes = 256 + ArrayWs::ctr_bytes(nc) + (size_t)nw * 8;
         void* p = nullptr;
         if (hipMalloc(&p, bytes) != hipSuccess)
@@ -159,15 +161,15 @@ static int64_t gcd64(int64_t a, int64_t b) {
 // 11.8), nor past 32 tiles, where the fewest already leave eight teams or fewer
 // a tile (3276 x 19999 46.4 -> 48.2).  Past the last-level cache (from 128 MiB)
 // 8-byte elements, whose loads bypass it, read the lines that tiles share from
-// memory twice: there a tile is at least four lines wide (1008246 x 65 fp64,
-// two tiles of 264 bytes, 92 -> 112; inside the cache 101265 x 79 28.6 -> 23.1).
+// memory twice: there tiles are wider than four lines (1008246 x 65 fp64, two
+// tiles of 264 bytes, 92 -> 112; inside the cache 101265 x 79 28.6 -> 23.1).
 static int64_t tile_count(int64_t rows, int64_t m, int64_t wmax, int esize) {
     const int64_t least = (m + wmax - 1) / wmax;
     const int64_t bytes = rows * m * esize;
     if (m <= 64 || least > 32 || bytes < ((int64_t)16 << 20)) return least;
     int64_t t = 1;
     while (t < least || t * t * 32 < m) t *= 2;
-    while (esize == 8 && bytes > ((int64_t)128 << 20) && t > least && m * esize < t * 4 * 128) t /= 2;
+    while (esize == 8 && bytes > ((int64_t)128 << 20) && t > least && m * esize <= t * 4 * 128) t /= 2;
     return std::max(t, least);
 }
 
@@ -240,7 +242,11 @@ struct ArrayPlan {
     int loads;   // ArrayLoads
     int threads, unroll;
     size_t lds;
-    int64_t most;   // row teams a tile before the estimate took fewer
+    // The most row teams that the runtime gives a block of this many columns,
+    // whatever its rows (0: the caller gave the team count).  Workspaces have room
+    // for them: its choice does not grow with the rows, and a call made once has to
+    // cover captures of smaller blocks.
+    int64_t most;
 };
 
 static omprt_status plan_array(int64_t rows, int64_t m, int dtype, int op, const void* in,
@@ -345,7 +351,7 @@ static omprt_status plan_array(int64_t rows, int64_t m, int dtype, int op, const
     if (choose) want_teams = device_cus() * (pl.loads == kElements ? 2 : 1);
     int64_t rt = std::max<int64_t>(1, want_teams / g.col_tiles);
     rt = std::min<int64_t>(rt, std::max<int64_t>(1, g.np));
-    pl.most = rt;
+    pl.most = choose ? std::max<int64_t>(1, want_teams / ((m + kTileCols - 1) / kTileCols)) : 0;
     // Election groups: as many teams as the last one can fold with at most
     // kFoldItems partials per thread (fold_group); one group when all fit.
     const int64_t wc_max = std::min(g.W, m);
@@ -429,20 +435,21 @@ extern "C" omprt_status omprt_reduce_array(const void* d_in, int64_t rows, int64
     const ArrayGeom& g = pl.g;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     ArrayCross ct{};
+    const int nw = acc_bytes(dtype, op) / 4;
+    // (groups have at least two teams)
+    const int64_t room = pl.most > 1 ? (pl.most + (pl.most + 1) / 2) * m * nw : 0;
     if (g.rt > 1) {
-        const int nw = acc_bytes(dtype, op) / 4;
         const int64_t counters = (int64_t)g.col_tiles * g.ng + (g.ng > 1 ? g.col_tiles : 0);
         const int64_t words = ((int64_t)g.rt + (g.ng > 1 ? g.ng : 0)) * m * nw;
         ArrayWs ws;
-        if (omprt_status st = array_ws_get(stream, counters, words, &ws)) return st;
+        if (omprt_status st = array_ws_get(stream, counters, words, room, &ws)) return st;
         ct = ArrayCross{ws.slots(), ws.slots() + (int64_t)g.rt * m * nw, ws.ctrs(), ws.done(),
                         ws.epoch(), ws.status()};
-    } else if (pl.most > 1) {
+    } else if (room) {
         // a smaller block may take several teams where the estimate gives this one
-        // a single one, and a call made once covers its capture: leave the
-        // workspace (this call itself needs none)
+        // a single one: leave the workspace (this call itself needs none)
         ArrayWs ws;
-        if (array_ws_get(stream, 0, 0, &ws) != OMPRT_OK) (void)hipGetLastError();
+        if (array_ws_get(stream, 0, 0, room, &ws) != OMPRT_OK) (void)hipGetLastError();
     }
     const ArrayLauncher f = array_launcher(dtype, op, pl.loads, pl.unroll);
     if (!f) return fail(OMPRT_ERR_UNSUPPORTED, "no array kernel for this combination");
