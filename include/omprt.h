@@ -266,7 +266,8 @@ omprt_status omprt_reduce(const void *d_in, int64_t n, int32_t dtype,
  * num_teams (default two per compute unit), threads_per_team (default
  * 512; the partitioned passes have their own), unroll 1, 2 or 4 (default
  * 4); with neither given the LDS copies take teams of 1024 threads, at most
- * one per compute unit and fewer the fewer keys there are.  bins 1..2^28.
+ * one per compute unit and fewer the fewer keys there are, or two per compute
+ * unit from 9e7 keys on with one range of up to 16384 bins.  bins 1..2^28.
  */
 omprt_status omprt_histogram(const int32_t *d_keys, int64_t n, int32_t bins,
                              int32_t *d_hist, const omprt_config *cfg,
@@ -458,7 +459,7 @@ omprt_status omprt_reduce_array_plan(int64_t rows, int64_t m, int32_t dtype,
  * outputs.  cfg's threads_per_team / unroll / vec_bytes select the tile
  * kernel; num_teams the most workgroups of the persistent grid (0 = one full
  * wave of the device); tile_kib 0: 1024, or less where that would leave
- * compute units idle.  Segments of a few KB are reduced by one wave each.
+ * compute units (or num_teams workgroups, if fewer) idle.  Segments of a few KB are reduced by one wave each.
  * Defining passages: each segment is one reduction region with omprt_reduce's
  * semantics; the tiles of a segment play its teams: each reduces its part
  * through the team-shared tree and the last tile, elected by the wrap-around
@@ -611,7 +612,10 @@ omprt_status omprt_empty_region(const omprt_sched *s, int64_t *d_iters,
  *   MAX      { v = *X; if (*X < E) *X = E; }           (unsigned compare)
  *   EXCHANGE { v = *X; *X = E; }
  *   CAS      { v = *X; if (*X == E) *X = D; }
- * Sequentially consistent at agent scope (one GPU). */
+ * Sequentially consistent among themselves at agent scope (one GPU): every
+ * thread of omprt_atomic_apply makes one operation, so any order that respects
+ * each word's own sequence of values is an order of them all.  They order no
+ * other memory accesses within the launch; the launch is stream-ordered. */
 typedef enum {
     OMPRT_ATOMIC_ADD = 0, OMPRT_ATOMIC_INC = 1, OMPRT_ATOMIC_MAX = 2,
     OMPRT_ATOMIC_EXCHANGE = 3, OMPRT_ATOMIC_CAS = 4
@@ -675,7 +679,7 @@ omprt_status omprt_mlp_adam(float *d_params, float *d_m, float *d_v,
  * t = *d_step + 1 and leaves *d_step = t.  Nothing depends on host values
  * that change from step to step, so a captured HIP graph of training steps
  * can be replayed.  The update equals omprt_mlp_adam's at step t bit for
- * bit.  Stream-ordered; d_step 4-byte aligned.
+ * bit.  Stream-ordered, two launches, no workspace; d_step 4-byte aligned.
  */
 omprt_status omprt_mlp_adam_counted(float *d_params, float *d_m, float *d_v,
                                     const float *d_grads, int64_t n, int32_t *d_step,

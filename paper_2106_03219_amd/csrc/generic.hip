@@ -4,7 +4,9 @@
 // memory (the routines a compiled target region calls, paper sec. 2.1).
 // The other threads wait at the team barrier for work -- a state machine --
 // run their share of the loop and meet the main thread, which works on the
-// loop as thread 0 of the team, at the join barrier.  One launch runs the
+// loop as thread 0 of the team, at the join barrier.  Loops with no sequential
+// code between them that needs their results are handed out together.  One
+// launch runs the
 // whole region, however many parallel loops it has, so nothing returns to
 // the host between them.
 //
@@ -338,14 +340,14 @@ extern "C" omprt_status omprt_generic_power(const float* d_diag, float* d_v, int
         return fail(OMPRT_ERR_INVALID, "n = %lld outside 1..2^32", (long long)n);
     if (iters < 1) return fail(OMPRT_ERR_INVALID, "iters %d < 1", iters);
     if (teams < 0) return fail(OMPRT_ERR_INVALID, "teams %d < 0", teams);
-    // default shape (measured at 2^10..2^23 elements, 100 steps, us a step): one
+    // default shape (measured at 2^10..2^24 elements, 100 steps, us a step): one
     // team of 512 threads while its loops are shorter than an all-gather (2^15:
-    // 1.95 against 2.25 with 8 teams), else teams of 512 threads with 16
-    // elements a thread up to half the CUs (2^16: 2.26 with 8 teams, 2.40 with
-    // 64 of 256; 2^20: 2.71 with 128 teams, 3.12 with 256 of 256) and one a CU
-    // past that (2^21: 3.14; 2^23: 4.15 against 16.4 with 128, whose share no
-    // longer fits the registers), of 256 threads once the loops stream (2^24:
-    // 30.9 against 34.7)
+    // 2.12 against 2.41 with 8 teams), else teams of 512 threads with 16
+    // elements a thread up to half the CUs (2^16: 2.56 with 8 teams, 2.65 with
+    // 64 of 256; 2^20: 3.15 with 128 teams, 3.33 with 256 of 256) and one a CU
+    // past that (2^21: 3.47 against 3.67 with 128; 2^23: 4.47 against 17.0,
+    // whose share no longer fits the registers), of 256 threads once the loops
+    // stream (2^24: 30.8, 30.4 with 512)
     const bool auto_threads = threads == 0;
     const int64_t cus = device_cus();
     if (auto_threads) threads = teams > 1 || (teams == 0 && n > cus * 512 * 64) ? 256 : 512;

@@ -8,7 +8,7 @@
 // through the forward pass, the softmax cross-entropy and both input
 // gradients with every weight in LDS; mlp_grads_kernel forms every weight and
 // bias gradient and the mean loss.  (16-64-64-64, 256 rows: loss and gradients
-// and Adam 65.6 us with a launch for each matrix, 18.3 us now.)
+// and Adam 65.6 us with a launch for each matrix, 19.3 us now.)
 #pragma once
 #include "device.h"
 #include "lines.h"
@@ -383,7 +383,7 @@ __device__ __forceinline__ void grad_tile(const float* __restrict__ D, const flo
 // VEC (every layer's inputs whole 16-byte blocks): a lane takes four columns
 // of one row at a time, so a wave's load of A covers 1 KiB and its load of D
 // serves four to sixteen rows; the loads, not the 8 operations a product, are
-// what a row costs otherwise (256 rows 5.6 us; one column a lane 7.7, four
+// what a row costs otherwise (256 rows 5.9 us; one column a lane 7.7, four
 // rows of W a lane over a quarter of the workgroups 10.2).
 template <bool VEC>
 __global__ __launch_bounds__(kGradThreads) void mlp_grads_kernel(MlpGradPlan p,

@@ -27,9 +27,10 @@ constexpr int DT_COUNT_ABI = 5;   // OMPRT_I32 .. OMPRT_BF16
 int dtype_bytes(int dtype);         // storage bytes of an input element
 int out_bytes(int dtype, int op);   // bytes of x
 
-// Per (device, stream) workspace of the plain kernels: a 256-byte header
-// (election counter, launch epoch, status bits; zeroed once at allocation,
-// self-maintaining afterwards) followed by the tagged cross-team slots.
+// Per (device, stream) workspace of the plain kernels: a header of kHeaderBytes
+// (election counter, launch epoch, status bits, the election groups' counters;
+// zeroed once at allocation, self-maintaining afterwards) followed by the
+// tagged cross-team slots.
 struct Workspace {
     void* base = nullptr;
     int32_t capacity = 0;   // slots
