@@ -180,7 +180,8 @@ static LaunchCfg heuristic(int64_t n, int dtype, int body, int64_t chunk) {
         cap = cus;
     } else if (body && chunk > 512) {
         constexpr int64_t kLanes = 64;                                          // a wave
-        const int64_t waves = ((n + chunk - 1) / chunk + kLanes - 1) / kLanes;  // waves of chunks
+        const int64_t chunks = std::max<int64_t>((n + chunk - 1) / chunk, 1);   // n may be 0
+        const int64_t waves = (chunks + kLanes - 1) / kLanes;                   // waves of chunks
         if (waves >= 2 * cus) {
             c.threads = 512;
             t = (n + 128 * chunk - 1) / (128 * chunk);

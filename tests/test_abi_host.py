@@ -340,3 +340,12 @@ def test_udr_declare_compiles_and_reports_errors():
     cfg = om.Config(0, 0, 16, 0, 0, 0)
     assert lib.omprt_reduce_udr(h, None, 0, ctypes.byref(x), ctypes.byref(cfg), None) == _lib.ERR_INVALID
     assert lib.omprt_reduce_udr(h, None, 0, ctypes.byref(x), None, None) == _lib.OK   # n == 0
+
+
+@pytest.mark.parametrize("chunk", [0, 1, 2, 64, 512, 513, 600, 1 << 40])
+@pytest.mark.parametrize("n", [0, 1, 2])
+def test_heuristic_smallest_loops(n, chunk):
+    """The AXPY body's default launch of loops of no or few iterations: one team at least, whole
+    waves, whatever the chunk."""
+    cfg, src = om.resolve_config(n, om.F32, "sum", 1, chunk)
+    assert src == 3 and cfg["teams"] == 1 and cfg["threads"] in range(64, 1025, 64)

@@ -116,3 +116,17 @@ def test_axpy_2pow26_default_launch(gpu_lib, axpy_inputs, chunk):
     """The runtime's own choice of teams and threads (the configuration it times)."""
     x, y, ref = axpy_inputs
     _run(gpu_lib, x, y, 0, 0, 0, chunk, ref=ref)
+
+
+@pytest.mark.parametrize("chunk", [0, 1, 600, 5000])
+def test_axpy_of_no_iterations(gpu_lib, chunk):
+    """No iterations at the runtime's own launch: the sum keeps its value."""
+    om = gpu_lib
+    x = torch.zeros(0, dtype=torch.float32, device="cuda")
+    s = torch.tensor([2.5], dtype=torch.float32, device="cuda")
+    om.axpy_sum(A, x, x.clone(), s, chunk=chunk)
+    om.region_axpy_sum(A, x, x.clone(), s, chunk=chunk)
+    for kind in ("dynamic", "guided"):
+        om.axpy_sum_queue(kind, A, x, x.clone(), s, chunk=chunk)
+    torch.cuda.synchronize()
+    assert s.item() == 2.5
