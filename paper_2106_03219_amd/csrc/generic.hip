@@ -6,9 +6,8 @@
 // run their share of the loop and meet the main thread, which works on the
 // loop as thread 0 of the team, at the join barrier.  Loops with no sequential
 // code between them that needs their results are handed out together.  One
-// launch runs the
-// whole region, however many parallel loops it has, so nothing returns to
-// the host between them.
+// launch runs the whole region, however many parallel loops it has, so nothing
+// returns to the host between them.
 //
 // The region is a power iteration on a diagonal matrix D = diag(d):
 //   repeat iters times:

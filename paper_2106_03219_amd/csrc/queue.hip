@@ -483,9 +483,8 @@ extern "C" omprt_status omprt_axpy_sum_queue(float a, const float* d_x, float* d
     // 202 -> 186).  Chunk 16 ran alike through the union; those between one and
     // two segments gain and lose with the size (48: 2e6 14.4 -> 13.1, 7e6 29.4
     // -> 32.8, 2^25 115 -> 104), longer ones lose at 1e6 (80: 11.4 -> 14.2).
-    // Guided rounds, whose
-    // lanes' chunks shrink along the wave so that few have lines: 16 7e6 43.4
-    // -> 31.3, 2^24 67 -> 58; not from where the first chunks are long (2^25,
+    // Guided rounds, whose lanes' chunks shrink along the wave so that few have
+    // lines: 16 7e6 43.4 -> 31.3, 2^24 67 -> 58; not from where the first chunks are long (2^25,
     // 512 iterations: 107 -> 114; 2^26: 185 -> 228), for chunks past two
     // segments (100: 7e6 32.2 -> 36.3) or the smallest blocks (7: 1e5 10.0 ->
     // 11.9).
